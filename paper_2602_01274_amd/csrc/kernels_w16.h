@@ -636,6 +636,15 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 8 ? (NT >= 5 ? 2 : 4) : 1)) v
 // outstanding load at the join, which serialises the pipeline on memory latency): tiles or K steps that
 // do not exist are replaced by the nearest one that does, and their products are never stored.
 // Requires KT % (4*KS) == 0.
+
+// Where lane l of a staging load takes its 16 bytes of a 1 KiB operand tile ([row][64 bytes]), and where MFMA lane l finds
+// its own in the staged copy (units of 16 bytes).  A load's 16-lane quarter covers 4 whole rows = 256 contiguous bytes
+// (two cache lines); taking the tile in MFMA lane order instead makes every quarter touch all eight lines of the tile,
+// four times the work of the CU's memory pipeline.  Chunk c of row r sits in slot 4r + (c ^ (r/2 % 4)), so that the
+// eight lanes that one LDS read cycle serves (rows r..r+7, same chunk) fall on different banks.
+__device__ __forceinline__ int stage_src(int l) { return (l & ~3) + ((l & 3) ^ ((l >> 3) & 3)); }
+__device__ __forceinline__ int stage_slot(int l) { return (l & 15) * 4 + ((l >> 4) ^ ((l >> 1) & 3)); }
+
 template <int EPI, int NTW, int MTB, int HL, int TAG, int KS>
 __global__ __launch_bounds__(256 * KS, (KS == 1 ? 2 : 1)) void gemm_wide_kernel(const GemmArgs ga, int n_tiles, int n_groups, int row_groups) {
   constexpr int UA = 4, KC = UA / KS, BT = MTB * HL, BI = (BT + 3) / 4;
@@ -667,8 +676,9 @@ __global__ __launch_bounds__(256 * KS, (KS == 1 ? 2 : 1)) void gemm_wide_kernel(
 #pragma unroll
   for (int it = 0; it < BI; ++it) {
     const int tp = min(it * 4 + wave, BT - 1), b = min(tp / HL, mtb - 1), h = tp % HL;
-    xsrc[it] = ga.X + ((size_t)(mt_lo + b) * 2 + h) * 64 + (lane & 15) * 4 + (lane >> 4);
+    xsrc[it] = ga.X + ((size_t)(mt_lo + b) * 2 + h) * 64 + stage_src(lane);
   }
+  const int slot_rd = stage_slot(lane);
   const size_t xstep = (size_t)mtt * 128;                      // operand elements (16 B) per K step
   u32x4 Areg[UA][NTW], Breg[KC][BI];
   auto loadA = [&](u32x4(&A)[NTW], int k) {                    // plain loads: row groups sharing these tiles find them in L2
@@ -714,13 +724,13 @@ __global__ __launch_bounds__(256 * KS, (KS == 1 ? 2 : 1)) void gemm_wide_kernel(
       // operand tiles of K step j+1 are read from LDS before the products of step j are issued (two register sets)
       u32x4 bfr[2][BT];
 #pragma unroll
-      for (int t = 0; t < BT; ++t) bfr[0][t] = Bs[ks][buf][0][t][lane];
+      for (int t = 0; t < BT; ++t) bfr[0][t] = Bs[ks][buf][0][t][slot_rd];
 #pragma unroll
       for (int j = 0; j < KC; ++j) {
         const int u = ss * KC + j;
         if (j + 1 < KC) {
 #pragma unroll
-          for (int t = 0; t < BT; ++t) bfr[(j + 1) & 1][t] = Bs[ks][buf][j + 1][t][lane];
+          for (int t = 0; t < BT; ++t) bfr[(j + 1) & 1][t] = Bs[ks][buf][j + 1][t][slot_rd];
         }
         __builtin_amdgcn_sched_barrier(0);
         half8 af[NTW];
@@ -826,11 +836,12 @@ __global__ __launch_bounds__(512, 1) void gemm_wide8_kernel(const GemmArgs ga, i
   for (int it = 0; it < ITS; ++it) {
     const int ti = min(it * WV + wave, KC * BT - 1), j = ti / BT, t = ti % BT;
     const int b = min(t / HL, mtb - 1), h = t % HL;
-    xsrc[it] = ga.X + ((size_t)(mt_lo + b) * 2 + h) * 64 + (lane & 15) * 4 + (lane >> 4);
+    xsrc[it] = ga.X + ((size_t)(mt_lo + b) * 2 + h) * 64 + stage_src(lane);
     xj[it] = j;
     xdst[it] = (j * BT + t) * 64 + lane;
   }
   const size_t xstep = (size_t)mtt * 128;                    // operand elements (16 B) per K step
+  const int slot_rd = stage_slot(lane);
   u32x4 Areg[UA][NTW], Breg[ITS];
   auto loadA = [&](u32x4(&A)[NTW], int k) {
     const size_t o = (size_t)min(k, ke - 1) * 64;
@@ -866,7 +877,7 @@ __global__ __launch_bounds__(512, 1) void gemm_wide8_kernel(const GemmArgs ga, i
       // same registers: the LDS latency then shows once per tile and the matrix unit idles two thirds of the time).
       u32x4 bfr[2][BT];
       {
-        const u32x4* bsrc = wide8_stage + ((size_t)(buf * KC) * BT) * 64 + lane;
+        const u32x4* bsrc = wide8_stage + ((size_t)(buf * KC) * BT) * 64 + slot_rd;
 #pragma unroll
         for (int t = 0; t < BT; ++t) bfr[0][t] = bsrc[t * 64];
       }
@@ -874,7 +885,7 @@ __global__ __launch_bounds__(512, 1) void gemm_wide8_kernel(const GemmArgs ga, i
       for (int j = 0; j < KC; ++j) {
         const int u = ss * KC + j;
         if (j + 1 < KC) {
-          const u32x4* bsrc = wide8_stage + ((size_t)(buf * KC + j + 1) * BT) * 64 + lane;
+          const u32x4* bsrc = wide8_stage + ((size_t)(buf * KC + j + 1) * BT) * 64 + slot_rd;
 #pragma unroll
           for (int t = 0; t < BT; ++t) bfr[(j + 1) & 1][t] = bsrc[t * 64];
         }
