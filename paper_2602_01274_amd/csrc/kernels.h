@@ -47,6 +47,22 @@ __device__ __forceinline__ int find_seq(const SeqRows& sr, int r) {
   return s;
 }
 
+// The sequence of row r with what the launch says about it.  Every table read has the same index in all lanes (scalar
+// loads that do not wait for each other), where find_seq followed by look-ups is a chain of vector loads per lane.
+struct SeqOf { int si, seq, row0, pos0; };
+__device__ __forceinline__ SeqOf seq_of_row(const SeqRows& sr, int r) {
+  SeqOf o{0, sr.seq[0], sr.row_off[0], sr.pos0[0]};
+#pragma unroll
+  for (int s = 1; s < PK_MAXB; ++s) {
+    const bool in = s < sr.n_seqs && sr.row_off[s] <= r;
+    o.si = in ? s : o.si;
+    o.seq = in ? sr.seq[s] : o.seq;
+    o.row0 = in ? sr.row_off[s] : o.row0;
+    o.pos0 = in ? sr.pos0[s] : o.pos0;
+  }
+  return o;
+}
+
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
   uint32_t u = __float_as_uint(f);

@@ -130,6 +130,14 @@ __device__ __forceinline__ void store_packed4(_Float16* __restrict__ xp, int MT_
   *reinterpret_cast<half4*>(p + 512) = l;
 }
 
+// 2 consecutive features of row m
+__device__ __forceinline__ void store_packed2(_Float16* __restrict__ xp, int MT_total, int m, int k0, float a, float b) {
+  const half2v h = {(_Float16)a, (_Float16)b}, l = {(_Float16)(a - (float)h[0]), (_Float16)(b - (float)h[1])};
+  _Float16* p = xp + ((size_t)((k0 >> 5) * MT_total + (m >> 4)) * 128 + ((m & 15) * 4 + ((k0 & 31) >> 3))) * 8 + (k0 & 7);
+  *reinterpret_cast<half2v*>(p) = h;
+  *reinterpret_cast<half2v*>(p + 512) = l;
+}
+
 // x = E[token]; operand = f16(x * g); ssq slot 0 = sum x^2; the row's accumulators of the other slots are cleared.
 // cos/sin of every absolute position for a model's rotation frequencies, evaluated in double and rounded once:
 // tab[pos][j] = (cos, sin)(pos * theta^(-2j/hd)).  Filled when the workspace is bound; the QKV epilogue reads the
@@ -250,25 +258,92 @@ struct GemmArgs {
   uint64_t pick_seed;
   uint32_t pick_step;
   SeqRows sr;
-  // K split across blocks (streaming kernel, KSB > 1): per-block partial sums [group][KSB][NT*MT][64] f32x4
-  // and one arrival counter per group of output tiles (zero between launches)
+  // K split across blocks: per-block partial sums (streaming kernel, KSB > 1: [group][KSB][NT*MT][64] f32x4) and one
+  // arrival counter per group of output tiles (zero between launches)
   float* sk_part;
   unsigned* sk_cnt;
 };
 
-// Epilogue of one accumulator lane, shared by the GEMM kernels.  Lane l of a 16x16 result tile holds
-// tile rows (outputs) 4*(l/16)..+3 of activation row m; s2 holds the same for the partner outputs i+8
-// (paired weight layouts: rotation pairs of QKV, gate/up of SwiGLU; lanes with l/16 < 2).  All 64 lanes
-// of the tile call this together (the row reductions use wave shuffles).
+// What an epilogue needs to know about an activation row, looked up once per row and used for all its output tiles.
+struct RowCtx {
+  bool live;
+  float rs;              // row scale of the operand's RMSNorm (1 without one)
+  int si, rl, pos;       // QKV: sequence slot, row within the sequence, absolute position
+  _Float16* Kc;          // QKV: the (sequence, layer)'s K block; V follows
+};
 // ssq_pre: the row's sum of squares (the integer parts added up) if the caller fetched it ahead of time
 template <int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& ga, int nt, int m, int l, f32x4 s, f32x4 s2, const u64* ssq_pre = nullptr) {
-  const int g4 = l >> 4;
-  const bool live = m < ga.R;
-  float rs = 1.f;
-  if (ga.ssq_in && live)
-    rs = ssq_pre ? 1.0f / sqrtf((float)*ssq_pre * SSQ_INV_SCALE * ga.inv_dim + ga.eps) : row_scale(ga.ssq_in, ga.ssq_stride, m, ga.inv_dim, ga.eps);
+__device__ __forceinline__ RowCtx row_ctx(const GemmArgs& ga, int m, const u64* ssq_pre = nullptr) {
+  RowCtx rc{};
+  rc.live = m < ga.R;
+  rc.rs = 1.f;
+  if (ga.ssq_in && rc.live)
+    rc.rs = ssq_pre ? 1.0f / sqrtf((float)*ssq_pre * SSQ_INV_SCALE * ga.inv_dim + ga.eps) : row_scale(ga.ssq_in, ga.ssq_stride, m, ga.inv_dim, ga.eps);
+  if (EPI == EPI_QKV && rc.live) {
+    const SeqOf q = seq_of_row(ga.sr, m);
+    rc.si = q.si;
+    rc.rl = m - q.row0;
+    rc.pos = q.pos0 + rc.rl;
+    rc.Kc = ga.kv + (((size_t)q.seq * ga.n_layers + ga.layer) * 2) * (size_t)ga.max_seq * ga.d;
+  }
+  return rc;
+}
+// What an epilogue reads for one (tile, row): the old residual values and the next norm's gains (RESID), or cos and sin
+// of the tile's rotation pairs (QKV).  Kernels with several tiles per wave read them for all tiles before the first
+// result is stored: a load after a store that may alias it waits for its own memory round trip.
+struct EpiAux { f32x4 a, b; };
+template <int EPI>
+__device__ __forceinline__ EpiAux epi_aux(const GemmArgs& ga, const RowCtx& rc, int nt, int m, int l) {
+  EpiAux x{};
+  if (!rc.live) return x;
+  if (EPI == EPI_RESID) {
+    const int n = nt * 16 + (l >> 4) * 4;
+    x.a = *reinterpret_cast<const f32x4*>(ga.out + (size_t)m * ga.ldo + n);
+    x.b = *reinterpret_cast<const f32x4*>(ga.g_next + n);
+  } else if (EPI == EPI_QKV) {
+    const int tiles_d = ga.d >> 4, half = ga.hd >> 1;
+    if (nt < 2 * tiles_d) {
+      const int tph = ga.hd >> 4, j0 = 8 * ((nt >= tiles_d ? nt - tiles_d : nt) % tph) + 4 * ((l >> 4) & 1);
+      const f32x4* tb = reinterpret_cast<const f32x4*>(ga.rope + ((size_t)rc.pos * half + j0) * 2);
+      x.a = tb[0];
+      x.b = tb[1];
+    }
+  }
+  return x;
+}
+// sum of a row's squares over the tile's outputs into the row's accumulator (all 64 lanes call it; sq: this lane's part)
+__device__ __forceinline__ void add_row_ssq(const GemmArgs& ga, const RowCtx& rc, int m, int l, float sq) {
+  sq += __shfl_xor(sq, 16, 64);
+  sq += __shfl_xor(sq, 32, 64);
+  if (rc.live && (l >> 4) == 0) atomicAdd(ga.ssq_out + (size_t)(blockIdx.x % SSQ_SUB) * ga.ssq_stride + m, (u64)(sq * SSQ_SCALE + 0.5f));
+}
+// 4 x 4 transpose of v among the four lanes of a quad: lane i gets v[i] of lanes 0..3
+__device__ __forceinline__ void quad_transpose(float (&v)[4], int l) {
+#pragma unroll
+  for (int o = 1; o <= 2; o <<= 1) {
+    const bool up = l & o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i & o) continue;
+      const float got = __shfl_xor(up ? v[i] : v[i + o], o, 64);
+      v[i] = up ? got : v[i];
+      v[i + o] = up ? v[i + o] : got;
+    }
+  }
+}
 
+// Epilogue of one accumulator lane, shared by the GEMM kernels.  Lane l of a 16x16 result tile holds tile rows (outputs)
+// 4*(l/16)..+3 of activation row m; s2 holds the same of lane l ^ 32, whose outputs are the partners i+8 resp. i-8
+// (paired weight layouts: rotation pairs of QKV, gate/up of SwiGLU).  All 64 lanes of the tile call this together.
+// RESID returns the lane's part of the row's sum of squares, for add_row_ssq.
+// VT: rows of a tile may be 16 consecutive positions (prompt rows): V is stored 4 positions at a time where they are.
+template <int EPI, bool VT = false>
+__device__ __forceinline__ float gemm_epilogue(const GemmArgs& ga, const RowCtx& rc, const EpiAux& ax, int nt, int m, int l, f32x4 s, f32x4 s2) {
+  typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+  const int g4 = l >> 4;
+  const bool live = rc.live;
+  const float rs = rc.rs;
+  float sq = 0.f;
   if (EPI == EPI_STORE) {
     const int n = nt * 16 + g4 * 4;
     const f32x4 lg = s * rs;
@@ -307,83 +382,83 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& ga, int nt, int m,
       }
     }
   } else if (EPI == EPI_RESID) {
-    float sq = 0.f;
     if (live) {
       const int n = nt * 16 + g4 * 4;
       float* o = ga.out + (size_t)m * ga.ldo + n;
-      const f32x4 xn = *reinterpret_cast<const f32x4*>(o) + s;
+      const f32x4 xn = ax.a + s, gn = ax.b;
       *reinterpret_cast<f32x4*>(o) = xn;
-      const float4 gn = *reinterpret_cast<const float4*>(ga.g_next + n);
-      store_packed4(ga.xp_out, ga.mt_total_out, m, n, xn[0] * gn.x, xn[1] * gn.y, xn[2] * gn.z, xn[3] * gn.w);
+      store_packed4(ga.xp_out, ga.mt_total_out, m, n, xn[0] * gn[0], xn[1] * gn[1], xn[2] * gn[2], xn[3] * gn[3]);
       sq = xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
     }
-    sq += __shfl_xor(sq, 16, 64);
-    sq += __shfl_xor(sq, 32, 64);
-    if (live && g4 == 0) atomicAdd(ga.ssq_out + (size_t)(blockIdx.x % SSQ_SUB) * ga.ssq_stride + m, (u64)(sq * SSQ_SCALE + 0.5f));
   } else if (EPI == EPI_SWIGLU) {
-    if (live && g4 < 2) {
-      const int f = nt * 8 + g4 * 4;
-      float v[4];
+    // lanes l and l ^ 32 hold gate and up of the same four features: each takes two of them
+    if (live) {
+      const bool up_lane = g4 >= 2;
+      const int r0 = up_lane ? 2 : 0;
+      float v[2];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float gt = s[r] * rs, up = s2[r] * rs;
+      for (int r = 0; r < 2; ++r) {
+        const float gt = (up_lane ? s2[r + 2] : s[r]) * rs, up = (up_lane ? s[r + 2] : s2[r]) * rs;
         v[r] = gt / (1.0f + expf(-gt)) * up;
       }
-      store_packed4(ga.xp_out, ga.mt_total_out, m, f, v[0], v[1], v[2], v[3]);
+      store_packed2(ga.xp_out, ga.mt_total_out, m, nt * 8 + (g4 & 1) * 4 + r0, v[0], v[1]);
     }
   } else {  // EPI_QKV
-    if (live) {
-      const int d = ga.d, hd = ga.hd, half = hd >> 1;
-      const int si = find_seq(ga.sr, m);
-      const int rl = m - ga.sr.row_off[si];
-      const int pos = ga.sr.pos0[si] + rl;
-      _Float16* Kc = ga.kv + (((size_t)ga.sr.seq[si] * ga.n_layers + ga.layer) * 2) * (size_t)ga.max_seq * d;
-      _Float16* Vt = Kc + (size_t)ga.max_seq * d;
-      const int tiles_d = d >> 4;
-      typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-      if (nt < 2 * tiles_d) {
-        if (g4 < 2) {
-          const int part = nt / tiles_d;
-          const int tq = nt - part * tiles_d;
-          const int tph = hd >> 4;
-          const int h = tq / tph, tt = tq % tph;
-          const int j0 = 8 * tt + 4 * g4;                   // rotation pairs j0..j0+3
-          const float* tb = ga.rope + ((size_t)pos * half + j0) * 2;
-          float va[4], vb[4];
+    const int d = ga.d, hd = ga.hd, half = hd >> 1;
+    const int tiles_d = d >> 4;
+    if (nt < 2 * tiles_d) {
+      if (live) {
+        // lane l ^ 32 holds the other members of the rotation pairs: lanes with g4 < 2 produce dims j0.., the others j0 + hd/2..
+        const int part = nt / tiles_d;
+        const int tq = nt - part * tiles_d;
+        const int tph = hd >> 4;
+        const int h = tq / tph, tt = tq % tph;
+        const int j0 = 8 * tt + 4 * (g4 & 1);             // rotation pairs j0..j0+3
+        const bool second = g4 >= 2;
+        const int dim = j0 + (second ? half : 0);
+        const float cs[4] = {ax.a[0], ax.a[2], ax.b[0], ax.b[2]}, sn[4] = {ax.a[1], ax.a[3], ax.b[1], ax.b[3]};
+        float v[4];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float cs = tb[2 * r], sn = tb[2 * r + 1];
-            const float x0 = s[r] * rs, x1 = s2[r] * rs;
-            va[r] = x0 * cs - x1 * sn;
-            vb[r] = x1 * cs + x0 * sn;
-          }
-          const half4 ha = {(_Float16)va[0], (_Float16)va[1], (_Float16)va[2], (_Float16)va[3]};
-          const half4 hb = {(_Float16)vb[0], (_Float16)vb[1], (_Float16)vb[2], (_Float16)vb[3]};
-          if (part == 0) {
-            // attention operand: [slot][head][kt][2 row tiles][hi|lo][lane][8], lane = 16*(dim%32/8) + row%16
-            const int kts = hd >> 5;
-            auto qidx = [&](int dim) {
-              return ((((size_t)si * ga.H + h) * kts + (dim >> 5)) * 2 + (rl >> 4)) * 1024 + (((dim & 31) >> 3) * 16 + (rl & 15)) * 8 + (dim & 7);
-            };
-            const half4 la = {(_Float16)(va[0] - (float)ha[0]), (_Float16)(va[1] - (float)ha[1]), (_Float16)(va[2] - (float)ha[2]), (_Float16)(va[3] - (float)ha[3])};
-            const half4 lb = {(_Float16)(vb[0] - (float)hb[0]), (_Float16)(vb[1] - (float)hb[1]), (_Float16)(vb[2] - (float)hb[2]), (_Float16)(vb[3] - (float)hb[3])};
-            *reinterpret_cast<half4*>(ga.qp + qidx(j0)) = ha;
-            *reinterpret_cast<half4*>(ga.qp + qidx(j0) + 512) = la;
-            *reinterpret_cast<half4*>(ga.qp + qidx(j0 + half)) = hb;
-            *reinterpret_cast<half4*>(ga.qp + qidx(j0 + half) + 512) = lb;
-          } else {
-            *reinterpret_cast<half4*>(Kc + kcache_index(h, hd, ga.max_seq, pos, j0)) = ha;
-            *reinterpret_cast<half4*>(Kc + kcache_index(h, hd, ga.max_seq, pos, j0 + half)) = hb;
-          }
+        for (int r = 0; r < 4; ++r) {
+          const float mine = s[r] * rs, other = s2[r] * rs;
+          v[r] = second ? mine * cs[r] + other * sn[r] : mine * cs[r] - other * sn[r];
         }
-      } else {
-        const int c0 = (nt - 2 * tiles_d) * 16 + g4 * 4;       // V feature index
-        const int h = c0 / hd, f0 = c0 - h * hd;
+        const half4 hi = {(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+        if (part == 0) {
+          // attention operand: [slot][head][kt][2 row tiles][hi|lo][lane][8], lane = 16*(dim%32/8) + row%16
+          const half4 lo = {(_Float16)(v[0] - (float)hi[0]), (_Float16)(v[1] - (float)hi[1]), (_Float16)(v[2] - (float)hi[2]), (_Float16)(v[3] - (float)hi[3])};
+          _Float16* q = ga.qp + ((((size_t)rc.si * ga.H + h) * (hd >> 5) + (dim >> 5)) * 2 + (rc.rl >> 4)) * 1024 + (((dim & 31) >> 3) * 16 + (rc.rl & 15)) * 8 + (dim & 7);
+          *reinterpret_cast<half4*>(q) = hi;
+          *reinterpret_cast<half4*>(q + 512) = lo;
+        } else {
+          *reinterpret_cast<half4*>(rc.Kc + kcache_index(h, hd, ga.max_seq, rc.pos, dim)) = hi;
+        }
+      }
+    } else {
+      _Float16* Vt = rc.Kc + (size_t)ga.max_seq * d;
+      const int c0 = (nt - 2 * tiles_d) * 16 + g4 * 4;     // V feature index
+      const int h = c0 / hd, f0 = c0 - h * hd;
+      float v[4] = {s[0] * rs, s[1] * rs, s[2] * rs, s[3] * rs};
+      bool quad = false;
+      if (VT) {
+        // the quad's rows are four live positions 4i..4i+3 of one sequence (rows ascend, so the last one decides)
+        const int last = l | 3;
+        const bool same = __shfl((int)live, last, 64) && __shfl(rc.si, last, 64) == rc.si && __shfl(rc.si, l & ~3, 64) == rc.si;
+        quad = same && (rc.pos & 3) == (l & 3);
+        float t[4] = {v[0], v[1], v[2], v[3]};
+        quad_transpose(t, l);
+        if (quad) {
+          const half4 hv = {(_Float16)t[0], (_Float16)t[1], (_Float16)t[2], (_Float16)t[3]};
+          *reinterpret_cast<half4*>(Vt + vcache_index(h, hd, ga.max_seq, rc.pos & ~3, f0 + (l & 3))) = hv;
+        }
+      }
+      if (live && !quad) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Vt[vcache_index(h, hd, ga.max_seq, pos, f0 + r)] = (_Float16)(s[r] * rs);
+        for (int r = 0; r < 4; ++r) Vt[vcache_index(h, hd, ga.max_seq, rc.pos, f0 + r)] = (_Float16)v[r];
       }
     }
   }
+  return sq;
 }
 
 // X17 = 1 (with MT = 2): the launch covers exactly 17 rows (a full draft window plus the committed
@@ -600,372 +675,23 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 8 ? (NT >= 5 ? 2 : 4) : 1)) v
     f32x4 s = red[0][ab][l];
 #pragma unroll
     for (int w = 1; w < NRED; ++w) s += red[w][ab][l];
-    f32x4 s2 = {0.f, 0.f, 0.f, 0.f};                   // partner rows i+8 (paired layouts, threads with g4 < 2)
-    if (paired && g4 < 2) {
-      s2 = red[0][ab][l + 32];
+    f32x4 s2 = {0.f, 0.f, 0.f, 0.f};                   // partner rows (paired layouts)
+    if (paired) {
+      s2 = red[0][ab][l ^ 32];
 #pragma unroll
-      for (int w = 1; w < NRED; ++w) s2 += red[w][ab][l + 32];
+      for (int w = 1; w < NRED; ++w) s2 += red[w][ab][l ^ 32];
     }
     if (X17 && HL == 2 && b == 1 && (l & 15) == 0) {   // row 16: hi product in column 0, lo product in column 1
 #pragma unroll
       for (int w = 0; w < NRED; ++w) s += red[w][ab][l + 1];
-      if (paired && g4 < 2) {
-#pragma unroll
-        for (int w = 0; w < NRED; ++w) s2 += red[w][ab][l + 33];
-      }
-    }
-    gemm_epilogue<EPI>(ga, nt, m, l, s, s2, &ssq_sum);
-  }
-}
-
-// ------------------------------------------------------------------ wide GEMM: more than 32 rows
-// Batched verification puts up to 16 x 17 rows through the target model; at that width the product is
-// bound by the matrix units and by operand delivery, not by the weight stream, so the roles change:
-//   block  = KS K-slices x 4 waves; a slice's 4 waves own 4*NTW output tiles x MTB row tiles over
-//            their 1/KS of K, walked in super-steps of KC = 4/KS K steps; the slices' sums meet in LDS
-//   weights: each wave streams its own NTW tiles into registers, 4 K steps ahead
-//   operand: a slice's MTB*HL tiles of a super-step are fetched once (two super-steps ahead), written
-//            to LDS in MFMA lane order (double buffered, one barrier per super-step) and read by the
-//            slice's four waves, so each operand byte feeds 4*NTW tiles and each weight byte MTB*HL MFMAs
-// KS > 1 is for matrices with few output tiles (O and down projections): it is what puts 8 waves on a CU
-// when there are fewer blocks than CUs, and a wave alone on its SIMD cannot hide the weight stream's latency.
-// Blocks that share weights (same output tiles, different rows) get consecutive slots on one XCD
-// (block id mod 8 picks the XCD), so the weight stream of the later ones comes from that XCD's L2
-// (measured: 1.2 to 1.5 x the weight bytes from HBM with three row groups).
-// The K loop has no branches and no conditional loads (a branch makes the compiler wait for every
-// outstanding load at the join, which serialises the pipeline on memory latency): tiles or K steps that
-// do not exist are replaced by the nearest one that does, and their products are never stored.
-// Requires KT % (4*KS) == 0.
-
-// Where lane l of a staging load takes its 16 bytes of a 1 KiB operand tile ([row][64 bytes]), and where MFMA lane l finds
-// its own in the staged copy (units of 16 bytes).  A load's 16-lane quarter covers 4 whole rows = 256 contiguous bytes
-// (two cache lines); taking the tile in MFMA lane order instead makes every quarter touch all eight lines of the tile,
-// four times the work of the CU's memory pipeline.  Chunk c of row r sits in slot 4r + (c ^ (r/2 % 4)), so that the
-// eight lanes that one LDS read cycle serves (rows r..r+7, same chunk) fall on different banks.
-__device__ __forceinline__ int stage_src(int l) { return (l & ~3) + ((l & 3) ^ ((l >> 3) & 3)); }
-__device__ __forceinline__ int stage_slot(int l) { return (l & 15) * 4 + ((l >> 4) ^ ((l >> 1) & 3)); }
-
-template <int EPI, int NTW, int MTB, int HL, int TAG, int KS>
-__global__ __launch_bounds__(256 * KS, (KS == 1 ? 2 : 1)) void gemm_wide_kernel(const GemmArgs ga, int n_tiles, int n_groups, int row_groups) {
-  constexpr int UA = 4, KC = UA / KS, BT = MTB * HL, BI = (BT + 3) / 4;
-  __shared__ u32x4 Bs[KS][2][KC][BI * 4][64];
-  static_assert(KS == 1 || 4 * NTW * MTB <= KS * 2 * KC * BI * 4, "slice sums reuse the operand buffers");
-  // wave-uniform ids as scalars, so that tile pointers and K offsets live in scalar registers
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wave = wid & 3, ks = wid >> 2, lane = threadIdx.x & 63;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int rg = slot % row_groups, ng = (slot / row_groups) * 8 + xcd;
-  if (ng >= n_groups) return;
-  const int mtt = ga.mt_total;
-  const int mt_lo = mtt * rg / row_groups;
-  const int mtb = mtt * (rg + 1) / row_groups - mt_lo;       // row tiles of this block, 1..MTB
-  const int nt0 = ga.nt_begin + (ng * 4 + wave) * NTW;
-  const int nt_end = ga.nt_begin + n_tiles;
-  const int KT = ga.KT, kb = ks * (KT / KS), ke = kb + KT / KS;
-
-  f32x4 acc[NTW][MTB];
-#pragma unroll
-  for (int a = 0; a < NTW; ++a)
-#pragma unroll
-    for (int b = 0; b < MTB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const u32x4* wp[NTW];
-#pragma unroll
-  for (int a = 0; a < NTW; ++a) wp[a] = ga.W + (size_t)min(nt0 + a, nt_end - 1) * KT * 64 + lane;
-  // operand staging: wave w copies tile-parts w, w+4, ...; lane 16g+j reads row j's bytes 16g..16g+15
-  const u32x4* xsrc[BI];
-#pragma unroll
-  for (int it = 0; it < BI; ++it) {
-    const int tp = min(it * 4 + wave, BT - 1), b = min(tp / HL, mtb - 1), h = tp % HL;
-    xsrc[it] = ga.X + ((size_t)(mt_lo + b) * 2 + h) * 64 + stage_src(lane);
-  }
-  const int slot_rd = stage_slot(lane);
-  const size_t xstep = (size_t)mtt * 128;                      // operand elements (16 B) per K step
-  u32x4 Areg[UA][NTW], Breg[KC][BI];
-  auto loadA = [&](u32x4(&A)[NTW], int k) {                    // plain loads: row groups sharing these tiles find them in L2
-    const size_t o = (size_t)min(k, ke - 1) * 64;
-#pragma unroll
-    for (int a = 0; a < NTW; ++a) A[a] = wp[a][o];
-  };
-  auto loadB = [&](u32x4(&B)[BI], int k) {
-    const size_t o = (size_t)min(k, ke - 1) * xstep;
-#pragma unroll
-    for (int it = 0; it < BI; ++it) B[it] = xsrc[it][o];
-  };
-  auto storeB = [&](int buf) {
-#pragma unroll
-    for (int j = 0; j < KC; ++j)
-#pragma unroll
-      for (int it = 0; it < BI; ++it) Bs[ks][buf][j][it * 4 + wave][lane] = Breg[j][it];
-  };
-  // Prologue: operand of super-step 0 into LDS, of super-step 1 into registers; weights of 4 steps.
-  // Loads are issued in the order the loop issues them (operand, then weights step by step) and the
-  // scheduler is told not to move them (sched_barrier): the load counter completes in order, so a wait
-  // for an older load can leave the newer ones in flight only if the order is the same on every path into
-  // the loop.  Left to itself the compiler gathered all loads at the end of the loop body and waited for
-  // every one of them at the top (1.3 to 1.5 x slower).
-#pragma unroll
-  for (int j = 0; j < KC; ++j) loadB(Breg[j], kb + j);
-  storeB(0);
-#pragma unroll
-  for (int j = 0; j < KC; ++j) loadB(Breg[j], kb + KC + j);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int u = 0; u < UA; ++u) loadA(Areg[u], kb + u);
-  __builtin_amdgcn_sched_barrier(0);
-  __syncthreads();
-  int buf = 0;
-  for (int k0 = kb; k0 < ke; k0 += UA) {
-#pragma unroll
-    for (int ss = 0; ss < UA / KC; ++ss) {
-      storeB(buf ^ 1);                                         // operand of the next super-step
-#pragma unroll
-      for (int j = 0; j < KC; ++j) loadB(Breg[j], k0 + ss * KC + 2 * KC + j);
-      __builtin_amdgcn_sched_barrier(0);
-      // operand tiles of K step j+1 are read from LDS before the products of step j are issued (two register sets)
-      u32x4 bfr[2][BT];
-#pragma unroll
-      for (int t = 0; t < BT; ++t) bfr[0][t] = Bs[ks][buf][0][t][slot_rd];
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        const int u = ss * KC + j;
-        if (j + 1 < KC) {
-#pragma unroll
-          for (int t = 0; t < BT; ++t) bfr[(j + 1) & 1][t] = Bs[ks][buf][j + 1][t][slot_rd];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        half8 af[NTW];
-#pragma unroll
-        for (int a = 0; a < NTW; ++a) af[a] = __builtin_bit_cast(half8, Areg[u][a]);
-#pragma unroll
-        for (int t = 0; t < BT; ++t)
-#pragma unroll
-          for (int a = 0; a < NTW; ++a)
-            acc[a][t / HL] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[a], __builtin_bit_cast(half8, bfr[j & 1][t]), acc[a][t / HL], 0, 0, 0);
-        // the step's weight registers are free now: refill them for the step UA ahead (after the products, so
-        // that the loads land in the same registers and need no copies at the loop's back edge)
-        loadA(Areg[u], k0 + UA + u);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      __syncthreads();
-      buf ^= 1;
-    }
-  }
-  if (KS > 1) {
-    // slices 1.. hand their sums to slice 0 through the (now idle) operand buffers, one slice at a time, in slice order
-    f32x4* red = reinterpret_cast<f32x4*>(&Bs[0][0][0][0][0]);
-#pragma unroll
-    for (int s = 1; s < KS; ++s) {
-      if (ks == s) {
-#pragma unroll
-        for (int a = 0; a < NTW; ++a)
-#pragma unroll
-          for (int b = 0; b < MTB; ++b) red[((wave * NTW + a) * MTB + b) * 64 + lane] = acc[a][b];
-      }
-      __syncthreads();
-      if (ks == 0) {
-#pragma unroll
-        for (int a = 0; a < NTW; ++a)
-#pragma unroll
-          for (int b = 0; b < MTB; ++b) acc[a][b] += red[((wave * NTW + a) * MTB + b) * 64 + lane];
-      }
-      __syncthreads();
-    }
-    if (ks > 0) return;
-  }
-
-  constexpr bool paired = (EPI == EPI_SWIGLU) || (EPI == EPI_QKV);
-#pragma unroll
-  for (int a = 0; a < NTW; ++a) {
-    if (nt0 + a >= nt_end) continue;
-#pragma unroll
-    for (int b = 0; b < MTB; ++b) {
-      if (b >= mtb) continue;
-      const f32x4 s = acc[a][b];
-      f32x4 s2 = {0.f, 0.f, 0.f, 0.f};
       if (paired) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s2[r] = __shfl(s[r], (lane + 32) & 63, 64);
+        for (int w = 0; w < NRED; ++w) s2 += red[w][ab][(l ^ 32) + 1];
       }
-      gemm_epilogue<EPI>(ga, nt0 + a, (mt_lo + b) * 16 + (lane & 15), lane, s, s2);
     }
-  }
-}
-
-// ------------------------------------------------------------------ wide GEMM, few output tiles: K slices across blocks
-// The O and down projections of a batched verification pass (about 100..200 rows) have only a few hundred
-// output tiles; with the kernel above their blocks either cover few rows (the weights are then read once per
-// row group) or are too few for the CUs.  Here a block is 8 waves that share ONE operand stage (wave w owns
-// NTW output tiles, all MTB row tiles of the block), so an operand byte feeds 8*NTW tiles, and K is split
-// over KSB blocks whose partial tiles are added by the block that finishes last (write-through stores,
-// counter, L2-bypassing loads: see gemm_w16_kernel).  Measured at d 5120, K 13824, 128 rows: 53 us against
-// 75 us for the best shape of the kernel above; 144 rows: 63 against 80 us.
-//   grid = ceil(groups / 8) * 8 * row_groups * KSB, block id -> (XCD = id % 8, then row group, K slice, group)
-//   dynamic LDS = 2 * KC * MTB * HL KiB (operand of two super-steps of KC K steps)
-// Requires KT % 4 == 0 and KT / 4 >= KSB.
-template <int EPI, int NTW, int MTB, int HL, int TAG, int KC, int KSB>
-__global__ __launch_bounds__(512, 1) void gemm_wide8_kernel(const GemmArgs ga, int n_tiles, int n_groups, int row_groups) {
-  constexpr int WV = 8, UA = 4, BT = MTB * HL, ITS = (KC * BT + WV - 1) / WV;
-  static_assert(UA % KC == 0, "super-steps divide the weight prefetch depth");
-  extern __shared__ __align__(16) u32x4 wide8_stage[];     // [2][KC][BT][64]
-  __shared__ unsigned arrived;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int rg = slot % row_groups, ksl = (slot / row_groups) % KSB, ng = (slot / (row_groups * KSB)) * 8 + xcd;
-  if (ng >= n_groups) return;
-  const int mtt = ga.mt_total;
-  const int mt_lo = mtt * rg / row_groups;
-  const int mtb = mtt * (rg + 1) / row_groups - mt_lo;       // row tiles of this block, 1..MTB
-  const int nt0 = ga.nt_begin + (ng * WV + wave) * NTW;
-  const int nt_end = ga.nt_begin + n_tiles;
-  const int units = ga.KT / UA;
-  const int kb = (int)((long)ksl * units / KSB) * UA, ke = (int)((long)(ksl + 1) * units / KSB) * UA;
-
-  f32x4 acc[NTW][MTB];
-#pragma unroll
-  for (int a = 0; a < NTW; ++a)
-#pragma unroll
-    for (int b = 0; b < MTB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const u32x4* wp[NTW];
-#pragma unroll
-  for (int a = 0; a < NTW; ++a) wp[a] = ga.W + (size_t)min(nt0 + a, nt_end - 1) * ga.KT * 64 + lane;
-  // operand staging: the KC*BT tile-parts of a super-step are dealt to the 8 waves round-robin; a part past
-  // the last repeats it (same data to the same LDS slot), a row tile past the block's last repeats that one
-  const u32x4* xsrc[ITS];
-  int xj[ITS], xdst[ITS];
-#pragma unroll
-  for (int it = 0; it < ITS; ++it) {
-    const int ti = min(it * WV + wave, KC * BT - 1), j = ti / BT, t = ti % BT;
-    const int b = min(t / HL, mtb - 1), h = t % HL;
-    xsrc[it] = ga.X + ((size_t)(mt_lo + b) * 2 + h) * 64 + stage_src(lane);
-    xj[it] = j;
-    xdst[it] = (j * BT + t) * 64 + lane;
-  }
-  const size_t xstep = (size_t)mtt * 128;                    // operand elements (16 B) per K step
-  const int slot_rd = stage_slot(lane);
-  u32x4 Areg[UA][NTW], Breg[ITS];
-  auto loadA = [&](u32x4(&A)[NTW], int k) {
-    const size_t o = (size_t)min(k, ke - 1) * 64;
-#pragma unroll
-    for (int a = 0; a < NTW; ++a) A[a] = wp[a][o];
-  };
-  auto loadB = [&](int k) {
-#pragma unroll
-    for (int it = 0; it < ITS; ++it) Breg[it] = xsrc[it][(size_t)min(k + xj[it], ke - 1) * xstep];
-  };
-  auto storeB = [&](int buf) {
-#pragma unroll
-    for (int it = 0; it < ITS; ++it) wide8_stage[(size_t)buf * KC * BT * 64 + xdst[it]] = Breg[it];
-  };
-  // same load order in the prologue and in the loop, pinned (see gemm_wide_kernel)
-  loadB(kb);
-  storeB(0);
-  loadB(kb + KC);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int u = 0; u < UA; ++u) loadA(Areg[u], kb + u);
-  __builtin_amdgcn_sched_barrier(0);
-  __syncthreads();
-  int buf = 0;
-  for (int k0 = kb; k0 < ke; k0 += UA) {
-#pragma unroll
-    for (int ss = 0; ss < UA / KC; ++ss) {
-      storeB(buf ^ 1);                                       // operand of the next super-step
-      loadB(k0 + ss * KC + 2 * KC);
-      __builtin_amdgcn_sched_barrier(0);
-      // The operand tiles of K step j+1 are read from LDS into a second register set before the products of
-      // step j are issued (with one set the compiler reads a tile, waits, multiplies, reads the next into the
-      // same registers: the LDS latency then shows once per tile and the matrix unit idles two thirds of the time).
-      u32x4 bfr[2][BT];
-      {
-        const u32x4* bsrc = wide8_stage + ((size_t)(buf * KC) * BT) * 64 + slot_rd;
-#pragma unroll
-        for (int t = 0; t < BT; ++t) bfr[0][t] = bsrc[t * 64];
-      }
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        const int u = ss * KC + j;
-        if (j + 1 < KC) {
-          const u32x4* bsrc = wide8_stage + ((size_t)(buf * KC + j + 1) * BT) * 64 + slot_rd;
-#pragma unroll
-          for (int t = 0; t < BT; ++t) bfr[(j + 1) & 1][t] = bsrc[t * 64];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        half8 af[NTW];
-#pragma unroll
-        for (int a = 0; a < NTW; ++a) af[a] = __builtin_bit_cast(half8, Areg[u][a]);
-#pragma unroll
-        for (int t = 0; t < BT; ++t) {
-          const half8 bf = __builtin_bit_cast(half8, bfr[j & 1][t]);
-#pragma unroll
-          for (int a = 0; a < NTW; ++a) acc[a][t / HL] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[a], bf, acc[a][t / HL], 0, 0, 0);
-        }
-        loadA(Areg[u], k0 + UA + u);                         // refill after the products: same registers, no copies
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      __syncthreads();
-      buf ^= 1;
-    }
-  }
-  if (KSB > 1) {
-    // partial tiles of this K slice, written through to memory; whoever arrives last adds all slices in slice order
-    u64* part = reinterpret_cast<u64*>(ga.sk_part);
-    const size_t per_block = (size_t)WV * NTW * MTB * 64 * 2;          // 8-byte words per block
-    const size_t gidx = (size_t)ng * row_groups + rg;
-    u64* mine = part + (gidx * KSB + ksl) * per_block + ((size_t)wave * NTW * MTB * 64 + lane) * 2;
-#pragma unroll
-    for (int a = 0; a < NTW; ++a)
-#pragma unroll
-      for (int b = 0; b < MTB; ++b) {
-        const float2 lo = {acc[a][b][0], acc[a][b][1]}, hi = {acc[a][b][2], acc[a][b][3]};
-        u64* d = mine + (size_t)(a * MTB + b) * 128;
-        __hip_atomic_store(d, __builtin_bit_cast(u64, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(d + 1, __builtin_bit_cast(u64, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    PACER_WAIT_VMCNT0();   // this wave's write-through stores have completed
-    __syncthreads();
-    if (threadIdx.x == 0) arrived = __hip_atomic_fetch_add(ga.sk_cnt + gidx, 1u, PACER_HO_ORDER, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (arrived != KSB - 1) return;
-    if (threadIdx.x == 0) __hip_atomic_store(ga.sk_cnt + gidx, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int a = 0; a < NTW; ++a)
-#pragma unroll
-      for (int b = 0; b < MTB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < KSB; ++s) {
-      const u64* src = part + (gidx * KSB + s) * per_block + ((size_t)wave * NTW * MTB * 64 + lane) * 2;
-      u64 v0[NTW][MTB], v1[NTW][MTB];
-#pragma unroll
-      for (int a = 0; a < NTW; ++a)
-#pragma unroll
-        for (int b = 0; b < MTB; ++b) {
-          v0[a][b] = __hip_atomic_load(src + (size_t)(a * MTB + b) * 128, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          v1[a][b] = __hip_atomic_load(src + (size_t)(a * MTB + b) * 128 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-#pragma unroll
-      for (int a = 0; a < NTW; ++a)
-#pragma unroll
-        for (int b = 0; b < MTB; ++b) {
-          const float2 lo = __builtin_bit_cast(float2, v0[a][b]), hi = __builtin_bit_cast(float2, v1[a][b]);
-          acc[a][b] += f32x4{lo.x, lo.y, hi.x, hi.y};
-        }
-    }
-  }
-  constexpr bool paired = (EPI == EPI_SWIGLU) || (EPI == EPI_QKV);
-#pragma unroll
-  for (int a = 0; a < NTW; ++a) {
-    if (nt0 + a >= nt_end) continue;
-#pragma unroll
-    for (int b = 0; b < MTB; ++b) {
-      if (b >= mtb) continue;
-      const f32x4 s = acc[a][b];
-      f32x4 s2 = {0.f, 0.f, 0.f, 0.f};
-      if (paired) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s2[r] = __shfl(s[r], (lane + 32) & 63, 64);
-      }
-      gemm_epilogue<EPI>(ga, nt0 + a, (mt_lo + b) * 16 + (lane & 15), lane, s, s2);
-    }
+    const RowCtx rc = row_ctx<EPI>(ga, m, &ssq_sum);
+    const float sq = gemm_epilogue<EPI>(ga, rc, epi_aux<EPI>(ga, rc, nt, m, l), nt, m, l, s, s2);
+    if (EPI == EPI_RESID) add_row_ssq(ga, rc, m, l, sq);
   }
 }
 

@@ -4,6 +4,7 @@
 #include "../../include/pacer.h"
 #include "kernels.h"
 #include "kernels_w16.h"
+#include "kernels_tile.h"
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -187,8 +188,8 @@ size_t carve(pacer_ctx* c, void* base) {
   c->ssq = k.take<u64>((size_t)(2 * c->lmax + 1) * SSQ_SUB * c->rcap);
   c->pick_val = k.take<float>((size_t)c->max_batch * (V / 16 + 1));
   c->pick_idx = k.take<int>((size_t)c->max_batch * (V / 16 + 1));
-  // streaming kernel: kSplitPartFloats; wide kernel with K slices: up to 3 slices x padded rows x padded outputs (d wide)
-  c->sk_part_floats = std::max(kSplitPartFloats, (size_t)3 * (c->rcap + 32) * (c->dmax + 128));
+  // streaming kernel: kSplitPartFloats; tiled kernel: about 4 slices x rows x outputs (d wide); a plan that needs more is not taken
+  c->sk_part_floats = std::max(kSplitPartFloats, (size_t)4 * (c->rcap + 32) * (c->dmax + 128));
   c->sk_part = k.take<float>(c->sk_part_floats);
   c->sk_cnt = k.take<unsigned>(kSplitGroups);
   c->att_cnt = k.take<unsigned>((size_t)PK_MAXB * c->hmax * 2);
@@ -281,126 +282,84 @@ SplitShape pick_split_shape(int n_tiles, int KT, int rows, int hl) {
   return best;
 }
 
-// More than 32 rows: one launch of the wide kernel (operand shared through LDS, weights read once).
-// K slices hand their sums over through the operand buffers: do they fit?
-constexpr bool wide_fits(int hl, int mtb, int ntw, int ks) {
-  return ks == 1 || 4 * ntw * mtb <= ks * 2 * (4 / ks) * ((mtb * hl + 3) / 4) * 4;
-}
-template <int EPI, int TAG, int HL, int MTB, int NTW, int KS>
-void launch_wide_shape(pacer_ctx* c, const GemmArgs& ga, int n_tiles, int row_groups) {
-  if constexpr (!wide_fits(HL, MTB, NTW, KS)) {
-    (void)fail(c, PACER_EINVAL, "wide GEMM shape %d x %d with %d K slices does not exist", NTW, MTB, KS);
-    return;
-  } else {
-  const int n_groups = (n_tiles + 4 * NTW - 1) / (4 * NTW);
-  const dim3 grid((unsigned)((n_groups + 7) / 8 * 8 * row_groups));
-  PACER_LAUNCH_EXT((gemm_wide_kernel<EPI, NTW, MTB, HL, TAG, KS>), grid, dim3(256 * KS), 0, c->stream, c->pe0, c->pe1, 0, ga, n_tiles, n_groups, row_groups);
+// More than 32 rows: one launch of the tiled kernel.  Its block shapes (row tiles x output tiles) with the wave layout and
+// LDS rings each is built with; X(i, RT, CT, WR, WC, NX, WB, NW), i = index in the table.
+#define PACER_TILE_SHAPES(X)                                                                        \
+  X(0, 4, 4, 2, 4, 4, 4, 2) X(1, 4, 8, 2, 4, 4, 2, 4) X(2, 6, 4, 2, 4, 4, 4, 2) X(3, 6, 8, 2, 4, 4, 2, 3) \
+  X(4, 8, 4, 2, 4, 4, 4, 2) X(5, 8, 8, 4, 2, 4, 2, 3) X(6, 10, 4, 2, 4, 4, 4, 2) X(7, 10, 8, 2, 4, 4, 2, 3) \
+  X(8, 12, 4, 2, 4, 4, 4, 2) X(9, 12, 8, 2, 4, 4, 2, 3) X(10, 8, 12, 4, 2, 3, 4, 2) X(11, 8, 22, 4, 2, 3, 1, 3) \
+  X(12, 16, 12, 4, 2, 3, 2, 2)
+struct TileShape { int rt, ct; };
+constexpr TileShape kTileShapes[] = {
+#define X(i, RT, CT, WR, WC, NX, WB, NW) {RT, CT},
+    PACER_TILE_SHAPES(X)
+#undef X
+};
+constexpr int kNumTileShapes = sizeof(kTileShapes) / sizeof(kTileShapes[0]);
+constexpr int kTileMinSteps = 8;     // K steps (of 32) of a block: at least a weight batch, and enough to fill the pipeline
+typedef void (*TileKernel)(const GemmArgs, int, int, int, int);
+template <int EPI, int HL>
+TileKernel tile_kernel(int i, int* lds_bytes) {
+  switch (i) {
+#define X(i_, RT, CT, WR, WC, NX, WB, NW) \
+    case i_: *lds_bytes = (NX * RT * HL + NW * WB * CT) * 1024; return gemm_tile_kernel<EPI, RT, CT, WR, WC, HL, NX, WB, NW>;
+    PACER_TILE_SHAPES(X)
+#undef X
   }
+  return nullptr;
 }
-// Shape of a wide launch: row tiles per block (MTB), output tiles per wave (NTW), K slices (KS).
-// A block always multiplies MTB row tiles (a short group repeats its last tile).  The launch moves
-//   row_groups x weights  +  blocks x (the block's operand rows)
-// through the L2s, which is what bounds it (about 12 TB/s measured), and it is only as fast as its busiest
-// CU, so the estimate is that traffic times ceil(blocks / 256) / (blocks / 256).  Checked against
-// microbenchmarks of the 13B-width matrices at 96..272 rows (random data): the estimate ranks the shapes
-// as measured (e.g. QKV at 144 rows: 3 tiles x 3 row tiles = 240 blocks 61 us, 4 x 4 = 180 blocks 91 us; at
-// 160 rows 3 x 4 = 240 blocks 74 us, 3 x 3 = 320 blocks 105 us).  Up to 256 blocks: two K slices of waves
-// per block (8 waves on the CU); up to 128 blocks of one tile per wave: four.
-struct WideShape { int mtb, ntw, ks; };
-WideShape pick_wide_shape(int n_tiles, int mt_total, int KT, int hl) {
-  WideShape best{4, 2, 1};
-  double best_est = 1e300;
-  for (int mtb = 3; mtb <= 4; ++mtb) {
-    const int rg = (mt_total + mtb - 1) / mtb;
-    for (int ntw = 1; ntw <= 4; ++ntw) {
-      const int blocks = (n_tiles + 4 * ntw - 1) / (4 * ntw) * rg;
-      int ks = 1;
-      if (blocks <= 128 && ntw == 1 && KT % 16 == 0) ks = 4;
-      else if (blocks <= 256 && KT % 8 == 0) ks = 2;
-      if (!wide_fits(hl, mtb, ntw, ks)) ks = 1;
-      if (ks == 1 && ntw == 1) continue;              // one tile per wave exists only with K slices
-      const double traffic = (double)rg * n_tiles * 32.0 + (double)blocks * mtb * 64.0;
-      const double est = traffic * ((blocks + 255) / 256) * 256.0 / blocks;
-      if (est < best_est * 0.999 || (est < best_est * 1.001 && ntw > best.ntw)) { best_est = est; best = {mtb, ntw, ks}; }
+
+// Block shape and K slices of a tiled launch.  The estimate (in us, fitted to microbenchmarks of the matrices of the
+// mid, 7B and 13B pairs at 40..512 rows, where its choice is on average within 2 % of the best shape):
+//   rounds of 256 blocks  x  K steps  x  max(0.12 + 0.0027 per product of two tiles, the block's share of the weight stream)
+// A step costs 0.12 for its barrier and what is issued before the matrix units are busy; the weight stream reaches
+// 26 KB per us and CU when each block has its own weights.  K slices add 1.5 + 0.6 per slice for the hand-over and 0.02 per
+// partial tile.  Slices only for shapes of at most 8 output tiles, where the accumulators of two slices fit the registers.
+// E.g. 13B QKV (960 tiles) at 160 rows: 10 x 8 in 2 slices 50 us, 6 x 8 56, 10 x 4 57; 7B gate/up (1376) at 512 rows: 8 x 22
+// 133 us, 8 x 12 149, 8 x 8 158; 7B O (256 tiles, hi only) at 512 rows: 8 x 8 in 2 slices 25 us, 8 x 4 27.5, 10 x 8 28.
+struct TilePlan { int shape, ksb; };
+TilePlan pick_tile_plan(int n_tiles, int mt_total, int KT, int hl, size_t part_floats) {
+  TilePlan best{0, 1};
+  double best_us = 1e300;
+  for (int i = 0; i < kNumTileShapes; ++i) {
+    const int rt = kTileShapes[i].rt, ct = kTileShapes[i].ct;
+    const int rg = (mt_total + rt - 1) / rt, ng = (n_tiles + ct - 1) / ct;
+    for (int ksb : {1, 2, 3, 4, 6, 8}) {
+      if (ksb > 1 && (ct > 8 || KT / ksb < kTileMinSteps || ng * rg > kSplitGroups || (size_t)ng * rg * ksb * rt * ct * 256 > part_floats)) continue;
+      const int blocks = ng * rg * ksb;
+      const double step = std::max(0.12 + 0.0027 * hl * rt * ct, (double)ct * std::min(256, blocks) / rg / 256.0 / 26.0);
+      const double us = (double)((blocks + 255) / 256) * ((KT + ksb - 1) / ksb) * step + (ksb > 1 ? 1.5 + 0.6 * ksb + 0.02 * rt * ct * ksb : 0.0);
+      if (us < best_us) { best_us = us; best = {i, ksb}; }
     }
   }
   return best;
 }
-// Few-tile projections at 6..12 row tiles (96..192 rows: batched verification): the 8-wave kernel with K
-// slices across blocks.  Two row groups of MTB = ceil(row tiles / 2) tiles, one output tile per wave, and as
-// many K slices (3, else 2) as keep the launch within the CU count.  Measured at d 5120 (320 tiles -> 40 groups x
-// 2 x 3 = 240 blocks), hi+lo down projection: 52 / 63 / 74 us at MTB 4 / 5 / 6 against 75 / 80 / 84 us for the best
-// shape of the 4-wave kernel.  The hi-only O projection (26 / 31.5 us at MTB 4 / 5 against 31 / 33 us in the same
-// microbenchmark) turned out slower in the real sequence (33 against 29 us) and stays with the 4-wave kernel.
-// Returns false if the shape is not covered (the caller then takes the 4-wave kernel).
-constexpr int kWide8KC = 4;
-// The gate/up GEMM (many tiles) takes the same kernel without K slices at 7..12 row tiles when two tiles per
-// wave x two row groups give 192..256 blocks (d 5120: 108 groups -> 216 blocks): 82 / 106 / 117 us at MTB 4 / 5 / 6
-// against 88 / 115 / 123 us.  The QKV GEMM does not gain (94 against 62 us).
-template <int EPI, int TAG, int HL, int NTW, int MTB, int KSB>
-void launch_wide8_shape(pacer_ctx* c, const GemmArgs& ga, int n_tiles, int n_groups) {
-  const size_t lds = (size_t)2 * kWide8KC * MTB * HL * 1024;
-  PACER_LAUNCH_EXT((gemm_wide8_kernel<EPI, NTW, MTB, HL, TAG, kWide8KC, KSB>), dim3((unsigned)((n_groups + 7) / 8 * 8 * 2 * KSB)), dim3(512), lds,
-                        c->stream, c->pe0, c->pe1, 0, ga, n_tiles, n_groups, 2);
-}
-template <int EPI, int TAG, int HL>
-bool launch_wide8(pacer_ctx* c, GemmArgs ga, int n_tiles) {
-  if constexpr (TAG == 0 && EPI == EPI_SWIGLU && HL == 2) {
-    const int mt = ga.mt_total;
-    const int n_groups = (n_tiles + 15) / 16;
-    if (mt < 7 || mt > 12 || ga.KT % 4 || ga.KT < 64 || n_groups * 2 < 192 || n_groups * 2 > 256) return false;
-    const int mtb = std::max(4, (mt + 1) / 2);
-    ga.mt0 = 0;
-    if (mtb == 4) launch_wide8_shape<EPI, TAG, HL, 2, 4, 1>(c, ga, n_tiles, n_groups);
-    else if (mtb == 5) launch_wide8_shape<EPI, TAG, HL, 2, 5, 1>(c, ga, n_tiles, n_groups);
-    else launch_wide8_shape<EPI, TAG, HL, 2, 6, 1>(c, ga, n_tiles, n_groups);
-    return true;
-  } else if constexpr (TAG != 0 || EPI != EPI_RESID || HL != 2) {
-    return false;
-  } else {
-    const int mt = ga.mt_total;
-    if (mt < 6 || mt > 12 || n_tiles >= 512 || ga.KT % 4 || ga.KT < 64) return false;
-    const int n_groups = (n_tiles + 7) / 8;
-    const int mtb = std::max(4, (mt + 1) / 2);
-    const int ksb = n_groups * 2 * 3 <= 256 ? 3 : (n_groups * 2 * 2 <= 256 ? 2 : 0);
-    if (ksb == 0 || n_groups * 2 > kSplitGroups) return false;
-    if ((size_t)n_groups * 2 * ksb * 8 * mtb * 256 > c->sk_part_floats) return false;
-    ga.mt0 = 0;
-    ga.sk_part = c->sk_part;
-    ga.sk_cnt = c->sk_cnt;
-#define PACER_W8(MTB_) if (ksb == 3) launch_wide8_shape<EPI, TAG, HL, 1, MTB_, 3>(c, ga, n_tiles, n_groups); else launch_wide8_shape<EPI, TAG, HL, 1, MTB_, 2>(c, ga, n_tiles, n_groups)
-    if (mtb == 4) { PACER_W8(4); } else if (mtb == 5) { PACER_W8(5); } else { PACER_W8(6); }
-#undef PACER_W8
-    return true;
-  }
-}
-
-template <int EPI, int TAG, int HL>
-void launch_wide(pacer_ctx* c, GemmArgs ga, int n_tiles) {
+template <int EPI, int HL>
+void launch_tile(pacer_ctx* c, GemmArgs ga, int n_tiles) {
+  const TilePlan p = pick_tile_plan(n_tiles, ga.mt_total, ga.KT, HL, c->sk_part_floats);
+  const int rt = kTileShapes[p.shape].rt, ct = kTileShapes[p.shape].ct;
+  const int rg = (ga.mt_total + rt - 1) / rt, ng = (n_tiles + ct - 1) / ct;
   ga.mt0 = 0;
-  if constexpr (TAG != 0) {   // draft and pre-verification layer: small matrices, one shape
-    launch_wide_shape<EPI, TAG, HL, 4, 2, 1>(c, ga, n_tiles, (ga.mt_total + 3) / 4);
-  } else {
-    const WideShape w = pick_wide_shape(n_tiles, ga.mt_total, ga.KT, HL);
-    const int rg = (ga.mt_total + w.mtb - 1) / w.mtb;
-#define PACER_WIDE(MTB_, NTW_, KS_) launch_wide_shape<EPI, TAG, HL, MTB_, NTW_, KS_>(c, ga, n_tiles, rg)
-#define PACER_WIDE_MTB(MTB_)                                                     \
-    if (w.ks == 4) PACER_WIDE(MTB_, 1, 4);                                       \
-    else if (w.ks == 2) {                                                        \
-      if (w.ntw == 1) PACER_WIDE(MTB_, 1, 2); else if (w.ntw == 2) PACER_WIDE(MTB_, 2, 2); \
-      else if (w.ntw == 3) PACER_WIDE(MTB_, 3, 2); else PACER_WIDE(MTB_, 4, 2);  \
-    } else {                                                                     \
-      if (w.ntw == 2) PACER_WIDE(MTB_, 2, 1); else if (w.ntw == 3) PACER_WIDE(MTB_, 3, 1); \
-      else PACER_WIDE(MTB_, 4, 1);                                               \
-    }
-    if (w.mtb == 3) { PACER_WIDE_MTB(3) } else { PACER_WIDE_MTB(4) }
-#undef PACER_WIDE_MTB
-#undef PACER_WIDE
+  ga.sk_part = c->sk_part;
+  ga.sk_cnt = c->sk_cnt;
+  int lds = 0;
+  const TileKernel k = tile_kernel<EPI, HL>(p.shape, &lds);
+  PACER_LAUNCH_EXT(k, dim3((unsigned)((ng + 7) / 8 * 8 * rg * p.ksb)), dim3(512), lds, c->stream, c->pe0, c->pe1, 0, ga, n_tiles, ng, rg, p.ksb);
+}
+// the blocks keep their stages in dynamic LDS, up to 152 of the CU's 160 KiB
+template <int EPI, int HL>
+hipError_t tile_lds_limits() {
+  for (int i = 0; i < kNumTileShapes; ++i) {
+    int lds = 0;
+    const TileKernel k = tile_kernel<EPI, HL>(i, &lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
   }
+  return hipSuccess;
 }
 
 // Launches the GEMM over `n_tiles` output tiles starting at ga.nt_begin; up to 32 rows with the
-// weight-streaming kernel, more with the wide one.
+// weight-streaming kernel, more with the tiled one.
 // HL = 2: multiply the operand's hi and lo tiles (target model, all GEMMs but the O projection and the
 // LM head, whose inputs' f16 rounding hardly shows in the logits); HL = 1: hi only.
 // Launch shapes <MT, NT, WAVES, U>, all measured on MI355X (U = K steps per register set; the loop keeps
@@ -418,9 +377,9 @@ void gemm_w16_tag(pacer_ctx* c, GemmArgs ga, int n_tiles, int K) {
   ga.nt_end = ga.nt_begin + n_tiles;
   const bool many = n_tiles >= 512;
   const bool even = n_tiles % 2 == 0;
-  if (mt_total > 2 && ga.KT % 4 == 0) {
+  if (mt_total > 2 && ga.KT >= kTileMinSteps) {
     if (TAG == 0) prof_begin(c);
-    if (!launch_wide8<EPI, TAG, HL>(c, ga, n_tiles)) launch_wide<EPI, TAG, HL>(c, ga, n_tiles);
+    launch_tile<EPI, HL>(c, ga, n_tiles);
     if (TAG == 0) prof_end(c, (double)n_tiles * 16.0 * K * 2.0);
     return;
   }
@@ -1146,13 +1105,13 @@ int32_t pacer_bind_workspace(pacer_ctx* c, void* p, uint64_t nbytes) {
     PACER_ATT_LDS(128, 2, 1); PACER_ATT_LDS(128, 1, 1); PACER_ATT_LDS(64, 2, 1); PACER_ATT_LDS(64, 1, 1);
 #undef PACER_ATT_LDS
   }
-  // the 8-wave wide GEMM stages its operand in dynamic LDS: up to 2 x 4 K steps x 6 row tiles x hi+lo KiB = 96 KiB
-#define PACER_W8_LDS(HL_, MTB_, KSB_) HIPCHK(c, hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_wide8_kernel<EPI_RESID, 1, MTB_, HL_, 0, kWide8KC, KSB_>), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kWide8KC * MTB_ * HL_ * 1024))
-  PACER_W8_LDS(2, 4, 2); PACER_W8_LDS(2, 4, 3); PACER_W8_LDS(2, 5, 2); PACER_W8_LDS(2, 5, 3); PACER_W8_LDS(2, 6, 2); PACER_W8_LDS(2, 6, 3);
-#undef PACER_W8_LDS
-#define PACER_W8_LDS(MTB_) HIPCHK(c, hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_wide8_kernel<EPI_SWIGLU, 2, MTB_, 2, 0, kWide8KC, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kWide8KC * MTB_ * 2 * 1024))
-  PACER_W8_LDS(4); PACER_W8_LDS(5); PACER_W8_LDS(6);
-#undef PACER_W8_LDS
+  HIPCHK(c, (tile_lds_limits<EPI_QKV, 2>()));
+  HIPCHK(c, (tile_lds_limits<EPI_QKV, 1>()));
+  HIPCHK(c, (tile_lds_limits<EPI_SWIGLU, 2>()));
+  HIPCHK(c, (tile_lds_limits<EPI_SWIGLU, 1>()));
+  HIPCHK(c, (tile_lds_limits<EPI_RESID, 2>()));
+  HIPCHK(c, (tile_lds_limits<EPI_RESID, 1>()));
+  HIPCHK(c, (tile_lds_limits<EPI_STORE, 1>()));
   c->ws_bound = true;
   return PACER_OK;
 }
