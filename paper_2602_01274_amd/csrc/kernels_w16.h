@@ -696,32 +696,37 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 8 ? (NT >= 5 ? 2 : 4) : 1)) v
 }
 
 // ------------------------------------------------------------------ MFMA attention over the f16 KV cache
-// grid (key splits, heads, sequences), 8 waves per block.  A block owns `kps` keys of one head; its
+// grid (key splits, heads, sequences), NW waves per block.  A block owns `kps` keys of one head; its
 // waves take the 32-key groups of that range round-robin, each running an online softmax in registers:
 //   scores  S^T[key][row] = K[key][:] . Q[row][:]   (A = K tile straight from the cache, B = Q operand)
 //   values  O^T[dim][row] += V^T[dim][keys] P^T[keys][row]; the probabilities leave the first MFMA in
 //           exactly the lane layout the second one wants for B (contraction index = the 8 keys a lane
 //           holds), and V^T rows are contiguous along keys.
-// The 8 wave states meet in LDS (dynamic, 8 x live rows x (HD + 4) floats) and are combined in one pass.
+// The NW wave states meet in LDS (dynamic, NW x live rows x (HD + 4) floats) and are combined in one pass.
 // With one split the block writes the f16 operand of the O projection directly; with several, each block
 // writes a partial (un-normalised values, running max, running sum per row) and the block of a (head,
 // sequence, row tile) that arrives last combines them, in split order.  The hand-over needs no device-scope
 // fence (see gemm_w16_kernel): write-through stores, a wait for their completion, an agent-scope counter,
 // and loads that bypass the reader's L2.  `cnt` holds one counter per (sequence slot, head, row-tile half),
 // zero between launches.
-// QL = 2: the query operand is used as hi + lo (target model), 1: hi only.
-template <int HD, int MT, int QL>
-__global__ __launch_bounds__(512) void attn_mfma_kernel(const _Float16* __restrict__ qp, const _Float16* __restrict__ kv, int layer,
+// QL = 2: the query operand is used as hi + lo (target model), 1: hi only.  NW waves per block.
+// order: which sequence slot a grid position takes, 4 bits each (longest first).
+// What bounds it: with few pairs a chain of memory and dependency latencies, with many the vector units' softmax beside the
+// cache stream.  Scores are kept in units of log2, so a probability is one v_exp_f32 (with expf: 16 instructions): 12 heads,
+// 530 keys 6.5 -> 5.4 us; 512 prompt rows, 32 heads 50 -> 43 us.  A second row tile without rows is skipped.
+__device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
+template <int HD, int MT, int QL, int NW>
+__global__ __launch_bounds__(NW * 64, HD == 128 ? (MT == 2 ? 2 : 3) : (MT == 2 ? 3 : 4)) void attn_mfma_kernel(const _Float16* __restrict__ qp, const _Float16* __restrict__ kv, int layer,
                                                         int n_layers, int max_seq, int d, SeqRows sr, int kps, int S, int H,
                                                         float* __restrict__ part, _Float16* __restrict__ xp_out, int MT_total_out,
-                                                        int rt_split, unsigned* __restrict__ cnt) {
-  constexpr int KTS = HD / 32, DTS = HD / 16, NW = 8;
+                                                        int rt_split, uint64_t order, unsigned* __restrict__ cnt) {
+  constexpr int KTS = HD / 32, DTS = HD / 16;
   __shared__ unsigned arrived;
-  extern __shared__ __align__(16) float att_state[];   // [8 waves][live rows][HD + 4]: values, running max, running sum
+  extern __shared__ __align__(16) float att_state[];   // [NW waves][live rows][HD + 4]: values, running max, running sum
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
   // rt_split (MT == 1 launches only): two blocks per key range, one per 16-row tile of the sequence
   const int rt = rt_split ? (int)(blockIdx.x & 1) : 0;
-  const int split = rt_split ? (int)(blockIdx.x >> 1) : (int)blockIdx.x, h = blockIdx.y, si = blockIdx.z;
+  const int split = rt_split ? (int)(blockIdx.x >> 1) : (int)blockIdx.x, h = blockIdx.y, si = (int)(order >> (4 * blockIdx.z)) & 15;
   const int r0 = sr.row_off[si] + rt * 16, pos0 = sr.pos0[si];
   const int n_keys = pos0 + sr.row_off[si + 1] - sr.row_off[si];
   const int Rs = sr.row_off[si + 1] - r0;                // rows from this block's first one to the sequence's last
@@ -730,8 +735,9 @@ __global__ __launch_bounds__(512) void attn_mfma_kernel(const _Float16* __restri
   const int ks_begin = split * kps, ks_end = min(n_keys, ks_begin + kps);
   const _Float16* Kc = kv + (((size_t)sr.seq[si] * n_layers + layer) * 2) * (size_t)max_seq * d + (size_t)h * HD * max_seq;
   const _Float16* Vt = Kc + (size_t)max_seq * d;
-  const float scale = 1.0f / sqrtf((float)HD);
-  typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+  // scores in units of log2: the softmax then takes the hardware's 2^x as it is
+  const float scale = 1.4426950408889634f / sqrtf((float)HD);
+  const int mts = MT == 2 && Rs > 16 ? 2 : 1;          // row tiles that have rows (uniform)
 
   half8 q[KTS][MT][QL];
 #pragma unroll
@@ -802,13 +808,13 @@ __global__ __launch_bounds__(512) void attn_mfma_kernel(const _Float16* __restri
     float ps = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float pe = (mn == -INFINITY) ? 0.f : expf(sv[e] - mn);
+      const float pe = (mn == -INFINITY) ? 0.f : exp2_hw(sv[e] - mn);
       ps += pe;
       pb[e] = (_Float16)pe;
     }
     ps += __shfl_xor(ps, 16, 64);
     ps += __shfl_xor(ps, 32, 64);
-    corr = (mrun[mt] == -INFINITY) ? 0.f : expf(mrun[mt] - mn);
+    corr = (mrun[mt] == -INFINITY) ? 0.f : exp2_hw(mrun[mt] - mn);
     lrun[mt] = lrun[mt] * corr + ps;
     mrun[mt] = mn;
   };
@@ -819,6 +825,7 @@ __global__ __launch_bounds__(512) void attn_mfma_kernel(const _Float16* __restri
     auto values = [&](half8(&va)[DTS], half8(&pb)[MT], float(&corr)[MT]) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
+        if (mt < mts)
 #pragma unroll
         for (int dt = 0; dt < DTS; ++dt) {
           acc[dt][mt] *= corr[mt];
@@ -838,7 +845,8 @@ __global__ __launch_bounds__(512) void attn_mfma_kernel(const _Float16* __restri
         half8 pb[MT];
         float corr[MT];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) scores(kk, mt, ka, pb[mt], corr[mt]);
+        for (int mt = 0; mt < MT; ++mt)
+          if (mt < mts) scores(kk, mt, ka, pb[mt], corr[mt]);
         __builtin_amdgcn_sched_barrier(0);
         load_k(kn, ka);
         __builtin_amdgcn_sched_barrier(0);
@@ -850,8 +858,8 @@ __global__ __launch_bounds__(512) void attn_mfma_kernel(const _Float16* __restri
     }
   }
 
-  // Merge of the 8 wave states: every wave writes its live rows (values, running max, running sum) to LDS
-  // once, then each thread combines the 8 states of one (row, 4 dims) group and writes the result.  One
+  // Merge of the wave states: every wave writes its live rows (values, running max, running sum) to LDS
+  // once, then each thread combines the states of one (row, 4 dims) group and writes the result.  One
   // barrier (a pairwise tree over the MFMA tiles took six per row tile and 1.4 to 4 us).
   const int rcap = min(Rs, MT * 16);
   float* st = att_state;
@@ -878,7 +886,7 @@ __global__ __launch_bounds__(512) void attn_mfma_kernel(const _Float16* __restri
     for (int w = 0; w < NW; ++w) {
       const float* pw = p + (size_t)w * rcap * (HD + 4);
       const float m = pw[HD];
-      const float wt = (m == -INFINITY) ? 0.f : expf(m - M);
+      const float wt = (m == -INFINITY) ? 0.f : exp2_hw(m - M);
       L += pw[HD + 1] * wt;
       a += *reinterpret_cast<const f32x4*>(pw + d4) * wt;
     }
@@ -922,13 +930,13 @@ __global__ __launch_bounds__(512) void attn_mfma_kernel(const _Float16* __restri
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         if (c0 + i < n_split) Mb = fmaxf(Mb, __builtin_bit_cast(float2, ml[i]).x);
-      const float keep = (M == -INFINITY) ? 0.f : expf(M - Mb);
+      const float keep = (M == -INFINITY) ? 0.f : exp2_hw(M - Mb);
       L *= keep;
       a *= keep;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const float2 mli = __builtin_bit_cast(float2, ml[i]);
-        const float w = (c0 + i < n_split && mli.x != -INFINITY) ? expf(mli.x - Mb) : 0.f;
+        const float w = (c0 + i < n_split && mli.x != -INFINITY) ? exp2_hw(mli.x - Mb) : 0.f;
         const float2 x01 = __builtin_bit_cast(float2, v01[i]), x23 = __builtin_bit_cast(float2, v23[i]);
         L += mli.y * w;
         a[0] += x01.x * w; a[1] += x01.y * w; a[2] += x23.x * w; a[3] += x23.y * w;
