@@ -349,7 +349,10 @@ template <> __device__ __forceinline__ float kv_dim<_Float16>(const uint32_t* ro
   return (dim & 1) ? f16hi(w) : f16lo(w);
 }
 
-template <typename KVT, int HD>
+// RPW: rows per wave, the launch's most rows of a sequence over the block's 4 waves (rows past a sequence's last compute on
+// whatever LDS holds and are not stored).  Latency bound at the sizes it serves: without conditions on the row the loops
+// over features and keys unroll, and their LDS reads overlap (3 rows, 35 keys: 20.2 -> 4.9 us).
+template <typename KVT, int HD, int RPW>
 __global__ __launch_bounds__(256) void attn_partial_kernel(const float* __restrict__ q, int ldq, const KVT* __restrict__ kv, int layer,
                                                            int n_layers, int max_seq, int d, SeqRows sr, int tiles_per_chunk,
                                                            int n_chunks, int H, float* __restrict__ part) {
@@ -375,9 +378,9 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float* __restri
 
   for (int i = tid; i < Rs * HD; i += 256) Qs[i / HD][i % HD] = q[(size_t)(r0 + i / HD) * ldq + h * HD + (i % HD)] * scale;
   if (tid < ATT_MAXR) { sm[tid] = -INFINITY; sl[tid] = 0.f; sc[tid] = 1.f; }
-  float acc[ATT_MAXR / 4][DPL];
+  float acc[RPW][DPL];
 #pragma unroll
-  for (int i = 0; i < ATT_MAXR / 4; ++i)
+  for (int i = 0; i < RPW; ++i)
 #pragma unroll
     for (int e = 0; e < DPL; ++e) acc[i][e] = 0.f;
   __syncthreads();
@@ -385,46 +388,52 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float* __restri
   for (int t = t_begin; t < t_end; ++t) {
     const int key0 = t * ATT_TILE;
     // stage K and V tiles: 16-byte global reads, 4-byte LDS writes
-    constexpr int V4 = WORDS / 4;                       // uint4 per key
-    for (int i = tid; i < ATT_TILE * V4; i += 256) {
-      const int key = i / V4, c = i % V4;
-      uint4 kq = make_uint4(0, 0, 0, 0), vq = kq;
-      if (key0 + key < n_keys) {
-        kq = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(Kb + (size_t)(key0 + key) * d) + c * 4);
-        vq = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(Vb + (size_t)(key0 + key) * d) + c * 4);
-      }
+    constexpr int V4 = WORDS / 4, NI = ATT_TILE * V4 / 256;   // uint4 per key, per thread
+    uint4 kq[NI], vq[NI];
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {                    // all requested before the first is used; a key past the end reads the last one
+      const int i = tid + it * 256, key = min(key0 + i / V4, n_keys - 1), c = i % V4;
+      kq[it] = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(Kb + (size_t)key * d) + c * 4);
+      vq[it] = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(Vb + (size_t)key * d) + c * 4);
+    }
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      const int i = tid + it * 256, key = i / V4, c = i % V4;
+      const bool in = key0 + key < n_keys;
+      const uint4 kk = in ? kq[it] : make_uint4(0, 0, 0, 0), vv = in ? vq[it] : make_uint4(0, 0, 0, 0);
       uint32_t* kd = Kt + key * STR + c * 4;
       uint32_t* vd = Vt + key * STR + c * 4;
-      kd[0] = kq.x; kd[1] = kq.y; kd[2] = kq.z; kd[3] = kq.w;
-      vd[0] = vq.x; vd[1] = vq.y; vd[2] = vq.z; vd[3] = vq.w;
+      kd[0] = kk.x; kd[1] = kk.y; kd[2] = kk.z; kd[3] = kk.w;
+      vd[0] = vv.x; vd[1] = vv.y; vd[2] = vv.z; vd[3] = vv.w;
     }
     __syncthreads();
     // scores: thread = (key, row group)
     {
-      float s[ATT_MAXR / 4];
+      float s[RPW];
 #pragma unroll
-      for (int i = 0; i < ATT_MAXR / 4; ++i) s[i] = 0.f;
+      for (int i = 0; i < RPW; ++i) s[i] = 0.f;
       const uint32_t* krow = Kt + lane * STR;
+#pragma unroll 8
       for (int w = 0; w < WORDS; ++w) {
         const uint32_t kw = krow[w];
         if (KvWords<KVT>::per_word == 2) {
           const float k0 = f16lo(kw), k1 = f16hi(kw);
 #pragma unroll
-          for (int i = 0; i < ATT_MAXR / 4; ++i) {
+          for (int i = 0; i < RPW; ++i) {
             const int r = wv + 4 * i;
-            if (r < Rs) s[i] += Qs[r][2 * w] * k0 + Qs[r][2 * w + 1] * k1;
+            s[i] += Qs[r][2 * w] * k0 + Qs[r][2 * w + 1] * k1;
           }
         } else {
           const float k0 = __uint_as_float(kw);
 #pragma unroll
-          for (int i = 0; i < ATT_MAXR / 4; ++i) {
+          for (int i = 0; i < RPW; ++i) {
             const int r = wv + 4 * i;
-            if (r < Rs) s[i] += Qs[r][w] * k0;
+            s[i] += Qs[r][w] * k0;
           }
         }
       }
 #pragma unroll
-      for (int i = 0; i < ATT_MAXR / 4; ++i) {
+      for (int i = 0; i < RPW; ++i) {
         const int r = wv + 4 * i;
         if (r < Rs) S[r][lane] = (key0 + lane <= pos0 + r) ? s[i] : -INFINITY;
       }
@@ -448,7 +457,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float* __restri
     __syncthreads();
     // weighted values: thread = (dims lane*DPL.., row group)
 #pragma unroll
-    for (int i = 0; i < ATT_MAXR / 4; ++i) {
+    for (int i = 0; i < RPW; ++i) {
       const int r = wv + 4 * i;
       if (r < Rs) {
         const float c = sc[r];
@@ -456,24 +465,23 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float* __restri
         for (int e = 0; e < DPL; ++e) acc[i][e] *= c;
       }
     }
+#pragma unroll 8
     for (int key = 0; key < ATT_TILE; ++key) {
       float vv[DPL];
 #pragma unroll
       for (int e = 0; e < DPL; ++e) vv[e] = kv_dim<KVT>(Vt + key * STR, lane * DPL + e);
 #pragma unroll
-      for (int i = 0; i < ATT_MAXR / 4; ++i) {
+      for (int i = 0; i < RPW; ++i) {
         const int r = wv + 4 * i;
-        if (r < Rs) {
-          const float p = S[r][key];
+        const float p = S[r][key];
 #pragma unroll
-          for (int e = 0; e < DPL; ++e) acc[i][e] += p * vv[e];
-        }
+        for (int e = 0; e < DPL; ++e) acc[i][e] += p * vv[e];
       }
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < ATT_MAXR / 4; ++i) {
+  for (int i = 0; i < RPW; ++i) {
     const int r = wv + 4 * i;
     if (r < Rs) {
       float* o = part + (((size_t)(r0 + r) * H + h) * n_chunks + chunk) * (HD + 2);

@@ -645,8 +645,11 @@ void lm_head_w16(pacer_ctx* c, const Model& m, int tag, int R, float* out, const
 
 void gemm_f32(pacer_ctx* c, const void* W, const float* act, int lda, float* out, int ldo, int R, int N, int K, int acc,
               const SeqRows& sr, int rowmap) {
-  PACER_LAUNCH(gemm_f32_kernel, dim3((N + 3) / 4), dim3(256), 0, c->stream, static_cast<const float*>(W), act, lda, out, ldo, R, N,
-                     K, acc, sr, rowmap, c->G1);
+#define PACER_GEMM_F32(RG_) PACER_LAUNCH((gemm_f32_kernel<RG_>), dim3((N + 3) / 4), dim3(256), 0, c->stream, static_cast<const float*>(W), act, lda, out, ldo, R, N, K, acc, sr, rowmap, c->G1)
+  if (R == 1) PACER_GEMM_F32(1);
+  else if (R <= 4) PACER_GEMM_F32(4);
+  else PACER_GEMM_F32(8);
+#undef PACER_GEMM_F32
 }
 
 void rmsnorm_f32(pacer_ctx* c, const Model& m, const float* g, int R, float* hid_out, const SeqRows& sr) {
@@ -665,14 +668,20 @@ void run_layers_f32(pacer_ctx* c, const Model& m, int R, const SeqRows& sr, bool
     PACER_LAUNCH((rope_append_kernel<float>), dim3(R, H), dim3(hd / 2), 0, c->stream, c->qkv, 3 * c->dmax, c->rope, sr, d, hd,
                        static_cast<float*>(m.kv), l, g.n_layers, g.max_seq, kv_only ? 1 : 0);
     if (kv_only || (cache_only && l + 1 == g.n_layers)) continue;
-    int max_keys = 0;
-    for (int i = 0; i < sr.n_seqs; ++i) max_keys = std::max(max_keys, sr.pos0[i] + sr.row_off[i + 1] - sr.row_off[i]);
+    int max_keys = 0, max_rows = 0;
+    for (int i = 0; i < sr.n_seqs; ++i) {
+      max_keys = std::max(max_keys, sr.pos0[i] + sr.row_off[i + 1] - sr.row_off[i]);
+      max_rows = std::max(max_rows, sr.row_off[i + 1] - sr.row_off[i]);
+    }
     const int n_tiles = (max_keys + ATT_TILE - 1) / ATT_TILE;
     int chunks = std::min(std::min(n_tiles, kMaxChunks), std::max(1, 1024 / (H * sr.n_seqs)));
     const int tpc = (n_tiles + chunks - 1) / chunks;
     chunks = (n_tiles + tpc - 1) / tpc;
-    PACER_LAUNCH((attn_partial_kernel<float, 64>), dim3(chunks, H, sr.n_seqs), dim3(256), 0, c->stream, c->qkv, 3 * c->dmax,
-                       static_cast<const float*>(m.kv), l, g.n_layers, g.max_seq, d, sr, tpc, chunks, H, c->part);
+#define PACER_ATT_F32(RPW_) PACER_LAUNCH((attn_partial_kernel<float, 64, RPW_>), dim3(chunks, H, sr.n_seqs), dim3(256), 0, c->stream, c->qkv, 3 * c->dmax, static_cast<const float*>(m.kv), l, g.n_layers, g.max_seq, d, sr, tpc, chunks, H, c->part)
+    if (max_rows <= 4) PACER_ATT_F32(1);
+    else if (max_rows <= 12) PACER_ATT_F32(3);
+    else PACER_ATT_F32(8);
+#undef PACER_ATT_F32
     PACER_LAUNCH(attn_combine_kernel, dim3(R, H), dim3(hd), 0, c->stream, c->part, chunks, H, hd, c->ao, c->dmax);
     gemm_f32(c, m.wo[l], c->ao, c->dmax, c->x, c->dmax, R, d, d, 1, none, ROWMAP_ID);
     rmsnorm_f32(c, m, m.ffn_norm[l], R, nullptr, sr);
