@@ -266,23 +266,37 @@ __device__ __forceinline__ u32x4 bf16x8_to_f16x8(u32x4 w) {
   return __builtin_bit_cast(u32x4, h);
 }
 
-// Plain f32 GEMM for f32 models and tiny heads: one wave per output feature, rows in groups of 8.
+// Plain f32 GEMM for f32 models and tiny heads: one wave per output feature, rows in groups of RG.  Latency bound (a few
+// hundred KiB of weights over 64..1024 waves): four K steps are requested before the first is used (d 256, 3 rows, K 688:
+// 8.4 -> 5.3 us).  The additions keep their order.
+template <int RG>
 __global__ void gemm_f32_kernel(const float* __restrict__ W, const float* __restrict__ X, int ldx, float* __restrict__ out, int ldo,
                                 int R, int N, int K, int accumulate, SeqRows sr, int rowmap, int G1) {
   const int n = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (n >= N) return;
   const float* w = W + (size_t)n * K;
-  for (int r0 = 0; r0 < R; r0 += 8) {
-    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int k = lane; k < K; k += 64) {
-      const float wv = w[k];
+  constexpr int U = 4;
+  for (int r0 = 0; r0 < R; r0 += RG) {
+    float acc[RG];
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (r0 + i < R) acc[i] += wv * X[(size_t)(r0 + i) * ldx + k];
+    for (int i = 0; i < RG; ++i) acc[i] = 0.f;
+    for (int k0 = lane; k0 < K; k0 += 64 * U) {
+      float wv[U], xv[U][RG];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + 64 * u;
+        wv[u] = k < K ? w[k] : 0.f;
+#pragma unroll
+        for (int i = 0; i < RG; ++i) xv[u][i] = k < K && r0 + i < R ? X[(size_t)(r0 + i) * ldx + k] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < RG; ++i) acc[i] += wv[u] * xv[u][i];
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < RG; ++i) {
       const float s = wave_sum(acc[i]);
       if (lane == 0 && r0 + i < R) {
         float* o = out + (size_t)map_row(sr, rowmap, G1, r0 + i) * ldo + n;
@@ -606,48 +620,93 @@ __device__ __forceinline__ void acc_chunk_range(int V, int chunk, int& v0, int& 
   v1 = min(V, v0 + per);
 }
 
-// grid (gamma_max+1, n_seqs, ACC_CHUNKS)
-// done_z (phase 1 only, may be null): the phase-0 results; a sequence whose entry is >= 0 already has its token
-// (a draft was rejected) and the bonus row is skipped.
+// (best, id) of a candidate and another one: the larger value, the lower id among equal values
+__device__ __forceinline__ void take_better(float& v, int& id, float ov, int oid) {
+  if (ov > v || (ov == v && oid < id)) { v = ov; id = oid; }
+}
+
+// Rows of a launch by phase: 0 rows i < gamma; 1 the bonus row i = gamma; 2 all of them (both logits buffers already hold
+// the bonus row: one set of launches instead of two).  False: this block has no row.
+#define ACC_PHASE_DRAFTS 0
+#define ACC_PHASE_BONUS 1
+#define ACC_PHASE_ALL 2
+__device__ __forceinline__ bool acc_row(int phase, int gamma, int bx, int& i) {
+  i = phase == ACC_PHASE_BONUS ? gamma : bx;
+  return i < gamma || (i == gamma && phase != ACC_PHASE_DRAFTS);
+}
+
+// grid (rows, n_seqs, ACC_CHUNKS).  One pass: a thread keeps the running maximum of what it has seen and the sum of exp
+// relative to it, eight entries requested at a time (two passes of dependent loads took 8.3 us for 17 rows of 32000).
 __global__ __launch_bounds__(256) void accept_stats_kernel(const float* __restrict__ tl, const float* __restrict__ ring, AccArgs aa, int G1,
-                                                           int V, int phase, float* __restrict__ part, const int* __restrict__ done_z) {
-  __shared__ float redv[16];
+                                                           int V, int phase, float* __restrict__ part) {
+  __shared__ float red[4][4];
   const int si = blockIdx.y, ch = blockIdx.z, sl = aa.slot[si];
-  const int i = phase ? aa.gamma[si] : blockIdx.x;
-  if (!phase && i >= aa.gamma[si]) return;
-  if (phase && done_z && done_z[sl] >= 0) return;
+  int i;
+  if (!acc_row(phase, aa.gamma[si], blockIdx.x, i)) return;
   const float beta = aa.beta[si];
   const float* t = tl + (size_t)(sl * G1 + i) * V;
   const float* q = ring + (size_t)(aa.qslot[si] * G1 + i) * V;
   int v0, v1;
   acc_chunk_range(V, ch, v0, v1);
-  float mp = -INFINITY, mq = -INFINITY;
-  for (int v = v0 + threadIdx.x; v < v1; v += blockDim.x) { mp = fmaxf(mp, t[v] + beta * q[v]); mq = fmaxf(mq, q[v]); }
-  mp = block_max(mp, redv);
-  mq = block_max(mq, redv);
-  float sp = 0.f, sq = 0.f;
-  for (int v = v0 + threadIdx.x; v < v1; v += blockDim.x) { sp += expf(t[v] + beta * q[v] - mp); sq += expf(q[v] - mq); }
-  sp = block_sum(sp, redv);
-  sq = block_sum(sq, redv);
-  if (threadIdx.x == 0) {
+  float m[2] = {-INFINITY, -INFINITY}, s[2] = {0.f, 0.f};              // [0] effective target, [1] draft
+  // an entry of -inf adds nothing; a NaN makes the sum NaN (fmaxf ignores it)
+  auto rel = [](float e, float mx) { return e == -INFINITY ? 0.f : expf(e - mx); };
+  constexpr int U = 8;
+  for (int base = v0 + threadIdx.x; base < v1; base += U * 256) {
+    float e[2][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int v = base + u * 256;
+      e[0][u] = v < v1 ? t[v] : -INFINITY;
+      e[1][u] = v < v1 ? q[v] : -INFINITY;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) e[0][u] = base + u * 256 < v1 ? e[0][u] + beta * e[1][u] : -INFINITY;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      float mn = m[k];
+#pragma unroll
+      for (int u = 0; u < U; ++u) mn = fmaxf(mn, e[k][u]);
+      s[k] *= rel(m[k], mn);
+#pragma unroll
+      for (int u = 0; u < U; ++u) s[k] += rel(e[k][u], mn);
+      m[k] = mn;
+    }
+  }
+  // wave, then block (4 waves, in wave order)
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const float mw = wave_max(m[k]);
+    s[k] = wave_sum(s[k] * (m[k] == -INFINITY ? 1.f : expf(m[k] - mw)));   // nothing seen: s is 0, or NaN
+    m[k] = mw;
+  }
+  if ((threadIdx.x & 63) == 0) {
+    float* r = red[threadIdx.x >> 6];
+    r[0] = m[0]; r[1] = s[0]; r[2] = m[1]; r[3] = s[1];
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const int k = threadIdx.x * 2;
+    float mb = -INFINITY, sb = 0.f;
+    for (int w = 0; w < 4; ++w) mb = fmaxf(mb, red[w][k]);
+    for (int w = 0; w < 4; ++w) sb += red[w][k + 1] * (red[w][k] == -INFINITY ? 1.f : expf(red[w][k] - mb));
     float* o = part + ((size_t)(sl * G1 + i) * ACC_CHUNKS + ch) * ACC_PART;
-    o[0] = mp; o[1] = sp; o[2] = mq; o[3] = sq;
+    o[k] = mb; o[k + 1] = sb;
   }
 }
 
-// grid (gamma_max+1, n_seqs, ACC_CHUNKS): row i of sequence slot si, vocabulary chunk ch.  Writes the chunk's
+// grid (rows, n_seqs, ACC_CHUNKS), 512 threads: row i of sequence slot si, vocabulary chunk ch.  Writes the chunk's
 // candidates (token emitted if this row is where drafting is cut) and, from chunk 0, rej (row's draft rejected).
-__global__ __launch_bounds__(256) void accept_rows_kernel(const float* __restrict__ tl, const float* __restrict__ ring,
+__global__ __launch_bounds__(512) void accept_rows_kernel(const float* __restrict__ tl, const float* __restrict__ ring,
                                                           const int* __restrict__ draft_tok, AccArgs aa, int G1, int V, int mode,
                                                           uint64_t seed, uint32_t step, int phase, float* __restrict__ part,
-                                                          int* __restrict__ rej, const int* __restrict__ done_z) {
+                                                          int* __restrict__ rej) {
   __shared__ float redv[16];
   __shared__ int redi[16];
   const int si = blockIdx.y, ch = blockIdx.z, s = aa.seq[si], sl = aa.slot[si];
   const int gamma = aa.gamma[si];
-  const int i = phase ? gamma : blockIdx.x;
-  if (!phase && i >= gamma) return;
-  if (phase && done_z && done_z[sl] >= 0) return;
+  int i;
+  if (!acc_row(phase, gamma, blockIdx.x, i)) return;
   const float beta = aa.beta[si];
   const float* t = tl + (size_t)(sl * G1 + i) * V;
   const float* q = ring + (size_t)(aa.qslot[si] * G1 + i) * V;
@@ -656,12 +715,32 @@ __global__ __launch_bounds__(256) void accept_rows_kernel(const float* __restric
   float* o = prow + ch * ACC_PART;
   int v0, v1;
   acc_chunk_range(V, ch, v0, v1);
+  // four consecutive entries (one Philox block) per thread and round; 16-byte loads where the row starts on 16 bytes
+  const bool wide = ((reinterpret_cast<uintptr_t>(t) | reinterpret_cast<uintptr_t>(q)) & 15) == 0;
+  auto load4 = [&](int v, float (&tv)[4], float (&qv)[4]) {
+    if (wide && v + 4 <= v1) {
+      const float4 a = *reinterpret_cast<const float4*>(t + v), b = *reinterpret_cast<const float4*>(q + v);
+      tv[0] = a.x; tv[1] = a.y; tv[2] = a.z; tv[3] = a.w;
+      qv[0] = b.x; qv[1] = b.y; qv[2] = b.z; qv[3] = b.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        tv[e] = v + e < v1 ? t[v + e] : -INFINITY;
+        qv[e] = v + e < v1 ? q[v + e] : -INFINITY;
+      }
+    }
+  };
   if (mode == 0) {
     float best = -INFINITY;
     int bi = 0x7fffffff;
-    for (int v = v0 + threadIdx.x; v < v1; v += blockDim.x) {
-      const float e = t[v] + beta * q[v];
-      if (e > best) { best = e; bi = v; }
+    for (int v = v0 + threadIdx.x * 4; v < v1; v += blockDim.x * 4) {
+      float tv[4], qv[4];
+      load4(v, tv, qv);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x = tv[e] + beta * qv[e];
+        if (v + e < v1 && x > best) { best = x; bi = v + e; }
+      }
     }
     block_argmax(best, bi, redv, redi);
     if (threadIdx.x == 0) {
@@ -670,32 +749,35 @@ __global__ __launch_bounds__(256) void accept_rows_kernel(const float* __restric
     }
     return;
   }
-  // log-sum-exp of effective target and of draft logits from the chunk statistics
-  float mp = -INFINITY, mq = -INFINITY;
-  for (int c = 0; c < ACC_CHUNKS; ++c) { mp = fmaxf(mp, prow[c * ACC_PART]); mq = fmaxf(mq, prow[c * ACC_PART + 2]); }
-  float sp = 0.f, sq = 0.f;
-  for (int c = 0; c < ACC_CHUNKS; ++c) {
-    const float m1 = prow[c * ACC_PART], m2 = prow[c * ACC_PART + 2];
-    if (m1 > -INFINITY) sp += prow[c * ACC_PART + 1] * expf(m1 - mp);
-    if (m2 > -INFINITY) sq += prow[c * ACC_PART + 3] * expf(m2 - mq);
-  }
+  // log-sum-exp of effective target and of draft logits from the chunk statistics: one chunk per lane, combined in the same
+  // order in every block of the row
+  const float* pc = prow + (threadIdx.x & 15) * ACC_PART;
+  const float m1 = pc[0], s1 = pc[1], m2 = pc[2], s2 = pc[3];
+  float mp = m1, mq = m2;
+#pragma unroll
+  for (int x = 8; x > 0; x >>= 1) { mp = fmaxf(mp, __shfl_xor(mp, x, 64)); mq = fmaxf(mq, __shfl_xor(mq, x, 64)); }
+  float sp = m1 > -INFINITY ? s1 * expf(m1 - mp) : 0.f, sq = m2 > -INFINITY ? s2 * expf(m2 - mq) : 0.f;
+#pragma unroll
+  for (int x = 8; x > 0; x >>= 1) { sp += __shfl_xor(sp, x, 64); sq += __shfl_xor(sq, x, 64); }
   const float lsp = mp + logf(sp), lsq = mq + logf(sq);
   // candidate token: Gumbel-max over log max(0, p - q) (rows < gamma) or log p (bonus row);
   // if no residual mass exists the row falls back to log p with the same noise
   float best = -INFINITY, bestp = -INFINITY;
   int bi = 0x7fffffff, bip = 0x7fffffff;
   for (int blk = (v0 >> 2) + threadIdx.x; blk * 4 < v1; blk += blockDim.x) {
+    float tv[4], qv[4];
+    load4(blk * 4, tv, qv);
     const uint4 b = vocab_bits(seed, s, step, (uint32_t)(i + 1), PURPOSE_NEXT, (uint32_t)blk);
     const float g4[4] = {gumbel(u01(b.x)), gumbel(u01(b.y)), gumbel(u01(b.z)), gumbel(u01(b.w))};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int v = blk * 4 + e;
       if (v < v1) {
-        const float lp = t[v] + beta * q[v] - lsp;
+        const float lp = tv[e] + beta * qv[e] - lsp;
         const float kp = lp + g4[e];
         if (kp > bestp) { bestp = kp; bip = v; }
         if (i < gamma) {
-          const float w = expf(lp) - expf(q[v] - lsq);
+          const float w = expf(lp) - expf(qv[e] - lsq);
           if (w > 0.f) {
             const float kr = logf(w) + g4[e];
             if (kr > best) { best = kr; bi = v; }
@@ -722,55 +804,58 @@ __global__ __launch_bounds__(256) void accept_rows_kernel(const float* __restric
   }
 }
 
-// Phase 0: n = first rejected row (or gamma).  n < gamma: next token = row n's candidate, tokens appended, results
-// (n, z) to the caller's arrays and to pinned host memory.  n = gamma: the bonus row has not been evaluated yet
-// (its draft logits need one more draft forward): the drafts are appended and (gamma, -1) says that phase 1, which
-// takes the token of row gamma, is still to come.  The ticket is written last; the host polls for it.
-// skip_done (phase 1): leave a sequence alone whose phase-0 result already holds a token (out_z >= 0).
+// n = first rejected row (or gamma).  n < gamma: next token = row n's candidate, tokens appended, results (n, z) to the
+// caller's arrays and to pinned host memory.  n = gamma: the bonus row's candidate if it has been evaluated (phases
+// BONUS and ALL); in phase DRAFTS its draft logits still need one more draft forward: the drafts are appended and
+// (gamma, -1) says that phase BONUS is still to come.  The ticket is written last; the host polls for it.
 // tokens and the host words may be null (acceptance on caller-held logits without a context).
-__global__ void accept_finalize_kernel(const float* __restrict__ part, const int* __restrict__ rej, const int* __restrict__ draft_tok,
+// One wave per sequence: 16 lanes look at a row's 16 chunks, so that the rows' candidates are a few rounds of loads (a
+// serial walk over rows and chunks took 50 us for 16 greedy windows).
+__global__ __launch_bounds__(64) void accept_finalize_kernel(const float* __restrict__ part, const int* __restrict__ rej, const int* __restrict__ draft_tok,
                                        AccArgs aa, int G1, int mode, int phase, int max_seq, int* __restrict__ tokens,
                                        int* __restrict__ out_n, int* __restrict__ out_z, int* __restrict__ host_res,
-                                       int* __restrict__ host_tick, int ticket, int skip_done, int V, int* host_bad) {
+                                       int* __restrict__ host_tick, int ticket, int V, int* host_bad) {
+  static_assert(ACC_CHUNKS == 16, "one lane per chunk, four rows at a time");
   const int si = blockIdx.x, s = aa.seq[si], sl = aa.slot[si], qs = aa.qslot[si];
-  const int gamma = aa.gamma[si];
-  if (phase && skip_done && out_z[sl] >= 0) return;
+  const int gamma = aa.gamma[si], lane = threadIdx.x, ch = lane & 15;
+  // best candidate over the chunks of a row (the 16 lanes of a group call it with their chunk's; all get the result)
+  auto over_chunks = [](float& v, int& id) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) take_better(v, id, __shfl_xor(v, o, 64), __shfl_xor(id, o, 64));
+  };
   int n = gamma;
-  if (!phase) {
+  if (phase != ACC_PHASE_BONUS) {
     if (mode == 0) {
       // greedy: row i's draft is rejected when it differs from the row's argmax
-      for (int i = gamma - 1; i >= 0; --i) {
-        const float* pr = part + (size_t)(sl * G1 + i) * ACC_CHUNKS * ACC_PART;
-        float best = -INFINITY;
-        int bi = 0x7fffffff;
-        for (int c = 0; c < ACC_CHUNKS; ++c) {
-          const float v = pr[c * ACC_PART + 6];
-          const int id = __float_as_int(pr[c * ACC_PART + 7]);
-          if (v > best || (v == best && id < bi)) { best = v; bi = id; }
-        }
-        if (bi != draft_tok[qs * G1 + i]) n = i;
+      for (int i0 = 0; i0 < gamma && n == gamma; i0 += 4) {
+        const int i = i0 + (lane >> 4), ic = min(i, gamma - 1);
+        const float* pr = part + ((size_t)(sl * G1 + ic) * ACC_CHUNKS + ch) * ACC_PART;
+        float best = pr[6];
+        int bi = __float_as_int(pr[7]);
+        // a chunk without a finite value leaves (-inf, sentinel), as does a row of them
+        over_chunks(best, bi);
+        const unsigned long long bad = __ballot(i < gamma && bi != draft_tok[qs * G1 + ic]);
+        if (bad) n = i0 + (__ffsll(bad) - 1) / 16;
       }
     } else {
-      for (int i = gamma - 1; i >= 0; --i)
-        if (rej[sl * G1 + i]) n = i;
+      for (int i0 = 0; i0 < gamma && n == gamma; i0 += 64) {
+        const unsigned long long bad = __ballot(i0 + lane < gamma && rej[sl * G1 + min(i0 + lane, gamma - 1)]);
+        if (bad) n = i0 + __ffsll(bad) - 1;
+      }
     }
   }
   int z = -1;
-  if (phase || n < gamma) {
+  if (phase != ACC_PHASE_DRAFTS || n < gamma) {
     // the emitted token: best residual candidate of row n over the chunks, else best candidate of p
-    const float* pr = part + (size_t)(sl * G1 + n) * ACC_CHUNKS * ACC_PART;
-    float best = -INFINITY, bestp = -INFINITY;
-    int bi = 0x7fffffff, bip = 0x7fffffff;
-    for (int c = 0; c < ACC_CHUNKS; ++c) {
-      const float v = pr[c * ACC_PART + 4], vp = pr[c * ACC_PART + 6];
-      const int id = __float_as_int(pr[c * ACC_PART + 5]), idp = __float_as_int(pr[c * ACC_PART + 7]);
-      if (v > best || (v == best && id < bi)) { best = v; bi = id; }
-      if (vp > bestp || (vp == bestp && idp < bip)) { bestp = vp; bip = idp; }
-    }
+    const float* pr = part + ((size_t)(sl * G1 + n) * ACC_CHUNKS + ch) * ACC_PART;
+    float best = pr[4], bestp = pr[6];
+    int bi = __float_as_int(pr[5]), bip = __float_as_int(pr[7]);
+    over_chunks(best, bi);
+    over_chunks(bestp, bip);
     z = (n < gamma && best > -INFINITY) ? bi : bip;
   }
   int* tk = tokens ? tokens + (size_t)s * max_seq + aa.len[si] : nullptr;
-  if (!phase && tk)
+  if (phase != ACC_PHASE_BONUS && tk)
     for (int k = threadIdx.x; k < n; k += blockDim.x) tk[k] = draft_tok[qs * G1 + k];
   if (threadIdx.x == 0) {
     if (z >= 0 && tk) tk[n] = checked_token(z, V, host_bad, s);   // out_z keeps the raw value: 0x7fffffff = no finite logit decided

@@ -842,13 +842,12 @@ void accept_launch(pacer_ctx* c, const AccArgs& aa, int rows, int phase, int mod
   if (rows > 0) {
     const dim3 grid(rows, aa.n_seqs, ACC_CHUNKS);
     if (mode != PACER_GREEDY)
-      PACER_LAUNCH(accept_stats_kernel, grid, dim3(256), 0, c->stream, dev_logits, c->ring, aa, c->G1, V, phase, c->acc_part,
-                   (const int*)nullptr);
-    PACER_LAUNCH(accept_rows_kernel, grid, dim3(256), 0, c->stream, dev_logits, c->ring, c->draft_tok, aa, c->G1, V, mode, seed,
-                 (uint32_t)ctr, phase, c->acc_part, c->rej, (const int*)nullptr);
+      PACER_LAUNCH(accept_stats_kernel, grid, dim3(256), 0, c->stream, dev_logits, c->ring, aa, c->G1, V, phase, c->acc_part);
+    PACER_LAUNCH(accept_rows_kernel, grid, dim3(512), 0, c->stream, dev_logits, c->ring, c->draft_tok, aa, c->G1, V, mode, seed,
+                 (uint32_t)ctr, phase, c->acc_part, c->rej);
   }
   PACER_LAUNCH(accept_finalize_kernel, dim3(aa.n_seqs), dim3(64), 0, c->stream, c->acc_part, c->rej, c->draft_tok, aa, c->G1, mode,
-               phase, c->max_seq, c->tokens, dev_n, dev_z, c->host_res_dev, c->host_res_dev + 2 * PACER_MAX_BATCH, ++c->acc_calls, 0, V,
+               phase, c->max_seq, c->tokens, dev_n, dev_z, c->host_res_dev, c->host_res_dev + 2 * PACER_MAX_BATCH, ++c->acc_calls, V,
                host_bad_dev(c));
   for (int i = 0; i < aa.n_seqs; ++i) c->seq[aa.seq[i]].acc_ticket = c->acc_calls;
 }
@@ -1451,19 +1450,15 @@ int32_t pacer_accept_noalloc(const float* dev_target_logits, const float* dev_dr
   const int G1 = gamma + 1;
   // Every word of the scratch that a launch reads was written earlier in this same call (statistics by
   // accept_stats, candidates and reject flags by accept_rows), so nothing has to start at zero.
-  for (int phase = 0; phase < (bonus_row ? 2 : 1); ++phase) {
-    const int rows = phase ? 1 : gamma;
-    if (rows > 0) {
-      const dim3 grid(rows, 1, ACC_CHUNKS);
-      const int* done = phase ? dev_z : nullptr;
-      if (mode != PACER_GREEDY)
-        hipLaunchKernelGGL(accept_stats_kernel, grid, dim3(256), 0, st, dev_target_logits, dev_draft_logits, aa, G1, vocab, phase, sc->part, done);
-      hipLaunchKernelGGL(accept_rows_kernel, grid, dim3(256), 0, st, dev_target_logits, dev_draft_logits, dev_draft_tokens, aa, G1, vocab, mode,
-                         seed, (uint32_t)ctr, phase, sc->part, sc->rej, done);
-    }
-    hipLaunchKernelGGL(accept_finalize_kernel, dim3(1), dim3(64), 0, st, sc->part, sc->rej, dev_draft_tokens, aa, G1, mode, phase, 0,
-                       (int*)nullptr, dev_n, dev_z, (int*)nullptr, (int*)nullptr, 0, 1, vocab, (int*)nullptr);
-  }
+  // The caller holds the bonus row's draft logits, so one set of launches evaluates it beside the others.
+  const int phase = bonus_row ? ACC_PHASE_ALL : ACC_PHASE_DRAFTS;
+  const dim3 grid(gamma + (bonus_row ? 1 : 0), 1, ACC_CHUNKS);
+  if (mode != PACER_GREEDY)
+    hipLaunchKernelGGL(accept_stats_kernel, grid, dim3(256), 0, st, dev_target_logits, dev_draft_logits, aa, G1, vocab, phase, sc->part);
+  hipLaunchKernelGGL(accept_rows_kernel, grid, dim3(512), 0, st, dev_target_logits, dev_draft_logits, dev_draft_tokens, aa, G1, vocab, mode, seed,
+                     (uint32_t)ctr, phase, sc->part, sc->rej);
+  hipLaunchKernelGGL(accept_finalize_kernel, dim3(1), dim3(64), 0, st, sc->part, sc->rej, dev_draft_tokens, aa, G1, mode, phase, 0, (int*)nullptr,
+                     dev_n, dev_z, (int*)nullptr, (int*)nullptr, 0, vocab, (int*)nullptr);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_noctx(PACER_EHIP, "accept_noalloc: %s", hipGetErrorString(e));
   return PACER_OK;
