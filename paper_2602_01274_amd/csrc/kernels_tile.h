@@ -1,11 +1,12 @@
-// Tiled GEMM of the bf16-weight path for many rows (gfx950): both operands staged in LDS by direct loads.
+// Tiled GEMM of the bf16-weight path for many rows (gfx950): operand and weights staged in LDS by direct loads.
 #pragma once
 #include "kernels_w16.h"
 #include <type_traits>
 
 // One wave's 1 KiB load from global memory straight into LDS: lane l's 16 bytes at base + voff go to LDS byte m0 + 16 l.
 // Written as asm because the compiler, which cannot tell the stages apart, waits for every outstanding load of this kind
-// before any LDS read; there is no output register, and the kernel counts the loads itself (s_waitcnt vmcnt).
+// before any LDS read; there is no output register, and the kernel counts the loads itself (s_waitcnt vmcnt).  m0 is the compiler's only where
+// it emits such loads itself, which these kernels leave to this function.
 __device__ __forceinline__ void load_to_lds(const void* base, unsigned voff, unsigned lds_byte) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(voff), "s"(base) : "memory");
 }
@@ -22,6 +23,23 @@ template <int N> __device__ __forceinline__ void wait_vm_lds() {   // vmcnt <= N
 __device__ __forceinline__ int stage_src(int l) { return (l & ~3) + ((l & 3) ^ ((l >> 3) & 3)); }
 __device__ __forceinline__ int stage_slot(int l) { return (l & 15) * 4 + ((l >> 4) ^ ((l >> 1) & 3)); }
 
+// More than 32 rows (batched verification, prompt passes, and some launches from 18 rows on).
+//   block   RT row tiles x CT output tiles, WR x WC waves of RT/WR x CT/WC tiles each
+//   K loop  one step of 32 inputs per barrier.  Operand (RT * HL KiB per step) and weights (CT KiB) go straight from global
+//           memory into two LDS rings: NX operand steps, NW batches of WB weight steps.  A wave reads the fragments of step
+//           k+1 from LDS between the products of step k, and issues its share of the loads of step k + NX there too.
+// Why this form (measured on MI355X):
+//   - LDS reads that a wave issues in one go after the barrier keep all waves from their products until the LDS has served
+//     all of them: 512 rows of the 7B QKV GEMM took 91 us that way and 83 us with the reads spread between the products.
+//   - A CU has about 40 KiB of loads in flight, returned in order, so an operand load that hits in L2 waits behind a weight
+//     load from HBM: what counts is the bytes a CU pulls per product, hence blocks of 64..192 tiles, and that the weights of
+//     several steps are under way together, hence their own ring with batches (80 us).
+//   - Register staging of the operand and per-wave register streams of the weights, the form this replaces: 119 us.
+// The library's GEMM with the same number of products (512 x 12288 x 8192, f16) takes 92 us on the same card; 16 x 12 tiles at
+// 1024 rows reach 1.4 PFLOP/s, which is what the card's largest matrix products reach (1.57) less the epilogue.
+// K slices across blocks (ksb > 1) hand their sums over as in gemm_w16_kernel.  Blocks that share weights (same output
+// tiles, other rows) get consecutive slots on one XCD (block id mod 8), so that the later ones find them in that L2.
+// Tiles and row tiles that do not exist are replaced by the nearest one that does; their products are never stored.
 template <int EPI, int RT, int CT, int WR, int WC, int HL, int NX, int WB, int NW>
 __global__ __launch_bounds__(WR * WC * 64, 1) void gemm_tile_kernel(const GemmArgs ga, int n_tiles, int n_groups, int row_groups, int ksb) {
   constexpr int WV = WR * WC, MR = RT / WR, NC = CT / WC, XT = RT * HL, WT = WB * CT;

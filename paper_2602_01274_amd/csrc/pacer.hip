@@ -282,27 +282,32 @@ SplitShape pick_split_shape(int n_tiles, int KT, int rows, int hl) {
   return best;
 }
 
-// More than 32 rows: one launch of the tiled kernel.  Its block shapes (row tiles x output tiles) with the wave layout and
-// LDS rings each is built with; X(i, RT, CT, WR, WC, NX, WB, NW), i = index in the table.
+// The tiled kernel's block shapes (row tiles x output tiles) with the wave layout and LDS rings each is built with;
+// X(i, RT, CT, WR, WC, NX, WB, NW), i = index in the table.  The shapes of two row tiles serve the target's QKV and gate/up
+// GEMMs only (see gemm_w16_tag).
 #define PACER_TILE_SHAPES(X)                                                                        \
   X(0, 4, 4, 2, 4, 4, 4, 2) X(1, 4, 8, 2, 4, 4, 2, 4) X(2, 6, 4, 2, 4, 4, 4, 2) X(3, 6, 8, 2, 4, 4, 2, 3) \
-  X(4, 8, 4, 2, 4, 4, 4, 2) X(5, 8, 8, 4, 2, 4, 2, 3) X(6, 10, 4, 2, 4, 4, 4, 2) X(7, 10, 8, 2, 4, 4, 2, 3) \
-  X(8, 12, 4, 2, 4, 4, 4, 2) X(9, 12, 8, 2, 4, 4, 2, 3) X(10, 8, 12, 4, 2, 3, 4, 2) X(11, 8, 22, 4, 2, 3, 1, 3) \
-  X(12, 16, 12, 4, 2, 3, 2, 2)
-struct TileShape { int rt, ct; };
+  X(4, 8, 4, 2, 4, 4, 4, 2) X(5, 8, 8, 4, 2, 4, 2, 3) X(6, 10, 4, 2, 4, 4, 4, 2) X(7, 10, 8, 2, 4, 4, 2, 4) \
+  X(8, 12, 4, 2, 4, 4, 4, 2) X(9, 12, 8, 2, 4, 4, 2, 3) X(10, 8, 12, 4, 2, 3, 2, 4) X(11, 8, 22, 4, 2, 3, 1, 4) \
+  X(12, 16, 12, 4, 2, 3, 2, 2) X(13, 2, 3, 2, 3, 8, 2, 8) X(14, 2, 4, 2, 4, 8, 4, 4) X(15, 2, 6, 2, 3, 6, 2, 4) \
+  X(16, 2, 7, 1, 7, 6, 2, 4) X(17, 2, 8, 2, 4, 6, 2, 4) X(18, 2, 10, 2, 5, 6, 2, 4)
+struct TileShape { int rt, ct, threads; };
 constexpr TileShape kTileShapes[] = {
-#define X(i, RT, CT, WR, WC, NX, WB, NW) {RT, CT},
+#define X(i, RT, CT, WR, WC, NX, WB, NW) {RT, CT, WR * WC * 64},
     PACER_TILE_SHAPES(X)
 #undef X
 };
 constexpr int kNumTileShapes = sizeof(kTileShapes) / sizeof(kTileShapes[0]);
+constexpr int kTileTwoRows = 13;     // the shapes from this one on have two row tiles
 constexpr int kTileMinSteps = 8;     // K steps (of 32) of a block: at least a weight batch, and enough to fill the pipeline
 typedef void (*TileKernel)(const GemmArgs, int, int, int, int);
 template <int EPI, int HL>
 TileKernel tile_kernel(int i, int* lds_bytes) {
   switch (i) {
 #define X(i_, RT, CT, WR, WC, NX, WB, NW) \
-    case i_: *lds_bytes = (NX * RT * HL + NW * WB * CT) * 1024; return gemm_tile_kernel<EPI, RT, CT, WR, WC, HL, NX, WB, NW>;
+    case i_:                              \
+      if constexpr (i_ < kTileTwoRows || ((EPI == EPI_SWIGLU || EPI == EPI_QKV) && HL == 2)) { *lds_bytes = (NX * RT * HL + NW * WB * CT) * 1024; return gemm_tile_kernel<EPI, RT, CT, WR, WC, HL, NX, WB, NW>; } \
+      break;
     PACER_TILE_SHAPES(X)
 #undef X
   }
@@ -312,6 +317,9 @@ TileKernel tile_kernel(int i, int* lds_bytes) {
 // Block shape and K slices of a tiled launch.  The estimate (in us, fitted to microbenchmarks of the matrices of the
 // mid, 7B and 13B pairs at 40..512 rows, where its choice is on average within 2 % of the best shape):
 //   rounds of 256 blocks  x  K steps  x  max(0.12 + 0.0027 per product of two tiles, the block's share of the weight stream)
+// Ring depths were chosen in verify and prompt passes, where the weights come from HBM (a microbenchmark that cycles through
+// 1 GiB finds part of them in the memory-side cache): 8 x 22 with 4 weight batches 142 us against 158 with 3, 8 x 12 with 4
+// batches of 2 steps 93 against 99 with 2 of 4; deeper rings than the table's gained nothing or lost.
 // A step costs 0.12 for its barrier and what is issued before the matrix units are busy; the weight stream reaches
 // 26 KB per us and CU when each block has its own weights.  K slices add 1.5 + 0.6 per slice for the hand-over and 0.02 per
 // partial tile.  Slices only for shapes of at most 8 output tiles, where the accumulators of two slices fit the registers.
@@ -323,6 +331,7 @@ TilePlan pick_tile_plan(int n_tiles, int mt_total, int KT, int hl, size_t part_f
   double best_us = 1e300;
   for (int i = 0; i < kNumTileShapes; ++i) {
     const int rt = kTileShapes[i].rt, ct = kTileShapes[i].ct;
+    if ((mt_total <= 2) != (i >= kTileTwoRows)) continue;
     const int rg = (mt_total + rt - 1) / rt, ng = (n_tiles + ct - 1) / ct;
     for (int ksb : {1, 2, 3, 4, 6, 8}) {
       if (ksb > 1 && (ct > 8 || KT / ksb < kTileMinSteps || ng * rg > kSplitGroups || (size_t)ng * rg * ksb * rt * ct * 256 > part_floats)) continue;
@@ -344,7 +353,7 @@ void launch_tile(pacer_ctx* c, GemmArgs ga, int n_tiles) {
   ga.sk_cnt = c->sk_cnt;
   int lds = 0;
   const TileKernel k = tile_kernel<EPI, HL>(p.shape, &lds);
-  PACER_LAUNCH_EXT(k, dim3((unsigned)((ng + 7) / 8 * 8 * rg * p.ksb)), dim3(512), lds, c->stream, c->pe0, c->pe1, 0, ga, n_tiles, ng, rg, p.ksb);
+  PACER_LAUNCH_EXT(k, dim3((unsigned)((ng + 7) / 8 * 8 * rg * p.ksb)), dim3(kTileShapes[p.shape].threads), lds, c->stream, c->pe0, c->pe1, 0, ga, n_tiles, ng, rg, p.ksb);
 }
 // the blocks keep their stages in dynamic LDS, up to 152 of the CU's 160 KiB
 template <int EPI, int HL>
@@ -352,6 +361,7 @@ hipError_t tile_lds_limits() {
   for (int i = 0; i < kNumTileShapes; ++i) {
     int lds = 0;
     const TileKernel k = tile_kernel<EPI, HL>(i, &lds);
+    if (!k) continue;
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
   }
@@ -377,7 +387,13 @@ void gemm_w16_tag(pacer_ctx* c, GemmArgs ga, int n_tiles, int K) {
   ga.nt_end = ga.nt_begin + n_tiles;
   const bool many = n_tiles >= 512;
   const bool even = n_tiles % 2 == 0;
-  if (mt_total > 2 && ga.KT >= kTileMinSteps) {
+  // Tiled kernel: more than 32 rows, and from 18 rows on the target's QKV and gate/up GEMMs with many tiles and K steps (the
+  // streaming kernel's second row tile costs it two more products and 16 more fetched rows per step; 7B at 27 rows in a
+  // verify pass: QKV 32.0 -> 26.3 us, gate/up 46.6 -> 41.8).  Its other launches up to 32 rows stay streamed: down 27.0 against
+  // 27.1, O 11.4 / 16.6, LM head 48.8 / 54.0, and gate/up at 17 rows 34.7 / 35.9: the stream's HBM latency, which the
+  // streaming kernel's eight waves of register loads cover better than the rings, bounds those.
+  const bool two_rows = TAG == 0 && HL == 2 && (EPI == EPI_QKV || EPI == EPI_SWIGLU) && many && ga.KT >= 64 && ga.R > 17;
+  if (ga.KT >= kTileMinSteps && (mt_total > 2 || two_rows)) {
     if (TAG == 0) prof_begin(c);
     launch_tile<EPI, HL>(c, ga, n_tiles);
     if (TAG == 0) prof_end(c, (double)n_tiles * 16.0 * K * 2.0);
