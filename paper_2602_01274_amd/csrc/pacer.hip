@@ -533,6 +533,20 @@ void run_layers_w16(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows&
     if (most >= 2 && !two_tiles_short && R <= c->prows) kps = ((max_keys + most - 1) / most + 31) / 32 * 32;
   }
   const int S = (max_keys + kps - 1) / kps;
+  // Attention blocks start longest sequence first, so that the short ones fill the launch's tail (16 sequences of 256..2048
+  // keys, 40 heads: 89.5 -> 85.3 us).  order: 4 bits per grid position, ties in list order.
+  uint64_t order = 0;
+  {
+    int perm[PK_MAXB], keys[PK_MAXB];
+    for (int i = 0; i < sr.n_seqs; ++i) {
+      const int k = sr.pos0[i] + sr.row_off[i + 1] - sr.row_off[i];
+      int at = i;
+      for (; at > 0 && keys[at - 1] < k; --at) { keys[at] = keys[at - 1]; perm[at] = perm[at - 1]; }
+      keys[at] = k;
+      perm[at] = i;
+    }
+    for (int i = 0; i < sr.n_seqs; ++i) order |= (uint64_t)perm[i] << (4 * i);
+  }
   GemmArgs base{};
   base.R = R;
   base.sr = sr;
@@ -565,14 +579,6 @@ void run_layers_w16(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows&
       // (7B shape, 550 keys, warm cache: 7.1 us against 10.0 us).  Long contexts and batches are bound by the
       // cache traffic and keep the two-tile kernel.
       const bool rt_split = max_rows > 16 && S == 1 && max_keys < 1000 && H * sr.n_seqs <= 64;
-      // Blocks start longest sequence first, so that the short ones fill the launch's tail (16 sequences of 256..2048 keys,
-      // 40 heads: 89.5 -> 85.3 us).  order: 4 bits per grid position.
-      int perm[PK_MAXB];
-      for (int i = 0; i < sr.n_seqs; ++i) perm[i] = i;
-      auto keys_of = [&](int i) { return sr.pos0[i] + sr.row_off[i + 1] - sr.row_off[i]; };
-      std::stable_sort(perm, perm + sr.n_seqs, [&](int a, int b) { return keys_of(a) > keys_of(b); });
-      uint64_t order = 0;
-      for (int i = 0; i < sr.n_seqs; ++i) order |= (uint64_t)perm[i] << (4 * i);
       const int mrows = rt_split ? 16 : max_rows;
       const dim3 grid(rt_split ? 2 * S : S, H, sr.n_seqs);
       // LDS for the wave states: 8 waves x live rows x (hd + 4) floats
