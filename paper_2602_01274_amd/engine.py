@@ -29,6 +29,7 @@ class Session:
         self.max_seq, self.max_batch = max_seq, max_batch
         self.stream = torch.cuda.current_stream().cuda_stream
         self.keep = []                      # tensors the library borrows
+        self._taps = {}                     # buffer -> views into the workspace, one per sequence
         self.not_finite = torch.zeros(1, dtype=torch.int32, device="cuda")   # weights that do not fit a half float
         cfg_t = B.model_cfg(w["target"] | {"n_layers": len(target["layers"])}, max_seq, self.dtype)
         cfg_d = B.model_cfg(w["draft"], max_seq, self.dtype)
@@ -115,16 +116,26 @@ class Session:
         B.pacer_bind(self.ctx, which, B.T_HEAD, 0, head)
 
     # ---- taps ----------------------------------------------------------------------------
-    def _peek(self, seq, what, dtype):
-        p, nb = B.pacer_peek(self.ctx, seq, what)
-        off = p - self.ws_view.data_ptr()
-        return self.ws_view[off:off + nb].view(dtype)
+    def _peek(self, seq, what, dtype, cols=None):
+        """View of one of a sequence's workspace buffers.  The workspace is bound once and holds a buffer's sequences one
+        after the other, so their views are made together when the buffer is first looked at (16-sequence
+        draft step of the 68M draft, three buffers each: 239 us with views made per call, 105 us)."""
+        views = self._taps.get(what)
+        if views is None:
+            p, nb = B.pacer_peek(self.ctx, 0, what)
+            off = p - self.ws_view.data_ptr()
+            t = self.ws_view[off:off + nb * self.max_batch].view(dtype)
+            t = t.view(self.max_batch, -1) if cols is None else t.view(self.max_batch, -1, cols)
+            views = self._taps[what] = [t[i] for i in range(self.max_batch)]
+        if not 0 <= seq < self.max_batch:
+            B.pacer_peek(self.ctx, seq, what)      # raises
+        return views[seq]
 
     def draft_logits(self, seq=0):
-        return self._peek(seq, B.PEEK_DRAFT_LOGITS, torch.float32).view(self.G1, self.V)
+        return self._peek(seq, B.PEEK_DRAFT_LOGITS, torch.float32, self.V)
 
     def draft_hidden(self, seq=0):
-        return self._peek(seq, B.PEEK_DRAFT_HIDDEN, torch.float32).view(self.G1, self.dD)
+        return self._peek(seq, B.PEEK_DRAFT_HIDDEN, torch.float32, self.dD)
 
     def draft_tokens(self, seq=0):
         return self._peek(seq, B.PEEK_DRAFT_TOKENS, torch.int32)
@@ -297,6 +308,7 @@ class Session:
             torch.cuda.synchronize()
             B.pacer_destroy(self.ctx)
             self.ctx = None
+            self._taps.clear()
 
     def __del__(self):
         try:
