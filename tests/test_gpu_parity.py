@@ -256,6 +256,22 @@ def test_batch_mid_bf16_eight_sequences_wide_gemm():
     _run_batch("mid", [40, 75, 150, 260, 33, 97, 201, 64], [1.0, 2.3, 3.7, 5.0, 4.0, 3.0, 2.0, 4.5], 4, 2e-2, 2e-2)
 
 
+@pytest.mark.parametrize("n_seqs,gamma", [(3, 10), (4, 11), (7, 6), (16, 12)])
+def test_mid_batch_rows_at_the_tiled_gemm_edges(n_seqs, gamma):
+    """33 rows (first size past the streaming kernels, one row in the third tile), 48 (three full tiles), 49, and 208 (the
+    largest of a batch of this pair: two row groups), with prompts whose lengths are in no order.  Bound as in the other
+    bf16 tests."""
+    prompts = [40, 150, 33, 260, 1, 75, 64, 201, 17, 97, 16, 130, 48, 31, 180, 90][:n_seqs]
+    _run_batch("mid", prompts, ([1.0, 2.3, 3.7, 5.0] * 4)[:n_seqs], 2, 2e-2, 2e-2, fixed_gamma=gamma, ragged=False)
+
+
+@pytest.mark.parametrize("n_seqs,gamma", [(3, 8), (2, 15)])
+def test_7b_width_two_row_tiles_tiled(n_seqs, gamma):
+    """27 and 32 rows at the 7B width: QKV and gate/up take the tiled kernel's two-row-tile shapes (n odd against their
+    column tiles), the other GEMMs stream."""
+    _run_batch("7b", [75, 20, 40][:n_seqs], [3.0, 4.0, 2.0][:n_seqs], 1, 2e-2, 2e-2, n_layers_target=2, fixed_gamma=gamma, ragged=False, max_seq=160)
+
+
 def test_13b_width_four_layers_batch_against_oracle():
     """The shapes of workload `13b_batch` (d 5120, 40 heads of 128, FFN 13824, V 32000) at a depth the oracle can
     afford, 12 sequences, ragged prompts and windows, per-sequence beta: up to 204 verify rows through the

@@ -3,6 +3,8 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import pacer_oracle as po
+from oracle import philox
 from paper_2602_01274_amd import binding as B
 from paper_2602_01274_amd import synth
 
@@ -185,3 +187,57 @@ def test_accept_noalloc_bad_values_do_not_index_out_of_range(mode):
     n, z = run(nan, dl, dt)
     assert z == 0x7FFFFFFF and 0 <= n <= gamma
     assert run(tl, dl, dt) == ref
+
+
+@pytest.mark.parametrize("gamma,vocab,shift", [(1, 1, 0), (2, 15, 0), (3, 17, 1), (5, 1023, 0), (16, 4096, 1), (31, 4099, 0), (4, 32000, 2)])
+def test_accept_noalloc_against_float64_at_odd_sizes(gamma, vocab, shift):
+    """One call per mode and coupling on random logits: vocabularies below and just above the 16 chunks, rows that are not a
+    multiple of four floats, logits that start off the 16-byte boundary (`shift` floats), the largest window; rows that are
+    all accepted (bonus row in the same launches) and rejections at every place the draws give.  Decisions are the
+    oracle's; one is left out only where the oracle's own margin is below what f32 log-probabilities can move it: a
+    log-sum-exp over <= 32000 f32 terms of magnitude <= 60 is good to 1e-5 (2 ulp of 60 each, summed pairwise), and a
+    margin is the difference of a few of them."""
+    eps = 1e-4
+    rng = np.random.default_rng(100 * gamma + vocab)
+    stream = torch.cuda.current_stream().cuda_stream
+    out_n = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    out_z = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+
+    def dev(a):
+        flat = torch.zeros(a.size + shift, dtype=torch.float32, device="cuda")
+        flat[shift:] = torch.from_numpy(a.reshape(-1)).cuda()
+        return flat[shift:].view(a.shape)
+
+    compared = set()
+    for trial in range(8):
+        beta = [0.0, 1.0, 4.0, 30.0][trial % 4]
+        t = (2 * rng.standard_normal((gamma + 1, vocab))).astype(np.float32)
+        d = rng.standard_normal((gamma + 1, vocab)).astype(np.float32)
+        eff = t.astype(np.float64) + float(np.float32(beta)) * d
+        y = np.array([int(np.argmax(eff[k] if trial < 4 else d[k])) for k in range(gamma)], dtype=np.int32)
+        for mode in (B.GREEDY, B.SAMPLE):
+            if mode == B.GREEDY:
+                key = eff
+                n = po.first_rejection([1.0 if int(np.argmax(eff[k])) == y[k] else -1.0 for k in range(gamma)], [0.0] * gamma)
+                margin = np.inf
+            else:
+                P, Q = po.softmax(eff), po.softmax(d.astype(np.float64))
+                ratios = np.array([P[k, y[k]] / Q[k, y[k]] for k in range(gamma)])
+                r = np.array([philox.scalar_uniform(11, 2, trial, k + 1, philox.PURPOSE_ACCEPT) for k in range(gamma)])
+                n = po.first_rejection(ratios, r)
+                margin = np.abs(np.log(np.maximum(ratios, 1e-300)) - np.log(r))[:n + 1].min()
+                with np.errstate(divide="ignore"):
+                    w = np.log(P[n] if n == gamma else po.residual_dist(P[n], Q[n]))
+                key = np.tile(w + philox.gumbel(philox.vocab_uniforms(11, 2, trial, n + 1, philox.PURPOSE_NEXT, vocab)), (gamma + 1, 1))
+            top = np.sort(key[n])[::-1]
+            if vocab > 1:
+                margin = min(margin, top[0] - top[1])
+            # residual mass that itself is the difference of nearly equal probabilities has no margin in f32
+            if not margin > eps * max(1.0, beta) or (mode == B.SAMPLE and n < gamma and np.maximum(0.0, P[n] - Q[n]).sum() < 1e-2):
+                continue
+            B.pacer_accept_noalloc(dev(t), dev(d), torch.from_numpy(y).cuda(), gamma, True, vocab, mode, beta, 11, trial, 2,
+                                   out_n, out_z, stream)
+            torch.cuda.synchronize()
+            assert (int(out_n.item()), int(out_z.item())) == (n, int(np.argmax(key[n]))), (mode, trial, margin)
+            compared.add(mode)
+    assert len(compared) == 2
