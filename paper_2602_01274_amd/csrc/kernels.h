@@ -595,8 +595,8 @@ __global__ void mb_head_kernel(const float* __restrict__ xn, int ldx, const floa
 
 // ------------------------------------------------------------------ acceptance (Eq. 5)
 // slot: the sequence's index in the verify call that wrote the logits (row slot*G1 + i of tl, entry slot of the
-// caller's n / z arrays).  The kernels run in two phases: phase 0 covers rows i < gamma (everything a step needs
-// unless every draft is accepted), phase 1 the bonus row i = gamma of the sequences that accepted all drafts.
+// caller's n / z arrays).  The kernels run over the rows i < gamma (ACC_PHASE_DRAFTS: everything a step needs unless
+// every draft is accepted), the bonus row i = gamma of the sequences that accepted all drafts (ACC_PHASE_BONUS), or both.
 // qslot: the sequence's block of G1 rows in the draft logits and draft token buffers (the sequence id for a context's
 // rings); seq itself keys the random streams and indexes the committed tokens and the host words.
 struct AccArgs { int n_seqs; int seq[PK_MAXB]; int slot[PK_MAXB]; int qslot[PK_MAXB]; int gamma[PK_MAXB]; int len[PK_MAXB]; float beta[PK_MAXB]; };
