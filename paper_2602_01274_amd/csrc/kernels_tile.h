@@ -271,7 +271,7 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void gemm_tile_kernel(const GemmAr
     for (int b = b0; b < b0 + BCH && b < MR; ++b) {
       if (wr * MR + b >= mtb) continue;
       const int m = (mt_lo + wr * MR + b) * 16 + (lane & 15);
-      float sq = 0.f;
+      u64 ssq = 0;
 #pragma unroll
       for (int a = 0; a < NC; ++a) {
         const int nt = nt0 + wc * NC + a;
@@ -282,9 +282,10 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void gemm_tile_kernel(const GemmAr
 #pragma unroll
           for (int r = 0; r < 4; ++r) s2[r] = __shfl_xor(s[r], 32, 64);
         }
-        sq += gemm_epilogue<EPI, true>(ga, rc[b], ax[b - b0][a], nt, m, lane, s, s2);
+        const float sq = gemm_epilogue<EPI, true>(ga, rc[b], ax[b - b0][a], nt, m, lane, s, s2);
+        if (EPI == EPI_RESID) ssq += tile_ssq(sq);
       }
-      if (EPI == EPI_RESID) add_row_ssq(ga, rc[b], m, lane, sq);
+      if (EPI == EPI_RESID) add_row_ssq(ga, rc[b], m, lane, ssq);
     }
   }
 }

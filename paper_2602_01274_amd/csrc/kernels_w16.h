@@ -311,11 +311,16 @@ __device__ __forceinline__ EpiAux epi_aux(const GemmArgs& ga, const RowCtx& rc, 
   }
   return x;
 }
-// sum of a row's squares over the tile's outputs into the row's accumulator (all 64 lanes call it; sq: this lane's part)
-__device__ __forceinline__ void add_row_ssq(const GemmArgs& ga, const RowCtx& rc, int m, int l, float sq) {
+// A row's squares over one tile's 16 outputs as a fixed-point number (all 64 lanes call it; sq: this lane's part), and the
+// addition to the row's accumulator.  Kernels with several tiles per wave add the tiles' numbers, which are whole, before the
+// one atomic: the accumulator ends up with the same bits however the tiles are dealt to waves and blocks.
+__device__ __forceinline__ u64 tile_ssq(float sq) {
   sq += __shfl_xor(sq, 16, 64);
   sq += __shfl_xor(sq, 32, 64);
-  if (rc.live && (l >> 4) == 0) atomicAdd(ga.ssq_out + (size_t)(blockIdx.x % SSQ_SUB) * ga.ssq_stride + m, (u64)(sq * SSQ_SCALE + 0.5f));
+  return (u64)(sq * SSQ_SCALE + 0.5f);
+}
+__device__ __forceinline__ void add_row_ssq(const GemmArgs& ga, const RowCtx& rc, int m, int l, u64 fixed) {
+  if (rc.live && (l >> 4) == 0) atomicAdd(ga.ssq_out + (size_t)(blockIdx.x % SSQ_SUB) * ga.ssq_stride + m, fixed);
 }
 // 4 x 4 transpose of v among the four lanes of a quad: lane i gets v[i] of lanes 0..3
 __device__ __forceinline__ void quad_transpose(float (&v)[4], int l) {
@@ -335,7 +340,7 @@ __device__ __forceinline__ void quad_transpose(float (&v)[4], int l) {
 // Epilogue of one accumulator lane, shared by the GEMM kernels.  Lane l of a 16x16 result tile holds tile rows (outputs)
 // 4*(l/16)..+3 of activation row m; s2 holds the same of lane l ^ 32, whose outputs are the partners i+8 resp. i-8
 // (paired weight layouts: rotation pairs of QKV, gate/up of SwiGLU).  All 64 lanes of the tile call this together.
-// RESID returns the lane's part of the row's sum of squares, for add_row_ssq.
+// RESID returns the lane's part of the row's sum of squares over this tile, for tile_ssq.
 // VT: rows of a tile may be 16 consecutive positions (prompt rows): V is stored 4 positions at a time where they are.
 template <int EPI, bool VT = false>
 __device__ __forceinline__ float gemm_epilogue(const GemmArgs& ga, const RowCtx& rc, const EpiAux& ax, int nt, int m, int l, f32x4 s, f32x4 s2) {
@@ -691,7 +696,7 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 8 ? (NT >= 5 ? 2 : 4) : 1)) v
     }
     const RowCtx rc = row_ctx<EPI>(ga, m, &ssq_sum);
     const float sq = gemm_epilogue<EPI>(ga, rc, epi_aux<EPI>(ga, rc, nt, m, l), nt, m, l, s, s2);
-    if (EPI == EPI_RESID) add_row_ssq(ga, rc, m, l, sq);
+    if (EPI == EPI_RESID) add_row_ssq(ga, rc, m, l, tile_ssq(sq));
   }
 }
 

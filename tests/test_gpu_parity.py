@@ -771,3 +771,44 @@ def test_logits_without_a_finite_value_are_reported_not_faulted():
             assert int(toks.min()) >= 0 and int(toks.max()) < V
             s.prefill(prompt)
         s.close()
+
+
+def test_row_scale_is_the_same_in_streamed_and_tiled_launches():
+    """The row sums of squares behind every norm are whole numbers added tile by tile, so a row's scale has the same bits
+    whichever kernel and block shape produced the row.  With zero O and down projections the residual rows stay the
+    embeddings, and with an identity head logit v is the row's feature v times its scale: 208 rows in one launch (tiled down
+    projection, several output tiles per wave) against the same 13 rows per sequence alone (streamed).  The squares sit in
+    eight tiles per row, which is where adding tiles in 32 bits first loses bits: sums of two tiles are rounded to 24 bits,
+    about a tenth of an ulp of the total each."""
+    from paper_2602_01274_amd import binding as B
+    d = v = 2048
+    w = synth.workload("mid")
+    w["target"].update(n_layers=1, d_model=d, n_heads=16, head_dim=128, d_ffn=5504, vocab=v)
+    w["draft"]["vocab"] = v
+    w["share_embed_head"] = False
+    tgt, drf, mb = synth.make_pair(w, seed=0)
+    lw = tgt["layers"][0]
+    lw["wo"].zero_()
+    lw["wd"].zero_()
+    tgt["embed"][:, :128] *= 64.0                       # about 1.3 each: a tile's sum has more than 24 bits above the fixed point
+    tgt["embed"][:, 128:] *= 2.0 ** -4
+    tgt["head"] = torch.eye(v, dtype=torch.bfloat16)
+    nb, g = 16, 12
+    s = _session(w, tgt, drf, mb, 64, max_batch=nb)
+    drafts = synth.make_prompt(v, nb * g, 3).cuda().view(nb, g)
+    for i in range(nb):
+        s.prefill(synth.make_prompt(v, 2 + i, 20 + i).tolist(), seq=i)
+        B.pacer_begin_step(s.ctx, i)
+    for _ in range(g):
+        B.pacer_draft_step(s.ctx, list(range(nb)), B.GREEDY, 0, 0)
+    for i in range(nb):
+        s.draft_tokens(i)[:g].copy_(drafts[i])
+    B.pacer_verify(s.ctx, list(range(nb)), [g] * nb, s.logits)
+    tiled = s.logits[:, :g + 1].clone()
+    assert torch.isfinite(tiled).all() and (tiled.abs().amax(2) > 0).all()
+    differ = 0
+    for i in range(nb):
+        B.pacer_verify(s.ctx, [i], [g], s.logits)
+        differ += int((s.logits[0, :g + 1] != tiled[i]).any(1).sum())
+    s.close()
+    assert differ == 0, f"{differ} of {nb * (g + 1)} rows"
