@@ -304,6 +304,13 @@ int32_t pacer_peek(pacer_ctx* ctx, int32_t seq, int32_t what, void** dev_ptr, ui
 int32_t pacer_launch_plan(int32_t n_out, int32_t n_in, int32_t rows, int32_t operand_parts,
                           int32_t* tiles_per_block, int32_t* k_slices);
 
+/* Host only: how the tiled GEMM would be launched in this context for n_out x n_in weights on `rows` activation rows with
+ * `operand_parts` f16 parts per activation (2 up to 32 rows: the target's QKV or gate/up GEMM): row tiles and output tiles
+ * (of 16) per block, K slices across blocks.  PACER_EINVAL on a null pointer, more rows than a launch holds, or a GEMM
+ * that this kernel does not serve. */
+int32_t pacer_tile_plan(const pacer_ctx* ctx, int32_t n_out, int32_t n_in, int32_t rows, int32_t operand_parts,
+                        int32_t* row_tiles, int32_t* col_tiles, int32_t* k_slices);
+
 /* Number of kernels the context has enqueued since it was created (benchmarks: launches per call). */
 int32_t pacer_launch_count(const pacer_ctx* ctx, int64_t* n_launches);
 

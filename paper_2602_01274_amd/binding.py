@@ -28,7 +28,7 @@ EXPORTS = [
     "pacer_kv_bytes", "pacer_bind_kv", "pacer_workspace_bytes", "pacer_bind_workspace",
     "pacer_prefill", "pacer_force_commit", "pacer_begin_step", "pacer_draft_step",
     "pacer_preverify_block", "pacer_wait_stop", "pacer_verify", "pacer_accept_rollback", "pacer_get_state",
-    "pacer_peek", "pacer_profile_enable", "pacer_profile_read", "pacer_launch_plan", "pacer_accept_noalloc",
+    "pacer_peek", "pacer_profile_enable", "pacer_profile_read", "pacer_launch_plan", "pacer_tile_plan", "pacer_accept_noalloc",
     "pacer_force_stop", "pacer_launch_count", "pacer_stream_probe",
     "pacer_draft_window",
 ]
@@ -79,6 +79,7 @@ def _load():
         "pacer_peek": (i32, [vp, i32, i32, C.POINTER(vp), C.POINTER(u64)]),
         "pacer_profile_enable": (i32, [vp, i32]),
         "pacer_launch_plan": (i32, [i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]),
+        "pacer_tile_plan": (i32, [vp, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]),
         "pacer_profile_read": (i32, [vp, C.POINTER(C.c_int64), C.POINTER(C.c_double), C.POINTER(C.c_double)]),
         "pacer_stream_probe": (i32, [vp, u64, i32, vp, vp]),
         "pacer_draft_window": (i32, [vp, C.POINTER(i32), i32, i32, u64, u64, vp, vp, C.POINTER(i32)]),
@@ -243,6 +244,14 @@ def pacer_launch_plan(n_out, n_in, rows, operand_parts):
     if rc != OK:
         raise PacerError(rc, "pacer_launch_plan: bad arguments")
     return nt.value, ksb.value
+
+
+def pacer_tile_plan(ctx, n_out, n_in, rows, operand_parts):
+    rt, ct, ksb = C.c_int32(), C.c_int32(), C.c_int32()
+    rc = _lib.pacer_tile_plan(ctx, n_out, n_in, rows, operand_parts, C.byref(rt), C.byref(ct), C.byref(ksb))
+    if rc != OK:
+        raise PacerError(rc, "pacer_tile_plan: bad arguments")
+    return rt.value, ct.value, ksb.value
 
 
 def pacer_profile_enable(ctx, on):

@@ -188,8 +188,6 @@ size_t carve(pacer_ctx* c, void* base) {
   c->ssq = k.take<u64>((size_t)(2 * c->lmax + 1) * SSQ_SUB * c->rcap);
   c->pick_val = k.take<float>((size_t)c->max_batch * (V / 16 + 1));
   c->pick_idx = k.take<int>((size_t)c->max_batch * (V / 16 + 1));
-  // streaming kernel: kSplitPartFloats; tiled kernel: about 4 slices x rows x outputs (d wide); a plan that needs more is not taken
-  c->sk_part_floats = std::max(kSplitPartFloats, (size_t)4 * (c->rcap + 32) * (c->dmax + 128));
   c->sk_part = k.take<float>(c->sk_part_floats);
   c->sk_cnt = k.take<unsigned>(kSplitGroups);
   c->att_cnt = k.take<unsigned>((size_t)PK_MAXB * c->hmax * 2);
@@ -285,12 +283,11 @@ SplitShape pick_split_shape(int n_tiles, int KT, int rows, int hl) {
 // The tiled kernel's block shapes (row tiles x output tiles) with the wave layout and LDS rings each is built with;
 // X(i, RT, CT, WR, WC, NX, WB, NW), i = index in the table.  The shapes of two row tiles serve the target's QKV and gate/up
 // GEMMs only (see gemm_w16_tag).
-#define PACER_TILE_SHAPES(X)                                                                        \
-  X(0, 4, 4, 2, 4, 4, 4, 2) X(1, 4, 8, 2, 4, 4, 2, 4) X(2, 6, 4, 2, 4, 4, 4, 2) X(3, 6, 8, 2, 4, 4, 2, 3) \
-  X(4, 8, 4, 2, 4, 4, 4, 2) X(5, 8, 8, 4, 2, 4, 2, 3) X(6, 10, 4, 2, 4, 4, 4, 2) X(7, 10, 8, 2, 4, 4, 2, 4) \
-  X(8, 12, 4, 2, 4, 4, 4, 2) X(9, 12, 8, 2, 4, 4, 2, 3) X(10, 8, 12, 4, 2, 3, 2, 4) X(11, 8, 22, 4, 2, 3, 1, 4) \
-  X(12, 16, 12, 4, 2, 3, 2, 2) X(13, 2, 3, 2, 3, 8, 2, 8) X(14, 2, 4, 2, 4, 8, 4, 4) X(15, 2, 6, 2, 3, 6, 2, 4) \
-  X(16, 2, 7, 1, 7, 6, 2, 4) X(17, 2, 8, 2, 4, 6, 2, 4) X(18, 2, 10, 2, 5, 6, 2, 4)
+#define PACER_TILE_SHAPES(X)                                                                                            \
+  X(0, 4, 4, 2, 4, 4, 4, 2) X(1, 4, 8, 2, 4, 4, 2, 4) X(2, 6, 4, 2, 4, 4, 4, 2) X(3, 6, 8, 2, 4, 4, 2, 3)               \
+  X(4, 8, 8, 4, 2, 4, 2, 3) X(5, 10, 8, 2, 4, 4, 2, 4) X(6, 12, 8, 2, 4, 4, 2, 3) X(7, 8, 12, 4, 2, 3, 2, 4)             \
+  X(8, 8, 22, 4, 2, 3, 1, 4) X(9, 2, 6, 2, 3, 6, 2, 4) X(10, 2, 7, 1, 7, 6, 2, 4) X(11, 2, 8, 2, 4, 6, 2, 4)             \
+  X(12, 2, 10, 2, 5, 6, 2, 4)
 struct TileShape { int rt, ct, threads; };
 constexpr TileShape kTileShapes[] = {
 #define X(i, RT, CT, WR, WC, NX, WB, NW) {RT, CT, WR * WC * 64},
@@ -298,7 +295,7 @@ constexpr TileShape kTileShapes[] = {
 #undef X
 };
 constexpr int kNumTileShapes = sizeof(kTileShapes) / sizeof(kTileShapes[0]);
-constexpr int kTileTwoRows = 13;     // the shapes from this one on have two row tiles
+constexpr int kTileTwoRows = 9;     // the shapes from this one on have two row tiles
 constexpr int kTileMinSteps = 8;     // K steps (of 32) of a block: at least a weight batch, and enough to fill the pipeline
 typedef void (*TileKernel)(const GemmArgs, int, int, int, int);
 template <int EPI, int HL>
@@ -314,17 +311,20 @@ TileKernel tile_kernel(int i, int* lds_bytes) {
   return nullptr;
 }
 
-// Block shape and K slices of a tiled launch.  The estimate (in us, fitted to microbenchmarks of the matrices of the
-// mid, 7B and 13B pairs at 40..512 rows, where its choice is on average within 2 % of the best shape):
-//   rounds of 256 blocks  x  K steps  x  max(0.12 + 0.0027 per product of two tiles, the block's share of the weight stream)
-// Ring depths were chosen in verify and prompt passes, where the weights come from HBM (a microbenchmark that cycles through
-// 1 GiB finds part of them in the memory-side cache): 8 x 22 with 4 weight batches 142 us against 158 with 3, 8 x 12 with 4
-// batches of 2 steps 93 against 99 with 2 of 4; deeper rings than the table's gained nothing or lost.
-// A step costs 0.12 for its barrier and what is issued before the matrix units are busy; the weight stream reaches
-// 26 KB per us and CU when each block has its own weights.  K slices add 1.5 + 0.6 per slice for the hand-over and 0.02 per
-// partial tile.  Slices only for shapes of at most 8 output tiles, where the accumulators of two slices fit the registers.
-// E.g. 13B QKV (960 tiles) at 160 rows: 10 x 8 in 2 slices 50 us, 6 x 8 56, 10 x 4 57; 7B gate/up (1376) at 512 rows: 8 x 22
-// 133 us, 8 x 12 149, 8 x 8 158; 7B O (256 tiles, hi only) at 512 rows: 8 x 8 in 2 slices 25 us, 8 x 4 27.5, 10 x 8 28.
+// Block shape and K slices of a tiled launch.  Estimate in us:
+//   rounds x (1.3 + 0.14 per partial tile pair + K steps x step) + (slices: 1.2 + 0.043 per slice and tile pair)
+//   step = max(0.2 + 0.002 per product of two tiles, the block's share of the weight stream at 24 KB per us and CU)
+// A tile pair is one row tile x one output tile.  rounds: blocks of one XCD (its groups of output tiles x row groups x slices)
+// over its 32 CUs, since a group's blocks stay on one XCD: 12 groups of 20 blocks take two rounds, not one.
+// Fitted to the launches' own times inside verify and prompt passes of the mid, 7B, 13B and 33B pairs (target and draft, 18 to
+// 512 rows, 752 GEMMs with every shape and slice count): the choice is on average 0.9 % slower than the best, at worst 16 %; fitted
+// to three of the pairs, 1.0 to 1.5 % on the fourth.  (Blocks of 8 x 4, 10 x 4, 12 x 4, 16 x 12, 2 x 3 and 2 x 4 tiles gained
+// nothing over the table's.)  Constants taken from a microbenchmark, whose weights partly sat in the
+// memory-side cache, without the cost per round, sliced launches that already fill the chip: 7B QKV (768 tiles) at 160 rows
+// 10 x 4 in 4 slices 88.6 us where 6 x 8 takes 53.5, 7B gate/up (1376) at 96 rows 6 x 8 in 4 slices 73.4 where unsliced 54.5.
+// Ring depths were chosen in passes too: 8 x 22 with 4 weight batches 142 us against 158 with 3, 8 x 12 with 4 batches of 2 steps
+// 93 against 99 with 2 of 4 (7B gate/up, 512 rows); deeper rings than the table's gained nothing or lost.
+// Slices only for shapes of at most 8 output tiles, where the accumulators of two slices fit the registers.
 struct TilePlan { int shape, ksb; };
 TilePlan pick_tile_plan(int n_tiles, int mt_total, int KT, int hl, size_t part_floats) {
   TilePlan best{0, 1};
@@ -335,9 +335,9 @@ TilePlan pick_tile_plan(int n_tiles, int mt_total, int KT, int hl, size_t part_f
     const int rg = (mt_total + rt - 1) / rt, ng = (n_tiles + ct - 1) / ct;
     for (int ksb : {1, 2, 3, 4, 6, 8}) {
       if (ksb > 1 && (ct > 8 || KT / ksb < kTileMinSteps || ng * rg > kSplitGroups || (size_t)ng * rg * ksb * rt * ct * 256 > part_floats)) continue;
-      const int blocks = ng * rg * ksb;
-      const double step = std::max(0.12 + 0.0027 * hl * rt * ct, (double)ct * std::min(256, blocks) / rg / 256.0 / 26.0);
-      const double us = (double)((blocks + 255) / 256) * ((KT + ksb - 1) / ksb) * step + (ksb > 1 ? 1.5 + 0.6 * ksb + 0.02 * rt * ct * ksb : 0.0);
+      const int per_xcd = (ng + 7) / 8 * rg * ksb;
+      const double step = std::max(0.2 + 0.002 * hl * rt * ct, ct * std::min(32, per_xcd) / (32.0 * rg * 24.0));
+      const double us = (per_xcd + 31) / 32 * (1.3 + 0.14 * rt * ct + (KT + ksb - 1) / ksb * step) + (ksb > 1 ? 1.2 + 0.043 * rt * ct * ksb : 0.0);
       if (us < best_us) { best_us = us; best = {i, ksb}; }
     }
   }
@@ -368,8 +368,19 @@ hipError_t tile_lds_limits() {
   return hipSuccess;
 }
 
-// Launches the GEMM over `n_tiles` output tiles starting at ga.nt_begin; up to 32 rows with the
-// weight-streaming kernel, more with the tiled one.
+// Which launches the tiled kernel serves: more than 32 rows, and from 18 rows on the target's QKV and gate/up GEMMs with many
+// tiles and K steps.  The streaming kernel's second row tile costs it two more products and 16 more fetched rows per step;
+// streamed / tiled in verify passes: gate/up 7B 38.4 / 35.4 us at 18 rows and 48.1 / 35.6 at 32, 13B 60.1 / 54.5 and 76.8 / 52.2, 33B
+// 104.7 / 98.4 and 136.5 / 93.6; QKV 7B 26.6 / 25.7 and 33.4 / 26.0, 33B 65.2 / 64.2 and 82.1 / 62.0, 13B 34.4 / 35.4 at 19 and 41.8 / 35.6
+// at 32.  The other launches up to 32 rows stay streamed: 7B down 27.0 against 27.1 at 27 rows, O 11.4 / 16.6, LM head 48.8 / 54.0, and
+// gate/up at 17 rows 34.7 / 35.9: the stream's HBM latency, which the streaming kernel's eight waves of register loads cover
+// better than the rings, bounds those.
+bool tiled_gemm(bool two_row_gemm, int n_tiles, int KT, int rows) {
+  return KT >= kTileMinSteps && (rows > 32 || (two_row_gemm && n_tiles >= 512 && KT >= 64 && rows > 17));
+}
+
+// Launches the GEMM over `n_tiles` output tiles starting at ga.nt_begin; with the weight-streaming kernel or the tiled one
+// (tiled_gemm).
 // HL = 2: multiply the operand's hi and lo tiles (target model, all GEMMs but the O projection and the
 // LM head, whose inputs' f16 rounding hardly shows in the logits); HL = 1: hi only.
 // Launch shapes <MT, NT, WAVES, U>, all measured on MI355X (U = K steps per register set; the loop keeps
@@ -387,13 +398,7 @@ void gemm_w16_tag(pacer_ctx* c, GemmArgs ga, int n_tiles, int K) {
   ga.nt_end = ga.nt_begin + n_tiles;
   const bool many = n_tiles >= 512;
   const bool even = n_tiles % 2 == 0;
-  // Tiled kernel: more than 32 rows, and from 18 rows on the target's QKV and gate/up GEMMs with many tiles and K steps (the
-  // streaming kernel's second row tile costs it two more products and 16 more fetched rows per step; 7B at 27 rows in a
-  // verify pass: QKV 32.0 -> 26.3 us, gate/up 46.6 -> 41.8).  Its other launches up to 32 rows stay streamed: down 27.0 against
-  // 27.1, O 11.4 / 16.6, LM head 48.8 / 54.0, and gate/up at 17 rows 34.7 / 35.9: the stream's HBM latency, which the
-  // streaming kernel's eight waves of register loads cover better than the rings, bounds those.
-  const bool two_rows = TAG == 0 && HL == 2 && (EPI == EPI_QKV || EPI == EPI_SWIGLU) && many && ga.KT >= 64 && ga.R > 17;
-  if (ga.KT >= kTileMinSteps && (mt_total > 2 || two_rows)) {
+  if (tiled_gemm(TAG == 0 && HL == 2 && (EPI == EPI_QKV || EPI == EPI_SWIGLU), n_tiles, ga.KT, ga.R)) {
     if (TAG == 0) prof_begin(c);
     launch_tile<EPI, HL>(c, ga, n_tiles);
     if (TAG == 0) prof_end(c, (double)n_tiles * 16.0 * K * 2.0);
@@ -1018,6 +1023,8 @@ int32_t pacer_create(pacer_ctx** out, const pacer_model_cfg* target, const pacer
   c->hdmax = std::max(target->head_dim, draft->head_dim);
   c->max_seq = target->max_seq;
   c->lmax = std::max(target->n_layers, draft->n_layers);
+  // streaming kernel: kSplitPartFloats; tiled kernel: about 4 slices x rows x outputs (d wide); a plan that needs more is not taken
+  c->sk_part_floats = std::max(kSplitPartFloats, (size_t)4 * (c->rcap + 32) * (c->dmax + 128));
   *out = c;
   return PACER_OK;
 }
@@ -1525,6 +1532,18 @@ int32_t pacer_launch_plan(int32_t n_out, int32_t n_in, int32_t rows, int32_t ope
   const SplitShape sp = n_in / 32 >= 64 ? pick_split_shape(n_out / 16, n_in / 32, rows, operand_parts) : SplitShape{1, 1};
   *tiles_per_block = sp.nt;
   *k_slices = sp.ksb;
+  return PACER_OK;
+}
+
+int32_t pacer_tile_plan(const pacer_ctx* c, int32_t n_out, int32_t n_in, int32_t rows, int32_t operand_parts, int32_t* row_tiles,
+                        int32_t* col_tiles, int32_t* k_slices) {
+  if (!c || !row_tiles || !col_tiles || !k_slices || n_out < 16 || n_out % 16 || n_in < 32 || n_in % 32 || rows < 1 || rows > c->rcap ||
+      operand_parts < 1 || operand_parts > 2 || !tiled_gemm(operand_parts == 2, n_out / 16, n_in / 32, rows))
+    return PACER_EINVAL;
+  const TilePlan p = pick_tile_plan(n_out / 16, (rows + 15) / 16, n_in / 32, operand_parts, c->sk_part_floats);
+  *row_tiles = kTileShapes[p.shape].rt;
+  *col_tiles = kTileShapes[p.shape].ct;
+  *k_slices = p.ksb;
   return PACER_OK;
 }
 
