@@ -7,8 +7,11 @@
 // Written as asm because the compiler, which cannot tell the stages apart, waits for every outstanding load of this kind
 // before any LDS read; there is no output register, and the kernel counts the loads itself (s_waitcnt vmcnt).  m0 is the compiler's only where
 // it emits such loads itself, which these kernels leave to this function.
+// ONCE: bytes that no other block reads; they pass L2 without displacing what the next kernels find there.
+template <bool ONCE>
 __device__ __forceinline__ void load_to_lds(const void* base, unsigned voff, unsigned lds_byte) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(voff), "s"(base) : "memory");
+  if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_byte), "v"(voff), "s"(base) : "memory");
+  else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(voff), "s"(base) : "memory");
 }
 template <int N> __device__ __forceinline__ void wait_vm_lds() {   // vmcnt <= N and all LDS reads of this wave back
   static_assert(N < 64, "6-bit counter");
@@ -45,6 +48,7 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void gemm_tile_kernel(const GemmAr
   constexpr int WV = WR * WC, MR = RT / WR, NC = CT / WC, XT = RT * HL, WT = WB * CT;
   constexpr int LX = (XT + WV - 1) / WV, LW = (WT + WV - 1) / WV;      // loads per wave: operand of a step, weights of a batch
   constexpr bool SPLIT = CT <= 8;      // wider blocks always take all of K
+  constexpr bool ONCE = RT == 2;       // up to 32 rows are one row group: each weight byte is one block's
   static_assert(RT % WR == 0 && CT % WC == 0, "the waves cover the block tile");
   static_assert(NX >= 3 && NW >= 2 && (WB == 1 || WB % 2 == 0) && (NW > 2 || WB > 1), "");
   extern __shared__ __align__(16) u32x4 tile_stage[];       // [NX][XT][64] operand, then [NW][WB][CT][64] weights
@@ -79,11 +83,11 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void gemm_tile_kernel(const GemmAr
     wdst[i] = lds0 + (NX * XT + j * CT + c) * 1024;
   }
   auto issue_x = [&](int i, int slot_x) {
-    load_to_lds(xk, xv[i], xdst[i] + slot_x * (XT * 1024));
+    load_to_lds<false>(xk, xv[i], xdst[i] + slot_x * (XT * 1024));
     if (i == LX - 1) xk += (unsigned)mtt * 2048;
   };
   auto issue_w = [&](int i, int k0, int slot_w) {                        // k0: the batch's first step; a short last batch starts earlier
-    load_to_lds(w0 + ((size_t)min(k0, nk - WB) << 10), wv[i], wdst[i] + slot_w * (WT * 1024));
+    load_to_lds<ONCE>(w0 + ((size_t)min(k0, nk - WB) << 10), wv[i], wdst[i] + slot_w * (WT * 1024));
   };
   f32x4 acc[NC][MR];
 #pragma unroll

@@ -370,9 +370,10 @@ hipError_t tile_lds_limits() {
 
 // Which launches the tiled kernel serves: more than 32 rows, and from 18 rows on the target's QKV and gate/up GEMMs with many
 // tiles and K steps.  The streaming kernel's second row tile costs it two more products and 16 more fetched rows per step;
-// streamed / tiled in verify passes: gate/up 7B 38.4 / 35.4 us at 18 rows and 48.1 / 35.6 at 32, 13B 60.1 / 54.5 and 76.8 / 52.2, 33B
-// 104.7 / 98.4 and 136.5 / 93.6; QKV 7B 26.6 / 25.7 and 33.4 / 26.0, 33B 65.2 / 64.2 and 82.1 / 62.0, 13B 34.4 / 35.4 at 19 and 41.8 / 35.6
-// at 32.  The other launches up to 32 rows stay streamed: 7B down 27.0 against 27.1 at 27 rows, O 11.4 / 16.6, LM head 48.8 / 54.0, and
+// streamed / tiled in verify passes at 20 and at 32 rows: gate/up 7B 39.1 / 33.3 and 48.0 / 33.7 us, 13B 61.9 / 49.2 and
+// 77.0 / 49.4, 33B 108.8 / 85.6 and 136.7 / 85.6; QKV 7B 27.4 / 24.1 and 33.1 / 24.2, 13B 34.2 / 33.2 and 42.7 / 33.8, 33B 67.5 / 57.5 and
+// 81.6 / 57.1; d 2048 gate/up 14.4 / 14.2 and 17.2 / 14.3, d 3072 gate/up 21.4 / 22.6 and 26.0 / 22.9, QKV 20.5 / 18.3 and 24.6 / 18.5.
+// The other launches up to 32 rows stay streamed: 7B down 27.0 against 27.1 at 27 rows, O 11.4 / 16.6, LM head 48.8 / 54.0, and
 // gate/up at 17 rows 34.7 / 35.9: the stream's HBM latency, which the streaming kernel's eight waves of register loads cover
 // better than the rings, bounds those.
 bool tiled_gemm(bool two_row_gemm, int n_tiles, int KT, int rows) {

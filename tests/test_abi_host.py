@@ -129,10 +129,10 @@ def test_launch_plan_of_the_few_tile_projections(B):
 
 
 @pytest.mark.parametrize("pair,n_out,n_in,rows,parts,us", [
-    ("7b", 22016, 4096, 18, 2, {(2, 6, 1): 35.4, (2, 8, 1): 39.1, (2, 10, 1): 46.7}),
-    ("7b", 12288, 4096, 19, 2, {(2, 6, 2): 25.6, (2, 8, 2): 27.8, (2, 6, 3): 30.0}),
-    ("13b_batch", 27648, 5120, 32, 2, {(2, 7, 1): 52.1, (2, 8, 1): 52.8, (2, 10, 1): 57.5}),
-    ("33b", 21504, 7168, 24, 2, {(2, 6, 1): 60.9, (2, 7, 1): 66.8, (2, 8, 3): 68.7}),
+    ("7b", 22016, 4096, 20, 2, {(2, 6, 1): 33.3, (2, 8, 1): 37.8, (2, 10, 1): 43.2}),
+    ("7b", 12288, 4096, 20, 2, {(2, 6, 2): 24.1, (2, 8, 2): 25.9, (2, 6, 3): 28.5}),
+    ("13b_batch", 27648, 5120, 32, 2, {(2, 7, 1): 49.4, (2, 8, 1): 50.3, (2, 10, 1): 55.2}),
+    ("33b", 21504, 7168, 24, 2, {(2, 6, 1): 58.1, (2, 7, 1): 62.7, (2, 8, 3): 64.7}),
     ("7b", 22016, 4096, 96, 2, {(6, 8, 1): 54.5, (8, 8, 1): 54.7, (6, 8, 4): 73.4}),
     ("7b", 12288, 4096, 112, 2, {(4, 8, 1): 44.3, (8, 8, 2): 44.6, (4, 8, 4): 61.4}),
     ("7b", 12288, 4096, 160, 2, {(6, 8, 1): 53.5, (10, 8, 2): 55.3, (8, 8, 1): 58.0, (10, 4, 4): 88.6}),
