@@ -44,3 +44,19 @@ def test_weights_that_one_block_reads_pass_the_cache(tile_kernels):
         loads = [i for i in ins if i.startswith("global_load_lds")]
         nt = [i for i in loads if i.endswith(" nt")]
         assert loads and (0 < len(nt) < len(loads) if rt == 2 else not nt), name
+
+
+def test_direct_loads_take_m0_from_the_compiler(tile_kernels):
+    """The loads into LDS take their LDS address from m0.  No asm text writes that register behind the compiler's back: it is
+    an operand, so each load has an instruction of the compiler's before it that sets m0, and the wait state."""
+    csrc = os.path.join(ROOT, "paper_2602_01274_amd", "csrc")
+    for f in os.listdir(csrc):
+        for text in re.findall(r'"((?:[^"\\]|\\.)*)"', open(os.path.join(csrc, f)).read()):
+            assert not re.search(r"\bs_\w+ m0\b", text), (f, text)
+    for name, ins in tile_kernels.items():
+        fresh = False                                  # m0 set since the last load
+        for prev, x in zip(ins, ins[1:]):
+            fresh = fresh or bool(re.match(r"s_\w+ m0, ", x))
+            if x.startswith("global_load_lds"):
+                assert fresh and prev == "s_nop 0", name
+                fresh = False
