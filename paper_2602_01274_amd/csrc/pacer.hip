@@ -296,7 +296,8 @@ constexpr TileShape kTileShapes[] = {
 };
 constexpr int kNumTileShapes = sizeof(kTileShapes) / sizeof(kTileShapes[0]);
 constexpr int kTileTwoRows = 9;     // the shapes from this one on have two row tiles
-constexpr int kTileMinSteps = 8;     // K steps (of 32) of a block: at least a weight batch, and enough to fill the pipeline
+constexpr int kTileMinSteps = 4;     // K steps (of 32) of a GEMM: a weight batch
+constexpr int kTileSliceSteps = 8;   // and of a K slice: enough to fill the pipeline
 typedef void (*TileKernel)(const GemmArgs, int, int, int, int);
 template <int EPI, int HL>
 TileKernel tile_kernel(int i, int* lds_bytes) {
@@ -334,7 +335,7 @@ TilePlan pick_tile_plan(int n_tiles, int mt_total, int KT, int hl, size_t part_f
     if ((mt_total <= 2) != (i >= kTileTwoRows)) continue;
     const int rg = (mt_total + rt - 1) / rt, ng = (n_tiles + ct - 1) / ct;
     for (int ksb : {1, 2, 3, 4, 6, 8}) {
-      if (ksb > 1 && (ct > 8 || KT / ksb < kTileMinSteps || ng * rg > kSplitGroups || (size_t)ng * rg * ksb * rt * ct * 256 > part_floats)) continue;
+      if (ksb > 1 && (ct > 8 || KT / ksb < kTileSliceSteps || ng * rg > kSplitGroups || (size_t)ng * rg * ksb * rt * ct * 256 > part_floats)) continue;
       const int per_xcd = (ng + 7) / 8 * rg * ksb;
       const double step = std::max(0.2 + 0.002 * hl * rt * ct, ct * std::min(32, per_xcd) / (32.0 * rg * 24.0));
       const double us = (per_xcd + 31) / 32 * (1.3 + 0.14 * rt * ct + (KT + ksb - 1) / ksb * step) + (ksb > 1 ? 1.2 + 0.043 * rt * ct * ksb : 0.0);

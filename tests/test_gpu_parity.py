@@ -812,3 +812,42 @@ def test_row_scale_is_the_same_in_streamed_and_tiled_launches():
         differ += int((s.logits[0, :g + 1] != tiled[i]).any(1).sum())
     s.close()
     assert differ == 0, f"{differ} of {nb * (g + 1)} rows"
+
+
+@pytest.mark.parametrize("d,f", [(128, 160), (192, 224), (256, 128)])
+def test_short_contractions_take_one_launch_for_a_prompt(d, f):
+    """bf16 models whose matrices have 4 to 8 K steps of 32 (d 128..256, FFN 128..224): the smallest the tiled GEMM takes, some
+    with a ragged last batch of weight steps.  A 300-token prompt (299 rows in one pass) costs one launch per GEMM: streamed 32
+    rows at a time it would be ten.  Then steps against the oracle, which look at the caches the prompt left, and a 33-row
+    verify pass."""
+    from paper_2602_01274_amd import binding as B
+    w = synth.workload("mid")
+    w["target"].update(n_layers=2, d_model=d, n_heads=d // 64, d_ffn=f, vocab=512)
+    w["draft"].update(n_layers=1, d_model=d, n_heads=d // 64, d_ffn=f, vocab=512)
+    tgt, drf, mb = synth.make_pair(w, seed=0, gain_jitter=0.1)
+    s = _session(w, tgt, drf, mb, 416, max_batch=3)
+    prompt = synth.make_prompt(512, 300, 1).tolist()
+    n0 = B.pacer_launch_count(s.ctx)
+    s.prefill(prompt)
+    n = B.pacer_launch_count(s.ctx) - n0
+    # embedding, layers of five launches (the target's last one stops after QKV), M_B's input and QKV, a few for the hidden rows
+    assert n <= 2 * (1 + 5 * 2) + 6, n
+    o = helpers.build_oracle(w, tgt, drf, mb, mode=po.GREEDY, seed=0, max_seq=416, cache=True)
+    o.prefill(prompt)
+    ck = StepChecker(s, o, 2e-2, 2e-2, mode=po.GREEDY, seed=0)
+    for _ in range(3):
+        ck.step()
+    ck.assert_flip_budget()
+    s.close()
+    ids = [prompt[:40], prompt[40:77], prompt[77:150]]
+    s = _session(w, tgt, drf, mb, 416, max_batch=3)
+    for i, p in enumerate(ids):
+        s.prefill(p, seq=i)
+    rs = s.step_batch([0, 1, 2], betas=[3.0] * 3, record=True, fixed_gamma=10)
+    for i, (p, r) in enumerate(zip(ids, rs)):
+        o = helpers.build_oracle(w, tgt, drf, mb, mode=po.GREEDY, seed=0, max_seq=416, cache=True, seq=i, beta=3.0)
+        o.prefill(p)
+        ro = o.step(fixed_gamma=10)
+        g = next((k for k in range(10) if ro["draft_tokens"][k] != r["draft_tokens"][k]), 10)      # rows of equal prefixes
+        assert rel_err(r["target_logits"][:g + 1].cpu().numpy(), ro["target_logits"][:g + 1]) < 2e-2
+    s.close()
