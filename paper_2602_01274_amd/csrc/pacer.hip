@@ -318,7 +318,7 @@ TileKernel tile_kernel(int i, int* lds_bytes) {
 // A tile pair is one row tile x one output tile.  rounds: blocks of one XCD (its groups of output tiles x row groups x slices)
 // over its 32 CUs, since a group's blocks stay on one XCD: 12 groups of 20 blocks take two rounds, not one.
 // Fitted to the launches' own times inside verify and prompt passes of the mid, 7B, 13B and 33B pairs (target and draft, 18 to
-// 512 rows, 752 GEMMs with every shape and slice count): the choice is on average 0.9 % slower than the best, at worst 16 %; fitted
+// 512 rows, 752 GEMMs with every shape and slice count): the choice is on average 0.8 % slower than the best, at worst 16 %; fitted
 // to three of the pairs, 1.0 to 1.5 % on the fourth.  (Blocks of 8 x 4, 10 x 4, 12 x 4, 16 x 12, 2 x 3 and 2 x 4 tiles gained
 // nothing over the table's.)  Constants taken from a microbenchmark, whose weights partly sat in the
 // memory-side cache, without the cost per round, sliced launches that already fill the chip: 7B QKV (768 tiles) at 160 rows
@@ -1025,8 +1025,9 @@ int32_t pacer_create(pacer_ctx** out, const pacer_model_cfg* target, const pacer
   c->hdmax = std::max(target->head_dim, draft->head_dim);
   c->max_seq = target->max_seq;
   c->lmax = std::max(target->n_layers, draft->n_layers);
-  // streaming kernel: kSplitPartFloats; tiled kernel: about 4 slices x rows x outputs (d wide); a plan that needs more is not taken
-  c->sk_part_floats = std::max(kSplitPartFloats, (size_t)4 * (c->rcap + 32) * (c->dmax + 128));
+  // streaming kernel: kSplitPartFloats; tiled kernel: about 3 slices x rows x outputs (d wide).  A plan that needs more is not
+  // taken; with room for four slices the plans of the measured sizes (see pick_tile_plan) are no faster.
+  c->sk_part_floats = std::max(kSplitPartFloats, (size_t)3 * (c->rcap + 32) * (c->dmax + 128));
   *out = c;
   return PACER_OK;
 }

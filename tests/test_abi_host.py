@@ -158,6 +158,19 @@ def test_tile_plan_against_launch_times_measured_in_passes(B, pair, n_out, n_in,
     assert plan in us and us[plan] <= 1.08 * min(us.values()), plan
 
 
+@pytest.mark.parametrize("pair,max_batch,nbytes", [("mid", 1, 46086656), ("7b", 1, 230280192), ("13b_batch", 16, 640774144), ("33b", 1, 399339520)])
+def test_workspace_need_does_not_grow(B, pair, max_batch, nbytes):
+    """A program keeps a workspace of the size it was told: the need of the named pairs at 1024 positions stays within what it
+    was when the layout was fixed (a buffer of that size has to go on binding)."""
+    from paper_2602_01274_amd import synth
+    w = synth.workload(pair)
+    ctx = B.pacer_create(B.model_cfg(w["target"], 1024, "bf16"), B.model_cfg(w["draft"], 1024, "bf16"),
+                         B.PvCfg(w["block"], w["gamma_max"], 0.5, 1.05, 0), max_batch, 0)
+    need = B.pacer_workspace_bytes(ctx)
+    B.pacer_destroy(ctx)
+    assert need <= nbytes
+
+
 def test_accept_noalloc_validates_on_the_host(B):
     """The allocation-free acceptance call checks its arguments before it touches a GPU: null pointers, modes,
     and a window beyond the fixed scratch's capacity (refused with PACER_EOVERFLOW and a message naming the limit)."""
