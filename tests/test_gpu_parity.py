@@ -851,3 +851,85 @@ def test_short_contractions_take_one_launch_for_a_prompt(d, f):
         g = next((k for k in range(10) if ro["draft_tokens"][k] != r["draft_tokens"][k]), 10)      # rows of equal prefixes
         assert rel_err(r["target_logits"][:g + 1].cpu().numpy(), ro["target_logits"][:g + 1]) < 2e-2
     s.close()
+
+
+def _small_target(d, f, v, n_layers, gamma_max=4):
+    """A pair whose target has the given sizes (heads of 64) and whose draft is as small as they get."""
+    w = synth.workload("mid")
+    w["target"].update(n_layers=n_layers, d_model=d, n_heads=d // 64, head_dim=64, d_ffn=f, vocab=v)
+    w["draft"].update(n_layers=1, d_model=128, n_heads=2, head_dim=64, d_ffn=128, vocab=v)
+    w["share_embed_head"] = False
+    w["gamma_max"] = gamma_max
+    return w, *synth.make_pair(w, seed=0, gain_jitter=0.1)
+
+
+def _tile_plan(s, w, gemm, rows):
+    from paper_2602_01274_amd import binding as B
+    d, f = w["target"]["d_model"], w["target"]["d_ffn"]
+    n_out, n_in, parts = {"qkv": (3 * d, d, 2), "o": (d, d, 1), "gate_up": (2 * f, d, 2), "down": (d, f, 2), "head": (w["target"]["vocab"], d, 1)}[gemm]
+    return B.pacer_tile_plan(s.ctx, n_out, n_in, rows, parts), n_out // 16
+
+
+@pytest.mark.parametrize("d,f,v,n_seqs,g1,gemm,plan", [
+    (2048, 8224, 528, 2, 10, "gate_up", (2, 6, 1)),
+    (2048, 4640, 528, 3, 7, "gate_up", (2, 6, 2)),
+    (2048, 12352, 528, 1, 19, "gate_up", (2, 7, 1)),
+    (2048, 6176, 528, 2, 16, "gate_up", (2, 7, 2)),
+    (2048, 7200, 528, 2, 11, "gate_up", (2, 8, 2)),
+    (2048, 16416, 528, 3, 9, "gate_up", (2, 10, 1)),
+    (256, 256, 528, 2, 17, "head", (4, 4, 1)),
+    (768, 256, 528, 3, 13, "head", (4, 4, 3)),
+    (2048, 256, 8208, 2, 17, "head", (4, 8, 3)),
+    (256, 256, 8208, 5, 16, "head", (6, 4, 1)),
+    (256, 2720, 8208, 13, 16, "gate_up", (4, 8, 1)),
+    (256, 2720, 8208, 13, 16, "head", (6, 8, 1)),
+    (256, 8224, 528, 13, 16, "gate_up", (8, 12, 1)),
+])
+def test_tiled_gemm_shapes_with_a_ragged_last_column_block_verify(d, f, v, n_seqs, g1, gemm, plan):
+    """Every block shape of the tiled GEMM that a verify pass can take, at sizes whose output tiles do not divide by the
+    block's: the last block repeats a tile and drops its results.  All logits of all rows against the oracle's forward over
+    the same tokens.  Bound as in the other bf16 tests."""
+    from paper_2602_01274_amd import binding as B
+    w, tgt, drf, mb = _small_target(d, f, v, 1, gamma_max=(g1 + 2) // 4 * 4)
+    s = _session(w, tgt, drf, mb, 96, max_batch=n_seqs)
+    got, tiles = _tile_plan(s, w, gemm, n_seqs * g1)
+    assert got == plan and tiles % plan[1], (got, tiles)
+    ids = [synth.make_prompt(v, 3 + 5 * i, 40 + i).tolist() for i in range(n_seqs)]
+    drafts = synth.make_prompt(v, n_seqs * (g1 - 1), 3).view(n_seqs, g1 - 1)
+    for i, p in enumerate(ids):
+        s.prefill(p, seq=i)
+        B.pacer_begin_step(s.ctx, i)
+    for _ in range(g1 - 1):
+        B.pacer_draft_step(s.ctx, list(range(n_seqs)), B.GREEDY, 0, 0)
+    for i in range(n_seqs):
+        s.draft_tokens(i)[:g1 - 1].copy_(drafts[i].cuda())
+    B.pacer_verify(s.ctx, list(range(n_seqs)), [g1 - 1] * n_seqs, s.logits)
+    ow, cfg = helpers.to_oracle(tgt, cache=True), helpers.oracle_cfg(w["target"])
+    for i, p in enumerate(ids):
+        _, ref = po.lm_forward(ow, cfg, p + drafts[i].tolist(), po.KVCache(1, d, 128))
+        err = rel_err(s.logits[i, :g1].cpu().numpy(), ref[-g1:])
+        assert err < 2e-2, (i, err)
+    s.close()
+
+
+@pytest.mark.parametrize("f,rows,plan", [(2720, 511, (8, 8, 1)), (4128, 416, (10, 8, 1)), (4128, 511, (12, 8, 1)), (8224, 416, (8, 22, 1))])
+def test_tiled_gemm_shapes_with_a_ragged_last_column_block_prompt(f, rows, plan):
+    """The block shapes that only a prompt pass takes, again with a ragged last block of output tiles (gate/up at d 256) and row
+    groups of unequal size.  The second layer's cached keys, which hold every row's first-layer output, against the oracle's:
+    f16 rounds a key to 2^-11 of its value (5 RMS at most), the rest of the bound is that of the other bf16 tests."""
+    d, v = 256, 528
+    w, tgt, drf, mb = _small_target(d, f, v, 2)
+    s = _session(w, tgt, drf, mb, 544)
+    got, tiles = _tile_plan(s, w, "gate_up", rows)
+    assert got == plan and tiles % plan[1], (got, tiles)
+    prompt = synth.make_prompt(v, rows + 1, 1).tolist()
+    s.prefill(prompt)
+    torch.cuda.synchronize()
+    oc = po.KVCache(2, d, 600)
+    po.lm_forward(helpers.to_oracle(tgt, cache=True), helpers.oracle_cfg(w["target"]), prompt[:rows], oc)
+    # K of (sequence 0, layer 1): [head][position / 16][dim / 32][(dim % 32) / 8][position % 16][dim % 8]
+    kv = s.keep[-3].view(torch.float16)
+    k = kv[2 * 544 * d:3 * 544 * d].view(d // 64, 544 // 16, 2, 4, 16, 8).permute(1, 4, 0, 2, 3, 5).reshape(544, d)[:rows].cpu().numpy()
+    err = rel_err(k, oc.K[1][:rows])
+    assert err < 2e-2, err
+    s.close()
