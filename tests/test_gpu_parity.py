@@ -148,7 +148,7 @@ def test_7b_width_long_context_4100_keys():
 
 
 def test_prompt_ingestion_1500_tokens_first_alpha_and_first_verify():
-    """Prompt ingestion (three passes of up to 512 rows through the wide GEMMs, the last one ragged, 16 slots of 32
+    """Prompt ingestion (three passes of up to 512 rows through the tiled GEMM, the last one ragged, 16 slots of 32
     positions in the attention kernel; the target's last layer stops after its K/V) is checked by what is computed
     from the caches it leaves: the pre-verification layer's first alpha values (its prefix rows), the draft logits
     and every row of the first verify pass, against the oracle, with the halting test deciding the windows."""
@@ -216,7 +216,7 @@ def test_batch_tiny_f32_sixteen_sequences():
 
 def test_batch_mid_bf16_ragged():
     """The batched workload in miniature: ragged batch, per-sequence beta in [1, 5], prompt lengths
-    spread over several attention tiles; 4 sequences x up to 13 verify rows = two 32-row GEMM chunks."""
+    spread over several attention tiles; 4 sequences x up to 13 verify rows = up to four row tiles."""
     _run_batch("mid", [40, 75, 150, 260], [1.0, 2.3, 3.7, 5.0], 6, 2e-2, 2e-2)
 
 
@@ -240,42 +240,43 @@ def test_batch_mid_bf16_bonus_row_for_part_of_the_batch():
 
 def test_7b_width_two_sequences_full_windows():
     """Two sequences with 17 verify rows each (fixed window of 16) at the 7B width: 34 rows go through the
-    wide GEMM, and attention runs as two one-tile blocks per (head, sequence)."""
+    tiled GEMM, and attention runs as two one-tile blocks per (head, sequence)."""
     _run_batch("7b", [40, 75], [3.0, 4.0], 2, 2e-2, 2e-2, n_layers_target=2, fixed_gamma=16, ragged=False, max_seq=160)
 
 
 def test_7b_width_two_sequences_eighteen_rows():
-    """Two sequences with 9 verify rows each at the 7B width: 18 rows are two row tiles of the streaming GEMM
-    (not the 17-row form), with the down projection's K split across blocks."""
+    """Two sequences with 9 verify rows each at the 7B width: 18 rows, the fewest for which QKV and gate/up are tiled; the
+    other GEMMs stream two row tiles (not the 17-row form), the down projection with its K split across blocks.  (QKV and
+    gate/up streamed with two row tiles: the mid pair's prompts of 19 to 33 tokens.)"""
     _run_batch("7b", [40, 75], [3.0, 4.0], 2, 2e-2, 2e-2, n_layers_target=2, fixed_gamma=8, ragged=False, max_seq=160)
 
 
 def test_batch_mid_bf16_eight_sequences_wide_gemm():
-    """8 sequences x up to 13 verify rows = up to 104 rows: the wide GEMM with several row groups per
-    output-tile group, ragged last row tile, per-sequence attention over different lengths."""
+    """8 sequences x up to 13 verify rows = up to 104 rows: the tiled GEMM with two row groups
+    (of four and three row tiles), ragged last row tile, per-sequence attention over different lengths."""
     _run_batch("mid", [40, 75, 150, 260, 33, 97, 201, 64], [1.0, 2.3, 3.7, 5.0, 4.0, 3.0, 2.0, 4.5], 4, 2e-2, 2e-2)
 
 
 @pytest.mark.parametrize("n_seqs,gamma", [(3, 10), (4, 11), (7, 6), (16, 12)])
 def test_mid_batch_rows_at_the_tiled_gemm_edges(n_seqs, gamma):
     """33 rows (first size past the streaming kernels, one row in the third tile), 48 (three full tiles), 49, and 208 (the
-    largest of a batch of this pair: two row groups), with prompts whose lengths are in no order.  Bound as in the other
-    bf16 tests."""
+    largest of a batch of this pair: four row groups in the layers, two in the LM head), with prompts whose lengths are in no
+    order.  Bound as in the other bf16 tests."""
     prompts = [40, 150, 33, 260, 1, 75, 64, 201, 17, 97, 16, 130, 48, 31, 180, 90][:n_seqs]
     _run_batch("mid", prompts, ([1.0, 2.3, 3.7, 5.0] * 4)[:n_seqs], 2, 2e-2, 2e-2, fixed_gamma=gamma, ragged=False)
 
 
 @pytest.mark.parametrize("n_seqs,gamma", [(3, 8), (2, 15)])
 def test_7b_width_two_row_tiles_tiled(n_seqs, gamma):
-    """27 and 32 rows at the 7B width: QKV and gate/up take the tiled kernel's two-row-tile shapes (n odd against their
-    column tiles), the other GEMMs stream."""
+    """27 and 32 rows at the 7B width: QKV (2 x 6 tiles in two K slices) and gate/up (2 x 6; 1376 tiles, so the last block has
+    two) are tiled, the other GEMMs stream."""
     _run_batch("7b", [75, 20, 40][:n_seqs], [3.0, 4.0, 2.0][:n_seqs], 1, 2e-2, 2e-2, n_layers_target=2, fixed_gamma=gamma, ragged=False, max_seq=160)
 
 
 def test_13b_width_four_layers_batch_against_oracle():
     """The shapes of workload `13b_batch` (d 5120, 40 heads of 128, FFN 13824, V 32000) at a depth the oracle can
     afford, 12 sequences, ragged prompts and windows, per-sequence beta: up to 204 verify rows through the
-    wide GEMM at the widths bench.py times (K 5120 and 13824, 960 / 320 / 1728 / 2000 output tiles; 3 and 4
+    tiled GEMM at the widths bench.py times (K 5120 and 13824, 960 / 320 / 1728 / 2000 output tiles; 6 and 8
     row tiles per block, K slices for the few-tile matrices)."""
     _run_batch("13b_batch", [18, 33, 47, 25, 60, 39, 21, 52, 30, 44, 27, 36],
                [1.0, 2.0, 3.0, 4.0, 5.0, 2.5, 3.5, 1.5, 4.5, 2.0, 3.0, 4.0], 2, 2e-2, 2e-2, max_seq=160, n_layers_target=4)
@@ -289,8 +290,9 @@ def test_13b_width_ragged_prompts_in_the_named_range():
 
 
 def test_13b_width_ten_full_windows_six_row_tiles_per_block():
-    """Ten sequences x 17 verify rows = 170 rows = 11 row tiles: the down and gate/up GEMMs run in the 8-wave
-    wide kernel with two row groups of six row tiles (the largest operand stage, 96 KiB of LDS)."""
+    """Ten sequences x 17 verify rows = 170 rows = 11 row tiles: gate/up in blocks of 12 x 8 tiles (one row group of 11, the
+    largest stage, 144 KiB of LDS), the down projection in 6 x 8 with two row groups (five and six row tiles) and three K
+    slices, O in 4 x 8 with three row groups and two slices."""
     _run_batch("13b_batch", [18, 33, 47, 25, 60, 39, 21, 52, 30, 44], [1.0, 2.0, 3.0, 4.0, 5.0, 2.5, 3.5, 1.5, 4.5, 2.0], 1, 2e-2, 2e-2,
                max_seq=160, n_layers_target=2, fixed_gamma=16, ragged=False)
 
@@ -302,15 +304,15 @@ def test_33b_width_two_layers_bf16():
 
 
 def test_33b_width_eight_sequences_down_projection_k_slices():
-    """Eight sequences x 13 verify rows = 104 rows at the 33B width: the down projection (448 output tiles)
-    runs in the 8-wave wide kernel with two K slices across blocks (56 tile groups x 2 row groups x 2)."""
+    """Eight sequences x 13 verify rows = 104 rows at the 33B width: the down projection (448 output tiles) runs in blocks of
+    8 x 8 tiles with four K slices (56 tile groups x 4), QKV in the same with three."""
     _run_batch("33b", [12, 20, 9, 16, 14, 22, 11, 18], [3.0, 2.0, 4.0, 3.5, 2.5, 3.0, 4.5, 1.5], 1, 2e-2, 2e-2,
                n_layers_target=2, fixed_gamma=12, ragged=False, max_seq=64)
 
 
 def test_13b_batch_full_depth_batch_invariance():
     """Workload `13b_batch` at full size (40 layers, 16 sequences) in the launch configuration bench.py
-    times.  Property that holds at any size: a sequence verified inside the ragged batch (wide GEMM,
+    times.  Property that holds at any size: a sequence verified inside the ragged batch (tiled GEMM,
     rows of 16 sequences) gets the logits and decisions it gets when stepped alone (weight-streaming
     GEMM) from the same state."""
     w = synth.workload("13b_batch")
@@ -331,7 +333,7 @@ def test_13b_batch_full_depth_batch_invariance():
     fresh()
     batched = s.step_batch(list(range(nb)), betas=betas, record=True)
     rows = sum(r["gamma"] + 1 for r in batched)
-    assert rows > 32                                            # the wide kernel really ran
+    assert rows > 32                                            # the tiled kernel really ran
     fresh()
     worst = 0.0
     for i in (0, 5, 10, 15):
@@ -340,7 +342,7 @@ def test_13b_batch_full_depth_batch_invariance():
         g = min(solo["gamma"], b["gamma"])
         assert solo["draft_tokens"][:g] == b["draft_tokens"][:g]
         if solo["gamma"] != b["gamma"]:
-            # the pre-verification layer ran 64 rows through the wide GEMM in the batch and 4 rows through the
+            # the pre-verification layer ran 64 rows through the tiled GEMM in the batch and 4 rows through the
             # streaming one alone: a different window is allowed only at a near-tie of the block mean
             k = g // w["block"] - 1
             mean = float(np.mean(b["alpha"][k * w["block"]:(k + 1) * w["block"]]))
@@ -471,7 +473,7 @@ def test_verify_twice_gives_the_same_bits():
 
 def test_verify_twice_gives_the_same_bits_batched_13b_width():
     """The same guard for the batched kernels: ten sequences x 17 rows = 170 rows at the 13B width put the down
-    projection through the 8-wave wide kernel with three K slices across blocks (partial tiles added by the
+    projection through the tiled kernel with three K slices across blocks and O with two (partial tiles added by the
     block that finishes last), and prompts of 40 to 1500 tokens give the sequences one to several key splits
     in one attention launch.  Repeated verify passes over the same drafts must agree bit for bit; the run
     stops at the first mismatch."""
