@@ -328,7 +328,7 @@ def main():
         "calls": calls, "context": context,
         "prefill": {"ms": round(prefill_ms, 2), "tokens": int(sum(lens)), "tok_s": round(sum(lens) / prefill_ms * 1e3, 1)},
         "roofline": {"bound": "hbm", "kernel": ("gemm_w16_kernel" if nb == 1 else "gemm_tile_kernel / gemm_w16_kernel")
-                               + ", target-model launches (template TAG 0), all shapes",
+                               + ", target-model launches, all shapes",
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "frac_of_streaming_read": round(achieved / ceiling["streaming_read_GBps"], 4),

@@ -103,16 +103,6 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   for (int i = 0; i < nw; ++i) t += red[i];
   return t;
 }
-__device__ __forceinline__ float block_max(float v, float* red) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-  v = wave_max(v);
-  __syncthreads();
-  if (lane == 0) red[w] = v;
-  __syncthreads();
-  float t = red[0];
-  for (int i = 1; i < nw; ++i) t = fmaxf(t, red[i]);
-  return t;
-}
 // Block-wide argmax; the lowest index wins among equal values.  Result valid in all threads.
 __device__ __forceinline__ void block_argmax(float& v, int& idx, float* redv, int* redi) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
@@ -599,7 +589,8 @@ __global__ void mb_head_kernel(const float* __restrict__ xn, int ldx, const floa
 // ------------------------------------------------------------------ acceptance (Eq. 5)
 // slot: the sequence's index in the verify call that wrote the logits (row slot*G1 + i of tl, entry slot of the
 // caller's n / z arrays).  The kernels run over the rows i < gamma (ACC_PHASE_DRAFTS: everything a step needs unless
-// every draft is accepted), the bonus row i = gamma of the sequences that accepted all drafts (ACC_PHASE_BONUS), or both.
+// every draft is accepted), the bonus row i = gamma of the sequences that accepted all drafts (ACC_PHASE_BONUS), or all rows
+// at once, the bonus row whether it is needed or not (ACC_PHASE_ALL: the caller already holds its draft logits).
 // qslot: the sequence's block of G1 rows in the draft logits and draft token buffers (the sequence id for a context's
 // rings); seq itself keys the random streams and indexes the committed tokens and the host words.
 struct AccArgs { int n_seqs; int seq[PK_MAXB]; int slot[PK_MAXB]; int qslot[PK_MAXB]; int gamma[PK_MAXB]; int len[PK_MAXB]; float beta[PK_MAXB]; };

@@ -23,7 +23,7 @@ template <int N> __device__ __forceinline__ void wait_vm_lds() {   // vmcnt <= N
 // its own in the staged copy (units of 16 bytes).  A load's 16-lane quarter covers 4 whole rows = 256 contiguous bytes
 // (two cache lines); taking the tile in MFMA lane order instead makes every quarter touch all eight lines of the tile,
 // four times the work of the CU's memory pipeline.  Chunk c of row r sits in slot 4r + (c ^ (r/2 % 4)), so that the
-// lanes that one LDS read cycle serves fall on different banks (SQ_LDS_BANK_CONFLICT reads 0).
+// lanes that one LDS read cycle serves fall on different banks (SQ_LDS_BANK_CONFLICT is 0 in verify and prompt passes).
 __device__ __forceinline__ int stage_src(int l) { return (l & ~3) + ((l & 3) ^ ((l >> 3) & 3)); }
 __device__ __forceinline__ int stage_slot(int l) { return (l & 15) * 4 + ((l >> 4) ^ ((l >> 1) & 3)); }
 
@@ -32,15 +32,14 @@ __device__ __forceinline__ int stage_slot(int l) { return (l & 15) * 4 + ((l >> 
 //   K loop  one step of 32 inputs per barrier.  Operand (RT * HL KiB per step) and weights (CT KiB) go straight from global
 //           memory into two LDS rings: NX operand steps, NW batches of WB weight steps.  A wave reads the fragments of step
 //           k+1 from LDS between the products of step k, and issues its share of the loads of step k + NX there too.
-// Why this form (measured on MI355X):
+// Why this form (7B QKV GEMM at 512 rows unless said otherwise):
 //   - LDS reads that a wave issues in one go after the barrier keep all waves from their products until the LDS has served
-//     all of them: 512 rows of the 7B QKV GEMM took 91 us that way and 83 us with the reads spread between the products.
-//   - A CU has about 40 KiB of loads in flight, returned in order, so an operand load that hits in L2 waits behind a weight
-//     load from HBM: what counts is the bytes a CU pulls per product, hence blocks of 64..192 tiles, and that the weights of
-//     several steps are under way together, hence their own ring with batches (80 us).
-//   - Register staging of the operand and per-wave register streams of the weights, the form this replaces: 119 us.
-// The library's GEMM with the same number of products (512 x 12288 x 8192, f16) takes 92 us on the same card; 16 x 12 tiles at
-// 1024 rows reach 1.4 PFLOP/s, which is what the card's largest matrix products reach (1.57) less the epilogue.
+//     all of them: 91 us in a microbenchmark, 83 with the reads spread between the products.
+//   - A CU's loads return in order, so an operand load that hits in L2 waits behind a weight load from HBM: what counts is the
+//     bytes a CU pulls per product, hence blocks as large as the rows and registers allow (up to 176 tile pairs), and that the
+//     weights of several steps are under way together, hence their own ring with batches (80 us).
+//   - In a prompt pass it takes 91 us; register staging of the operand with per-wave register streams of the weights, the
+//     form this replaces, took 118, and the library's GEMM with the same number of products (512 x 12288 x 8192, f16) 92.
 // K slices across blocks (ksb > 1) hand their sums over as in gemm_w16_kernel.  Blocks that share weights (same output
 // tiles, other rows) get consecutive slots on one XCD (block id mod 8), so that the later ones find them in that L2.
 // Tiles and row tiles that do not exist are replaced by the nearest one that does; their products are never stored.

@@ -356,7 +356,7 @@ void launch_tile(pacer_ctx* c, GemmArgs ga, int n_tiles) {
   const TileKernel k = tile_kernel<EPI, HL>(p.shape, &lds);
   PACER_LAUNCH_EXT(k, dim3((unsigned)((ng + 7) / 8 * 8 * rg * p.ksb)), dim3(kTileShapes[p.shape].threads), lds, c->stream, c->pe0, c->pe1, 0, ga, n_tiles, ng, rg, p.ksb);
 }
-// the blocks keep their stages in dynamic LDS, up to 152 of the CU's 160 KiB
+// the blocks keep their stages in dynamic LDS, up to 144 of the CU's 160 KiB
 template <int EPI, int HL>
 hipError_t tile_lds_limits() {
   for (int i = 0; i < kNumTileShapes; ++i) {
@@ -391,7 +391,8 @@ bool tiled_gemm(bool two_row_gemm, int n_tiles, int KT, int rows) {
 // block share an operand fetch among NT tiles; HL = 2 doubles the operand traffic from L2, which becomes
 // the limiter as rows grow.  17 rows exactly (full window + committed token): the second row tile is
 // reduced to its one live column (X17).
-// TAG gives the target model's launches their own kernel symbols; the GEMM profile counts those.
+// TAG gives the target model's streamed launches their own kernel symbols (the tiled kernel's serve all models); the GEMM
+// profile brackets the target's launches of both.
 template <int EPI, int TAG, int HL>
 void gemm_w16_tag(pacer_ctx* c, GemmArgs ga, int n_tiles, int K) {
   const int mt_total = (ga.R + 15) / 16;
