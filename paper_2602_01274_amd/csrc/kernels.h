@@ -603,8 +603,8 @@ struct AccArgs { int n_seqs; int seq[PK_MAXB]; int slot[PK_MAXB]; int qslot[PK_M
 //                         order, so every chunk of a row derives the same value), then the chunk's best
 //                         candidates; chunk 0 also takes the row's accept test
 //   accept_finalize_kernel per sequence: best candidate over the chunks of each row, first rejection, tokens
-// Rows i < gamma first; the bonus row i = gamma (whose draft logits cost one more draft forward) only for the
-// sequences that turn out to have accepted every draft.
+// In a context rows i < gamma come first; the bonus row i = gamma (whose draft logits cost one more draft forward) only for
+// the sequences that turn out to have accepted every draft.  pacer_accept_noalloc, whose caller holds them, evaluates it beside.
 #define ACC_CHUNKS 16
 #define ACC_PART 8      // floats per (row, chunk): [0..3] = mp, sp, mq, sq ; [4..7] = best, bi, bestp, bip
 
