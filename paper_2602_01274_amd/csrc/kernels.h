@@ -50,9 +50,9 @@ __device__ __forceinline__ int find_seq(const SeqRows& sr, int r) {
 // The sequence of row r with what the launch says about it.  Every table read has the same index in all lanes (scalar
 // loads that do not wait for each other), where find_seq followed by look-ups is a chain of vector loads per lane.  A launch
 // of one sequence reads only the first entries (all sixteen cost the streamed QKV launches 0.3 us each).
-struct SeqOf { int si, seq, row0, pos0; };
+struct SeqOf { int si, seq, row0, pos0, len; };
 __device__ __forceinline__ SeqOf seq_of_row(const SeqRows& sr, int r) {
-  SeqOf o{0, sr.seq[0], sr.row_off[0], sr.pos0[0]};
+  SeqOf o{0, sr.seq[0], sr.row_off[0], sr.pos0[0], sr.len[0]};
   if (sr.n_seqs > 1) {
 #pragma unroll
     for (int s = 1; s < PK_MAXB; ++s) {
@@ -61,6 +61,7 @@ __device__ __forceinline__ SeqOf seq_of_row(const SeqRows& sr, int r) {
       o.seq = in ? sr.seq[s] : o.seq;
       o.row0 = in ? sr.row_off[s] : o.row0;
       o.pos0 = in ? sr.pos0[s] : o.pos0;
+      o.len = in ? sr.len[s] : o.len;
     }
   }
   return o;
