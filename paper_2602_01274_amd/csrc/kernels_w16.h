@@ -119,20 +119,16 @@ __global__ void pack_weight_kind_kernel(uint4* __restrict__ dst, const uint16_t*
 // contiguous bytes, and MFMA lane 16*g + j reads bytes 64*j + 16*g..+15 of it.  (Storing the tile in
 // lane order instead makes a launch with 9..16 rows touch all eight 128-byte lines of every tile and
 // measured 5 to 10 % slower GEMMs; this way the lines touched follow the row count.)
-// 4 consecutive features of row m into the packed operand
-__device__ __forceinline__ void store_packed4(_Float16* __restrict__ xp, int MT_total, int m, int k0, float a, float b, float c, float d) {
-  const int kt = k0 >> 5, g = (k0 & 31) >> 3, e = k0 & 7;
+// where feature k0 of row m starts (hi part; lo is 512 elements further); 4 or 2 consecutive features there
+__device__ __forceinline__ _Float16* packed_at(_Float16* xp, int MT_total, int m, int k0) {
+  return xp + ((size_t)((k0 >> 5) * MT_total + (m >> 4)) * 128 + ((m & 15) * 4 + ((k0 & 31) >> 3))) * 8 + (k0 & 7);
+}
+__device__ __forceinline__ void store_packed4(_Float16* p, float a, float b, float c, float d) {
   typedef _Float16 half4 __attribute__((ext_vector_type(4)));
   const half4 h = {(_Float16)a, (_Float16)b, (_Float16)c, (_Float16)d};
   const half4 l = {(_Float16)(a - (float)h[0]), (_Float16)(b - (float)h[1]), (_Float16)(c - (float)h[2]), (_Float16)(d - (float)h[3])};
-  _Float16* p = xp + ((size_t)(kt * MT_total + (m >> 4)) * 128 + ((m & 15) * 4 + g)) * 8 + e;
   *reinterpret_cast<half4*>(p) = h;
   *reinterpret_cast<half4*>(p + 512) = l;
-}
-
-// where feature k0 of row m starts (hi part; lo is 512 elements further), and 2 consecutive features there
-__device__ __forceinline__ _Float16* packed_at(_Float16* xp, int MT_total, int m, int k0) {
-  return xp + ((size_t)((k0 >> 5) * MT_total + (m >> 4)) * 128 + ((m & 15) * 4 + ((k0 & 31) >> 3))) * 8 + (k0 & 7);
 }
 __device__ __forceinline__ void store_packed2(_Float16* p, float a, float b) {
   const half2v h = {(_Float16)a, (_Float16)b}, l = {(_Float16)(a - (float)h[0]), (_Float16)(b - (float)h[1])};
@@ -174,7 +170,7 @@ __device__ __forceinline__ void embed_row_w16(const uint16_t* __restrict__ e, in
     const float v0 = __uint_as_float(w.x << 16), v1 = __uint_as_float(w.x & 0xffff0000u);
     const float v2 = __uint_as_float(w.y << 16), v3 = __uint_as_float(w.y & 0xffff0000u);
     *reinterpret_cast<float4*>(o.x + (size_t)r * o.ldx + k) = make_float4(v0, v1, v2, v3);
-    store_packed4(o.xp, o.MT_total, r, k, v0 * o.g[k], v1 * o.g[k + 1], v2 * o.g[k + 2], v3 * o.g[k + 3]);
+    store_packed4(packed_at(o.xp, o.MT_total, r, k), v0 * o.g[k], v1 * o.g[k + 1], v2 * o.g[k + 2], v3 * o.g[k + 3]);
     ss += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
   }
   ss = block_sum(ss, red);
@@ -210,7 +206,7 @@ __global__ void mb_input_w16_kernel(const float* __restrict__ src, int lds, cons
     const float4 a = first ? a0 : *reinterpret_cast<const float4*>(h + k), b = first ? b0 : *reinterpret_cast<const float4*>(e + k);
     const float v0 = a.x + b.x, v1 = a.y + b.y, v2 = a.z + b.z, v3 = a.w + b.w;
     *reinterpret_cast<float4*>(x + (size_t)r * ldx + k) = make_float4(v0, v1, v2, v3);
-    store_packed4(xp, MT_total, r, k, v0 * g[k], v1 * g[k + 1], v2 * g[k + 2], v3 * g[k + 3]);
+    store_packed4(packed_at(xp, MT_total, r, k), v0 * g[k], v1 * g[k + 1], v2 * g[k + 2], v3 * g[k + 3]);
     ss += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
   }
   ss = block_sum(ss, red);
@@ -260,6 +256,7 @@ struct GemmArgs {
   uint64_t pick_seed;
   uint32_t pick_step;
   SeqRows sr;
+  u64 row_slot;          // launches of up to 16 rows: sequence slot of row m in bits 4m..4m+3
   // K split across blocks: per-block partial sums (streaming kernel, KSB > 1: [group][KSB][NT*MT][64] f32x4) and one
   // arrival counter per group of output tiles (zero between launches)
   float* sk_part;
@@ -276,20 +273,26 @@ struct RowCtx {
   int seq, draft;        // STORE with token choice: sequence id, 1-based draft index
 };
 // everything but the row scale, which waits for memory
-template <int EPI>
+// FEW: at most 16 rows, whose slots the launch lists (walking the table of 16 sequences takes a wave 110 instructions)
+template <int EPI, bool FEW = false>
 __device__ __forceinline__ RowCtx row_place(const GemmArgs& ga, int m) {
   RowCtx rc{};
   rc.live = m < ga.R;
   rc.rs = 1.f;
+  auto seq_of = [&]() {
+    if (!FEW || ga.sr.n_seqs == 1) return seq_of_row(ga.sr, m);
+    const int si = (int)(ga.row_slot >> (4 * m)) & 15;
+    return SeqOf{si, ga.sr.seq[si], ga.sr.row_off[si], ga.sr.pos0[si], ga.sr.len[si]};
+  };
   if (EPI == EPI_QKV && rc.live) {
-    const SeqOf q = seq_of_row(ga.sr, m);
+    const SeqOf q = seq_of();
     rc.si = q.si;
     rc.rl = m - q.row0;
     rc.pos = q.pos0 + rc.rl;
     rc.Kc = ga.kv + (((size_t)q.seq * ga.n_layers + ga.layer) * 2) * (size_t)ga.max_seq * ga.d;
   }
   if (EPI == EPI_STORE && rc.live) {
-    const SeqOf q = seq_of_row(ga.sr, m);
+    const SeqOf q = seq_of();
     const int rl = m - q.row0;
     rc.seq = q.seq;
     rc.draft = q.pos0 + rl - (q.len - 1) + 1;
@@ -382,9 +385,11 @@ __device__ __forceinline__ void quad_transpose(float (&v)[4], int l) {
 // 4*(l/16)..+3 of activation row m; s2 holds the same of lane l ^ 32, whose outputs are the partners i+8 resp. i-8
 // (paired weight layouts: rotation pairs of QKV, gate/up of SwiGLU).  All 64 lanes of the tile call this together.
 // RESID returns the lane's part of the row's sum of squares over this tile, for tile_ssq.
+// XP: RESID's operand goes to xp, which the caller has worked out ahead.
 // VT: rows of a tile may be 16 consecutive positions (prompt rows): V is stored 4 positions at a time where they are.
-template <int EPI, bool VT = false>
-__device__ __forceinline__ float gemm_epilogue(const GemmArgs& ga, const RowCtx& rc, const EpiAux& ax, int nt, int m, int l, f32x4 s, f32x4 s2) {
+template <int EPI, bool VT = false, bool XP = false>
+__device__ __forceinline__ float gemm_epilogue(const GemmArgs& ga, const RowCtx& rc, const EpiAux& ax, int nt, int m, int l, f32x4 s, f32x4 s2,
+                                               _Float16* xp = nullptr) {
   typedef _Float16 half4 __attribute__((ext_vector_type(4)));
   const int g4 = l >> 4;
   const bool live = rc.live;
@@ -421,10 +426,9 @@ __device__ __forceinline__ float gemm_epilogue(const GemmArgs& ga, const RowCtx&
     }
   } else if (EPI == EPI_RESID) {
     if (live) {
-      const int n = nt * 16 + g4 * 4;
       const f32x4 xn = ax.a + s, gn = ax.b;
       *reinterpret_cast<f32x4*>(ax.p) = xn;
-      store_packed4(ga.xp_out, ga.mt_total_out, m, n, xn[0] * gn[0], xn[1] * gn[1], xn[2] * gn[2], xn[3] * gn[3]);
+      store_packed4(XP ? xp : packed_at(ga.xp_out, ga.mt_total_out, m, nt * 16 + g4 * 4), xn[0] * gn[0], xn[1] * gn[1], xn[2] * gn[2], xn[3] * gn[3]);
       sq = xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
     }
   } else if (EPI == EPI_SWIGLU) {
@@ -750,6 +754,118 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 8 ? (NT >= 5 ? 2 : 4) : 1)) v
   }
 }
 
+// ------------------------------------------------------------------ GEMM of a few rows over a short K
+// Up to 16 rows and a K that a block's waves hold in registers: the draft and pre-verification layers, narrow targets.
+//   block   one output tile, or half of one (HALF); WAVES waves take the K tiles round-robin, U steps each
+// Such a launch takes 3 to 5 us of which the bytes take a fraction; what bounds it is one wave's way through the kernel:
+// each memory round trip (0.2 to 1 us), and 2.4 to 3.7 ns for every instruction of a wave that is alone on its SIMD, so 300
+// instructions are one more us.  Hence: everything is requested at once, without a loop; loads go through buffer
+// descriptors whose range ends with the tile's last K step (a step past it reads zeros: no clamps, no selects) and whose
+// lane offsets are the same for all steps; the arguments that the loads need come first and in registers (kernarg preload);
+// what the epilogue needs is worked out while the weights travel, down to the addresses it stores to.
+// Kernel durations, gemm_w16_kernel -> this: 1 row of d 768 O 3.7 -> 3.2 us, down 5.3 -> 4.4, gate/up 4.8 -> 4.2; 13 rows hi+lo
+// QKV 4.3 -> 4.2, gate/up 4.9 -> 4.5, down 6.0 -> 5.5; 1 row of d 2048 O and down together 13.4 -> 11.5, QKV 7.1 -> 6.5.
+// HALF: a matrix of at most 128 tiles leaves CUs idle.  A weight load takes 8 outputs of two K tiles: lanes of tile rows 0..7
+// bring K tile 2s, the others 2s + 1.  Both K tiles' products run with the whole register; of the first the lanes of result
+// rows 0..7 count, of the second the others, and the epilogue adds the two.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+// v of lane l ^ 32
+__device__ __forceinline__ float other_half(float v, int lane) {
+  const unsigned u = __float_as_uint(v);
+  const auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(lane < 32 ? p[1] : p[0]);
+}
+template <int EPI, int TAG, int HL, int WAVES, int U, int HALF>
+__global__ __launch_bounds__(WAVES * 64) void gemm_row_kernel(const u32x4* W, const u32x4* X, int KT, int R, int nt_begin, const GemmArgs ga) {
+  static_assert(!HALF || (EPI != EPI_QKV && EPI != EPI_SWIGLU), "half tiles have no pairs");
+  constexpr int KP = HALF ? 2 : 1;                     // K tiles per step
+  constexpr int NT_LOAD = 2;                           // cache policy: non-temporal
+  __shared__ f32x4 red[WAVES - 1][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int half = HALF ? blockIdx.x & 1 : 0, nt = nt_begin + (HALF ? blockIdx.x >> 1 : blockIdx.x);
+  const auto wr = buffer_of(W + (size_t)nt * KT * 64, KT * 1024), xr = buffer_of(X, KT * 2048);
+  const int wv = HALF ? (lane & 48) * 16 + half * 128 + (lane & 7) * 16 + ((lane >> 3) & 1) * 1024 : lane * 16;
+  const int xv = min(lane & 15, R - 1) * 64 + (lane >> 4) * 16;      // lanes of rows that do not exist repeat the last one's
+  u32x4 A[U], B[U][KP * HL];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int s = (wave + u * WAVES) * KP;
+    A[u] = __builtin_amdgcn_raw_buffer_load_b128(wr, wv, s * 1024, NT_LOAD);
+#pragma unroll
+    for (int j = 0; j < KP; ++j)
+#pragma unroll
+      for (int h = 0; h < HL; ++h) B[u][j * HL + h] = __builtin_amdgcn_raw_buffer_load_b128(xr, xv + j * 2048 + h * 1024, s * 2048, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const int m = lane & 15, l = HALF ? (lane & 31) + 32 * half : lane;  // l: the lane whose outputs this one finishes
+  RowCtx rc{};
+  EpiAux ax{};
+  _Float16* xp = nullptr;
+  u64* ssq_to = nullptr;
+  // the arguments of the epilogue in one round trip
+  if (EPI == EPI_RESID) asm volatile("" ::"s"(ga.R), "s"(ga.out), "s"(ga.xp_out), "s"(ga.g_next), "s"(ga.ssq_out), "s"(ga.ldo), "s"(ga.mt_total_out), "s"(ga.ssq_stride));
+  else asm volatile("" ::"s"(ga.R), "s"(ga.ssq_in), "s"(ga.ssq_stride), "s"(ga.inv_dim), "s"(ga.eps));
+  if (EPI == EPI_SWIGLU) asm volatile("" ::"s"(ga.xp_out), "s"(ga.mt_total_out));
+  if (EPI == EPI_QKV) asm volatile("" ::"s"(ga.qp), "s"(ga.kv), "s"(ga.rope), "s"(ga.max_seq), "s"(ga.H), "s"(ga.hd), "s"(ga.d), "s"(ga.layer), "s"(ga.n_layers), "s"(ga.sr.n_seqs), "s"(ga.sr.seq[0]), "s"(ga.sr.row_off[0]), "s"(ga.sr.pos0[0]));
+  if (EPI == EPI_STORE) asm volatile("" ::"s"(ga.out), "s"(ga.pick_val), "s"(ga.pick_idx), "s"(ga.pick_tiles), "s"(ga.pick_mode), "s"(ga.pick_seed), "s"(ga.pick_step), "s"(ga.sr.n_seqs), "s"(ga.sr.seq[0]), "s"(ga.sr.row_off[0]), "s"(ga.sr.pos0[0]), "s"(ga.sr.len[0]));
+  if (wave == 0) {
+    u64 ssq = 0;
+    if (EPI != EPI_RESID) {
+      const u64* sp = ga.ssq_in + (size_t)((lane >> 4) * 2) * ga.ssq_stride + min(m, R - 1);
+      ssq = sp[0] + sp[ga.ssq_stride];
+    }
+    rc = row_place<EPI, true>(ga, m);
+    ax = epi_aux<EPI>(ga, rc, nt, m, l);
+    if (EPI == EPI_RESID) {
+      xp = packed_at(ga.xp_out, ga.mt_total_out, m, nt * 16 + (l >> 4) * 4);
+      ssq_to = ga.ssq_out + (size_t)(blockIdx.x % SSQ_SUB) * ga.ssq_stride + m;
+    } else {
+      ssq += __shfl_xor((unsigned long long)ssq, 16, 64);
+      ssq += __shfl_xor((unsigned long long)ssq, 32, 64);
+      rc.rs = 1.0f / sqrtf((float)ssq * SSQ_INV_SCALE * ga.inv_dim + ga.eps);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  f32x4 acc[KP];
+#pragma unroll
+  for (int j = 0; j < KP; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int j = 0; j < KP; ++j)
+#pragma unroll
+      for (int h = 0; h < HL; ++h)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, A[u]), __builtin_bit_cast(half8, B[u][j * HL + h]), acc[j], 0, 0, 0);
+  f32x4 s = acc[0];
+  if (HALF) {
+    const bool first = lane < 32;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s[r] = first ? acc[0][r] : acc[KP - 1][r];
+  }
+  if (wave) red[wave - 1][lane] = s;
+  __syncthreads();
+  if (wave) return;
+#pragma unroll
+  for (int w = 0; w < WAVES - 1; ++w) s += red[w][lane];
+  f32x4 s2 = {0.f, 0.f, 0.f, 0.f};
+  if (HALF || EPI == EPI_SWIGLU || EPI == EPI_QKV) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s2[r] = other_half(s[r], lane);
+  }
+  if (HALF) {
+    s += s2;
+    if (lane >= 32) rc.live = false;                   // lane - 32 finishes these outputs
+  }
+  const float sq = gemm_epilogue<EPI, false, true>(ga, rc, ax, nt, m, l, s, s2, xp);
+  if (EPI == EPI_RESID) {
+    const u64 fixed = tile_ssq(sq);
+    if (rc.live && lane < 16) atomicAdd(ssq_to, fixed);
+  }
+}
+
 // ------------------------------------------------------------------ MFMA attention over the f16 KV cache
 // grid (key splits, heads, sequences), NW waves per block.  A block owns `kps` keys of one head; its
 // waves take the 32-key groups of that range round-robin, each running an online softmax in registers:
@@ -947,7 +1063,7 @@ __global__ __launch_bounds__(NW * 64, HD == 128 ? (MT == 2 ? 2 : 3) : (MT == 2 ?
     }
     if (n_split == 1) {
       const float inv = 1.0f / L;
-      store_packed4(xp_out, MT_total_out, r0 + rl, h * HD + d4, a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv);
+      store_packed4(packed_at(xp_out, MT_total_out, r0 + rl, h * HD + d4), a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv);
     } else {
       // several splits: un-normalised partial (values, running max, running sum), written through to memory
       u64* o = reinterpret_cast<u64*>(part + (((size_t)(r0 + rl) * H + h) * S + split) * (HD + 2));
@@ -999,7 +1115,7 @@ __global__ __launch_bounds__(NW * 64, HD == 128 ? (MT == 2 ? 2 : 3) : (MT == 2 ?
       M = Mb;
     }
     const float inv = 1.0f / L;
-    store_packed4(xp_out, MT_total_out, r0 + rl, h * HD + d4, a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv);
+    store_packed4(packed_at(xp_out, MT_total_out, r0 + rl, h * HD + d4), a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv);
   }
 }
 

@@ -381,6 +381,32 @@ bool tiled_gemm(bool two_row_gemm, int n_tiles, int KT, int rows) {
   return KT >= kTileMinSteps && (rows > 32 || (two_row_gemm && n_tiles >= 512 && KT >= 64 && rows > 17));
 }
 
+// A GEMM of up to 16 rows whose K fits the registers of a block's waves (gemm_row_kernel): false if it is not one.
+// Wide matrices with 9 rows and more stay with gemm_w16_kernel, whose waves share an operand fetch among several tiles.
+// Half tiles up to 128 tiles: 256 blocks of half the bytes, one per CU, instead of 128.
+template <int EPI, int TAG, int HL>
+bool launch_row(pacer_ctx* c, const GemmArgs& ga, int n_tiles) {
+  constexpr bool CAN_HALF = EPI == EPI_RESID;
+  const bool half = CAN_HALF && n_tiles <= 128;
+  const int steps = half ? (ga.KT + 1) / 2 : ga.KT;
+  if (ga.R > 16 || steps > (HL == 2 ? (half ? 48 : 64) : (half ? 96 : 64))) return false;
+  if (n_tiles >= 512 && ga.KT > 24 && (HL == 2 || ga.R > 8)) return false;
+#define PACER_ROW(WAVES_, U_, HALF_) PACER_LAUNCH_EXT((gemm_row_kernel<EPI, TAG, HL, WAVES_, U_, HALF_>), dim3(HALF_ ? 2 * n_tiles : n_tiles), dim3(WAVES_ * 64), 0, c->stream, c->pe0, c->pe1, 0, ga.W, ga.X, ga.KT, ga.R, ga.nt_begin, ga)
+  if constexpr (CAN_HALF) {
+    if (half) {
+      if (steps <= 12) PACER_ROW(4, 3, 1);
+      else if (steps <= 32) PACER_ROW(8, 4, 1);
+      else if (steps <= 48) PACER_ROW(8, 6, 1);
+      else if constexpr (HL == 1) PACER_ROW(8, 12, 1);
+      return true;
+    }
+  }
+  if (steps <= 24) PACER_ROW(4, 6, 0);
+  else PACER_ROW(8, 8, 0);
+#undef PACER_ROW
+  return true;
+}
+
 // Launches the GEMM over `n_tiles` output tiles starting at ga.nt_begin; with the weight-streaming kernel or the tiled one
 // (tiled_gemm).
 // HL = 2: multiply the operand's hi and lo tiles (target model, all GEMMs but the O projection and the
@@ -404,6 +430,12 @@ void gemm_w16_tag(pacer_ctx* c, GemmArgs ga, int n_tiles, int K) {
   if (tiled_gemm(TAG == 0 && HL == 2 && (EPI == EPI_QKV || EPI == EPI_SWIGLU), n_tiles, ga.KT, ga.R)) {
     if (TAG == 0) prof_begin(c);
     launch_tile<EPI, HL>(c, ga, n_tiles);
+    if (TAG == 0) prof_end(c, (double)n_tiles * 16.0 * K * 2.0);
+    return;
+  }
+  ga.mt0 = 0;
+  if (TAG == 0) prof_begin(c);
+  if (launch_row<EPI, TAG, HL>(c, ga, n_tiles)) {
     if (TAG == 0) prof_end(c, (double)n_tiles * 16.0 * K * 2.0);
     return;
   }
@@ -432,12 +464,7 @@ void gemm_w16_tag(pacer_ctx* c, GemmArgs ga, int n_tiles, int K) {
     }
     if (HL == 1) {
       if (mt == 1) {
-        // K <= 768 (draft, pre-verification layer): 4 waves with at most 6 K steps each; the LM head and the
-        // gate/up matrix (many tiles) run one step per register set, the small ones three
-        if (ga.KT <= 24) {
-          if (n_tiles >= 256) launch_w16<EPI, TAG, 1, 1, 1, 4, 1>(c, ga, n_tiles);
-          else launch_w16<EPI, TAG, 1, 1, 1, 4, 3>(c, ga, n_tiles);
-        } else if (many && even && rows > 8) launch_w16<EPI, TAG, 1, 1, 2, 4, 2>(c, ga, n_tiles);
+        if (many && even && rows > 8) launch_w16<EPI, TAG, 1, 1, 2, 4, 2>(c, ga, n_tiles);
         else launch_w16<EPI, TAG, 1, 1, 1, 8, 2>(c, ga, n_tiles);
       } else if (rows == 17) {
         if (many && even && n_tiles >= 1024) launch_w16<EPI, TAG, 1, 2, 2, 4, 2, 1>(c, ga, n_tiles);
@@ -507,6 +534,14 @@ void rope_table(pacer_ctx* c, const Model& m, int R, const SeqRows& sr) {
   PACER_LAUNCH(rope_table_kernel, dim3(R), dim3(m.cfg.head_dim / 2), 0, c->stream, sr, m.cfg.head_dim, m.cfg.rope_theta, c->rope);
 }
 
+// the sequence slots of a launch's first 16 rows, 4 bits each
+u64 row_slots(const SeqRows& sr) {
+  u64 v = 0;
+  for (int i = 0; i < sr.n_seqs; ++i)
+    for (int r = sr.row_off[i]; r < std::min(16, sr.row_off[i + 1]); ++r) v |= (u64)i << (4 * r);
+  return v;
+}
+
 // Decoder stack of a bf16 model on R rows.  On entry x holds the rows, xpA their f16 operand x*g of
 // the first norm and slot 0 their sums of squares.  On exit (not kv_only) x holds the final residual
 // rows, xpA = f16(x * g_final) and slot 2L their sums of squares.
@@ -564,6 +599,7 @@ void run_layers_w16(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows&
   base.ssq_stride = c->rcap;
   base.d = d; base.hd = hd; base.n_layers = L; base.max_seq = g.max_seq; base.H = H;
   base.mt_total_out = mt_total;
+  base.row_slot = row_slots(sr);
   for (int l = 0; l < L; ++l) {
     {
       GemmArgs ga = base;
@@ -661,6 +697,7 @@ void lm_head_w16(pacer_ctx* c, const Model& m, int tag, int R, float* out, const
     ga.pick_seed = pick->seed;
     ga.pick_step = pick->step;
   }
+  ga.row_slot = row_slots(sr);
   ga.R = R; ga.sr = sr; ga.G1 = c->G1; ga.rowmap = rowmap; ga.eps = m.cfg.rms_eps;
   ga.W = static_cast<const u32x4*>(m.head);
   ga.X = reinterpret_cast<const u32x4*>(c->xpA);

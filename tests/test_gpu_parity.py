@@ -935,3 +935,45 @@ def test_tiled_gemm_shapes_with_a_ragged_last_column_block_prompt(f, rows, plan)
     err = rel_err(k, oc.K[1][:rows])
     assert err < 2e-2, err
     s.close()
+
+
+@pytest.mark.parametrize("d,f,n_seqs,g1", [
+    (192, 2080, 1, 1),      # half tiles of an odd number of K tiles (6 and 65), one row
+    (192, 2080, 3, 5),      # 15 rows of three sequences
+    (128, 3072, 16, 1),     # one row of each of 16 sequences, the most half-tile steps of hi+lo operands (48)
+    (256, 3104, 2, 8),      # one K tile more: the draft's stays, the target's is streamed
+    (2048, 6144, 2, 3),     # 128 output tiles: the widest in half tiles; the draft's longest K (96 steps)
+    (2112, 224, 1, 16),     # wider than that, K of 66 tiles: streamed beside a short one
+])
+def test_few_rows_over_a_short_k_at_the_edges(d, f, n_seqs, g1):
+    """Up to 16 rows and matrices whose K fits a block's registers take their own GEMM kernel: sizes at its edges, for a
+    target (hi and lo operand parts) and a draft of the same shape (hi only).  Verify rows and first draft rows against the
+    oracle's forwards.  Bound as in the other bf16 tests."""
+    from paper_2602_01274_amd import binding as B
+    v = 528
+    w, _, _, _ = _small_target(d, f, v, 1, gamma_max=max(4, (g1 + 2) // 4 * 4))
+    w["draft"].update(d_model=d, n_heads=d // 64, d_ffn=f)
+    tgt, drf, mb = synth.make_pair(w, seed=0, gain_jitter=0.1)
+    s = _session(w, tgt, drf, mb, 64, max_batch=n_seqs)
+    ids = [synth.make_prompt(v, 3 + i, 40 + i).tolist() for i in range(n_seqs)]
+    drafts = synth.make_prompt(v, max(1, n_seqs * (g1 - 1)), 3)[:n_seqs * (g1 - 1)].view(n_seqs, g1 - 1)
+    every = list(range(n_seqs))
+    for i, p in enumerate(ids):
+        s.prefill(p, seq=i)
+        B.pacer_begin_step(s.ctx, i)
+    for _ in range(max(1, g1 - 1)):
+        B.pacer_draft_step(s.ctx, every, B.GREEDY, 0, 0)
+    q = [s.draft_logits(i)[0].cpu().numpy() for i in every]
+    for i in every:
+        s.draft_tokens(i)[:g1 - 1].copy_(drafts[i].cuda())
+    B.pacer_verify(s.ctx, every, [g1 - 1] * n_seqs, s.logits)
+    ot, od = helpers.to_oracle(tgt, cache=True), helpers.to_oracle(drf, cache=True)
+    ct, cd = helpers.oracle_cfg(w["target"]), helpers.oracle_cfg(w["draft"])
+    for i, p in enumerate(ids):
+        _, ref = po.lm_forward(ot, ct, p + drafts[i].tolist(), po.KVCache(1, d, 64))
+        err = rel_err(s.logits[i, :g1].cpu().numpy(), ref[-g1:])
+        assert err < 2e-2, ("verify", i, err)
+        _, ref = po.lm_forward(od, cd, p, po.KVCache(w["draft"]["n_layers"], d, 64))
+        err = rel_err(q[i][None], ref[-1:])
+        assert err < 2e-2, ("draft", i, err)
+    s.close()
