@@ -577,8 +577,8 @@ void run_layers_w16(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows&
   }
   const int S = (max_keys + kps - 1) / kps;
   // Attention blocks start longest sequence first, so that the short ones fill the launch's tail (16 sequences of 256..2048
-  // keys, 40 heads: 89.5 -> 85.3 us).  order: 4 bits per grid position, ties in list order.
-  uint64_t order = 0;
+  // keys, 40 heads: 89.5 -> 85.3 us), ties in list order.
+  AttnSeqs seqs{};
   {
     int perm[PK_MAXB], keys[PK_MAXB];
     for (int i = 0; i < sr.n_seqs; ++i) {
@@ -588,7 +588,10 @@ void run_layers_w16(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows&
       keys[at] = k;
       perm[at] = i;
     }
-    for (int i = 0; i < sr.n_seqs; ++i) order |= (uint64_t)perm[i] << (4 * i);
+    for (int i = 0; i < sr.n_seqs; ++i) {
+      const int k = perm[i];
+      seqs.s[i] = {sr.seq[k], k, sr.row_off[k], sr.row_off[k + 1] - sr.row_off[k], sr.pos0[k], {0, 0, 0}};
+    }
   }
   GemmArgs base{};
   base.R = R;
@@ -629,7 +632,7 @@ void run_layers_w16(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows&
       // Two row tiles of 128 dims fill the registers at 8 waves per CU: as two blocks of 4 waves when there is a block per
       // CU and more, so that one block's start and merge run beside the other's keys (512 prompt rows, 32 heads, up to
       // 4000 keys: 43.2 -> 40.2 us); one sequence's few pairs keep 8 waves per pair.
-#define PACER_ATTN(HD_, MT_, QL_, NW_) PACER_LAUNCH((attn_mfma_kernel<HD_, MT_, QL_, NW_>), grid, dim3(NW_ * 64), (size_t)NW_ * std::min(mrows, MT_ * 16) * (HD_ + 4) * 4, c->stream, c->qp, kv, l, L, g.max_seq, d, sr, kps, S, H, c->part, c->xpB, mt_total, rt_split ? 1 : 0, order, c->att_cnt)
+#define PACER_ATTN(HD_, MT_, QL_, NW_) PACER_LAUNCH((attn_mfma_kernel<HD_, MT_, QL_, NW_>), grid, dim3(NW_ * 64), (size_t)NW_ * std::min(mrows, MT_ * 16) * (HD_ + 4) * 4, c->stream, c->qp, kv, l, L, g.max_seq, d, kps, H, rt_split ? 1 : 0, S, c->xpB, mt_total, c->part, c->att_cnt, seqs)
 #define PACER_ATT(HD_, MT_, QL_) if constexpr (HD_ == 128 && MT_ == 2) { if (S == 1 && H * sr.n_seqs >= 256) { PACER_ATTN(HD_, MT_, QL_, 4); } else { PACER_ATTN(HD_, MT_, QL_, 8); } } else { PACER_ATTN(HD_, MT_, QL_, 8); }
       if (tag == 0) {
         if (hd == 128) { if (mrows > 16) { PACER_ATT(128, 2, 2); } else { PACER_ATT(128, 1, 2); } }
