@@ -567,9 +567,11 @@ void run_layers_w16(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows&
   int kps = (max_keys + 31) / 32 * 32;
   {
     const int pairs = H * sr.n_seqs;
-    // (the small draft model's keys are re-read every few microseconds and sit in L2: 770 keys, 12 heads take
-    // 6.6 us unsplit and 7.3 us in 4 splits, so its blocks keep at least 1024 keys)
-    const int min_keys = tag == 0 ? (max_keys >= 512 ? 96 : 256) : 1024;
+    // A draft's keys are re-read every few microseconds and sit in L2; what a block of it can pull through its CU decides: 64-dim
+    // heads split from 1024 keys on (drafting round of the 68M draft at 800 / 2000 / 4000 keys, blocks of at least 512 against
+    // 1024 keys: 257 / 274 / 277 against 257 / 282 / 291 us), 128-dim heads, twice the bytes, from 512 keys on (1.35B draft step
+    // at 400 / 640 / 1200 / 2000 keys, split against not: 807 / 802 / 820 / 887 against 801 / 821 / 881 / 1212 us).
+    const int min_keys = tag == 0 ? (max_keys >= 512 ? 96 : 256) : hd == 64 ? 512 : (max_keys >= 512 ? 128 : 1024);
     const int most = std::min({256 / pairs, max_keys / min_keys, kMaxChunks});   // splits that still leave one block per CU
     // 17..32 rows below 1000 keys: two one-tile blocks per pair instead (see the attention launch)
     const bool two_tiles_short = max_rows > 16 && max_keys < 1000;

@@ -977,3 +977,26 @@ def test_few_rows_over_a_short_k_at_the_edges(d, f, n_seqs, g1):
         err = rel_err(q[i][None], ref[-1:])
         assert err < 2e-2, ("draft", i, err)
     s.close()
+
+
+@pytest.mark.parametrize("hd,n_keys", [(128, (512, 300)), (128, (513, 1281)), (128, (511, 40)), (64, (1024, 500)), (64, (1025, 1023))])
+def test_draft_attention_with_split_keys(hd, n_keys):
+    """A draft step whose attention splits its keys over blocks (128-dim heads from 512 keys on, 64-dim heads from 1024), with
+    sequences of other split counts beside it, against the oracle.  Bound as in the other bf16 tests."""
+    from paper_2602_01274_amd import binding as B
+    v, d = 528, 256
+    w, _, _, _ = _small_target(128, 128, v, 1)
+    w["draft"].update(d_model=d, n_heads=d // hd, head_dim=hd, d_ffn=256)
+    tgt, drf, mb = synth.make_pair(w, seed=0, gain_jitter=0.1)
+    s = _session(w, tgt, drf, mb, 1344, max_batch=2)
+    ids = [synth.make_prompt(v, n, 40 + i).tolist() for i, n in enumerate(n_keys)]
+    for i, p in enumerate(ids):
+        s.prefill(p, seq=i)
+        B.pacer_begin_step(s.ctx, i)
+    B.pacer_draft_step(s.ctx, [0, 1], B.GREEDY, 0, 0)
+    od, cd = helpers.to_oracle(drf, cache=True), helpers.oracle_cfg(w["draft"])
+    for i, p in enumerate(ids):
+        _, ref = po.lm_forward(od, cd, p, po.KVCache(w["draft"]["n_layers"], d, 1344))
+        err = rel_err(s.draft_logits(i)[0].cpu().numpy()[None], ref[-1:])
+        assert err < 2e-2, (i, err)
+    s.close()
