@@ -28,8 +28,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 #define PK_MAXB 16
-#define ATT_MAXR 32   // rows of one sequence in one attention launch
-#define ATT_TILE 64   // keys per LDS tile
 
 // Rows of a launch: sequence si (slot in the call's list) owns rows row_off[si]..row_off[si+1]-1
 // at consecutive absolute positions starting at pos0[si]; len[si] = committed tokens.
@@ -68,20 +66,10 @@ __device__ __forceinline__ SeqOf seq_of_row(const SeqRows& sr, int r) {
 }
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);   // round to nearest even
-  return (uint16_t)(u >> 16);
-}
 
 template <typename T> __device__ __forceinline__ float ld_f32(const T* p);
 template <> __device__ __forceinline__ float ld_f32<float>(const float* p) { return *p; }
 template <> __device__ __forceinline__ float ld_f32<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
-template <typename T> __device__ __forceinline__ void st_f32(T* p, float v);
-template <> __device__ __forceinline__ void st_f32<float>(float* p, float v) { *p = v; }
-template <> __device__ __forceinline__ void st_f32<uint16_t>(uint16_t* p, float v) { *p = f32_to_bf16(v); }
-template <> __device__ __forceinline__ void st_f32<_Float16>(_Float16* p, float v) { *p = (_Float16)v; }
-
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -190,62 +178,21 @@ __global__ void mb_input_kernel(const float* __restrict__ src, int lds, const fl
 }
 
 // ------------------------------------------------------------------ f32 path: norm and activation
-// RMSNorm of R rows (one block each); writes the normalised rows as f32 (xn) and optionally scattered
-// copies for the draft's hidden-state ring (hid_out row = seq*G1 + draft index).
-__global__ void rmsnorm_pack_kernel(const float* __restrict__ x, int ldx, const float* __restrict__ g, float eps, int R, int d,
-                                    float* __restrict__ xn, int ldxn, float* __restrict__ hid_out, int G1, SeqRows sr) {
+// RMSNorm of rows (one block each): the draft's hidden states of a prompt, which M_B's prefix rows start from
+__global__ void rmsnorm_rows_kernel(const float* __restrict__ x, int ldx, const float* __restrict__ g, float eps, int d, float* __restrict__ out, int ldo) {
   __shared__ float red[16];
-  const int r = blockIdx.x;
-  const int ng = d >> 3;
-  if (r >= R) return;
-  const float* xr = x + (size_t)r * ldx;
+  const float* xr = x + (size_t)blockIdx.x * ldx;
   float ss = 0.f;
   for (int k = threadIdx.x; k < d; k += blockDim.x) { const float v = xr[k]; ss += v * v; }
   ss = block_sum(ss, red);
   const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-  float* ho = nullptr;
-  if (hid_out) {
-    const int si = find_seq(sr, r);
-    const int j = sr.pos0[si] + (r - sr.row_off[si]) - (sr.len[si] - 1);
-    ho = hid_out + (size_t)(sr.seq[si] * G1 + j) * d;
-  }
-  for (int kg = threadIdx.x; kg < ng; kg += blockDim.x) {
-    float v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = xr[kg * 8 + i] * inv * g[kg * 8 + i];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) xn[(size_t)r * ldxn + kg * 8 + i] = v[i];
-    if (ho) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) ho[kg * 8 + i] = v[i];
-    }
-  }
-}
-
-// SwiGLU: act = silu(gate) * up for gu = [gate | up] rows, f32
-__global__ void swiglu_pack_kernel(const float* __restrict__ gu, int ldg, int R, int F, float* __restrict__ act, int lda) {
-  const int r = blockIdx.y;
-  const int kg = blockIdx.x * blockDim.x + threadIdx.x;
-  if (kg >= (F >> 3) || r >= R) return;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const float gt = gu[(size_t)r * ldg + kg * 8 + i], up = gu[(size_t)r * ldg + F + kg * 8 + i];
-    act[(size_t)r * lda + kg * 8 + i] = gt / (1.0f + expf(-gt)) * up;
-  }
+  for (int k = threadIdx.x; k < d; k += blockDim.x) out[(size_t)blockIdx.x * ldo + k] = xr[k] * inv * g[k];
 }
 
 // ------------------------------------------------------------------ output row mapping of a GEMM
 #define ROWMAP_ID 0      // out row = r
 #define ROWMAP_RING 1    // out row = seq*G1 + draft index      (draft logits ring)
 #define ROWMAP_LIST 2    // out row = slot*G1 + row within seq  (verify logits)
-__device__ __forceinline__ int map_row(const SeqRows& sr, int mode, int G1, int r) {
-  if (mode == ROWMAP_ID) return r;
-  const int si = find_seq(sr, r);
-  const int rr = r - sr.row_off[si];
-  if (mode == ROWMAP_LIST) return si * G1 + rr;
-  return sr.seq[si] * G1 + (sr.pos0[si] + rr - (sr.len[si] - 1));
-}
-
 // bf16 -> f16 of 8 weights (exact for |w| >= 2^-17; smaller ones round to the nearest f16 subnormal,
 // absolute error <= 2^-25).  Done once, when a matrix is packed.
 __device__ __forceinline__ u32x4 bf16x8_to_f16x8(u32x4 w) {
@@ -260,261 +207,243 @@ __device__ __forceinline__ u32x4 bf16x8_to_f16x8(u32x4 w) {
   return __builtin_bit_cast(u32x4, h);
 }
 
-// Plain f32 GEMM for f32 models and tiny heads: one wave per output feature, rows in groups of RG.  Latency bound (a few
-// hundred KiB of weights over 64..1024 waves): four K steps are requested before the first is used (d 256, 3 rows, K 688:
-// 8.4 -> 5.3 us).  The additions keep their order.
-template <int RG>
-__global__ void gemm_f32_kernel(const float* __restrict__ W, const float* __restrict__ X, int ldx, float* __restrict__ out, int ldo,
-                                int R, int N, int K, int accumulate, SeqRows sr, int rowmap, int G1) {
-  const int n = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+// ------------------------------------------------------------------ f32 models: GEMMs with fused norm and epilogue
+// A wave's exchange without a trip to LDS: v of another lane of the same 16 (DPP), and the two swaps between 16-lane groups.
+template <int CTRL> __device__ __forceinline__ float dpp_f32(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+// over the four 16-lane groups of a wave, same lane of each
+__device__ __forceinline__ float group_max(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned w = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float group_sum(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned w = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+// over 16 lanes: quad_perm [1,0,3,2] and [2,3,0,1], row_half_mirror, row_mirror
+__device__ __forceinline__ float row16_sum(float v) {
+  v += dpp_f32<0xB1>(v);
+  v += dpp_f32<0x4E>(v);
+  v += dpp_f32<0x141>(v);
+  v += dpp_f32<0x140>(v);
+  return v;
+}
+__device__ __forceinline__ float wave_total(float v) { return group_sum(row16_sum(v)); }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+
+#define F32_QKV 0      // norm; rotation, q rows out, K and V rows into the cache
+#define F32_RESID 1    // out += the product
+#define F32_SWIGLU 2   // norm; silu(gate) * up
+#define F32_LOGITS 3   // norm; logits, and the normalised rows for the hidden-state ring
+struct F32Args {
+  float eps;
+  int rowmap, G1;
+  const float* rope;                     // [max_seq][32][2] cos, sin by absolute position
+  float* kv;
+  int layer, n_layers, max_seq, d;
+  float* hid_out;                        // LOGITS: may be null; one block per row behind the output's blocks
+  SeqRows sr;
+};
+// One wave per output, or per pair of outputs that the epilogue needs together (a rotation pair, gate and up, two logits), for
+// RG rows at a time; 4 waves per block.  The launch is a chain of latencies over a few hundred KiB, and what counts is what is
+// not in it: the norm costs no launch of its own (a wave that reads a row adds its squares up on the way), nor do rotation,
+// cache append and SwiGLU.  16-byte loads through descriptors that end with the row: a K that is not a multiple of 256 reads
+// zeros.  The arguments that the first loads need come first, in registers; the others are read in one go while those travel.
+// n_waves: waves with work.  extra: 1 = K and V only (QKV); the number of outputs (LOGITS).  Tiny pair (d 256,
+// FFN 688, 4 layers), two draft steps, their pre-verification and verification: 88 launches and 285 us of kernels with norm,
+// rotation and SwiGLU as kernels of their own, now 45 and 141.
+template <int RG, int U, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* W, const float* X, int K, int ldx, int R, int ldo, float* out, const float* gain,
+                                                       int n_waves, int extra, const F32Args a) {
+  constexpr bool NORM = EPI != F32_RESID, PAIR = EPI != F32_RESID;
   const int lane = threadIdx.x & 63;
-  if (n >= N) return;
-  const float* w = W + (size_t)n * K;
-  constexpr int U = 4;
+  const int out_blocks = (n_waves + 3) >> 2;
+  if (EPI == F32_LOGITS && (int)blockIdx.x >= out_blocks) {            // hidden state of one row
+    __shared__ float red[16];
+    const int r = blockIdx.x - out_blocks, si = find_seq(a.sr, r);
+    const float* xr = X + (size_t)r * ldx;
+    float ss = 0.f;
+    for (int k = threadIdx.x; k < K; k += 256) ss += xr[k] * xr[k];
+    const float inv = 1.0f / sqrtf(block_sum(ss, red) / (float)K + a.eps);
+    const int j = a.sr.pos0[si] + (r - a.sr.row_off[si]) - (a.sr.len[si] - 1);
+    float* ho = a.hid_out + (size_t)(a.sr.seq[si] * a.G1 + j) * K;
+    for (int k = threadIdx.x; k < K; k += 256) ho[k] = xr[k] * inv * gain[k];
+    return;
+  }
+  const int n = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const int part = EPI == F32_QKV ? extra + (int)blockIdx.y : 0;       // Q, K, V: K rows of W each (d outputs of d inputs)
+  if (n >= n_waves) return;
+  // the wave's two rows of W: dims j and j + 32 of a head (QKV), gate and up, two neighbours
+  const int ca = EPI == F32_QKV ? (n >> 5) * 64 + (n & 31) : EPI == F32_LOGITS ? 2 * n : n;
+  const int cb = EPI == F32_QKV ? ca + 32 : EPI == F32_LOGITS ? min(ca + 1, extra - 1) : n_waves + n;
+  const auto wa = buffer_of(W + (size_t)(part * K + ca) * K, K * 4), wb = buffer_of(W + (size_t)(part * K + (PAIR ? cb : ca)) * K, K * 4);
+  const auto gr = buffer_of(gain, K * 4);
   for (int r0 = 0; r0 < R; r0 += RG) {
-    float acc[RG];
+    float sa[RG], sb[RG], ss[RG];
 #pragma unroll
-    for (int i = 0; i < RG; ++i) acc[i] = 0.f;
-    for (int k0 = lane; k0 < K; k0 += 64 * U) {
-      float wv[U], xv[U][RG];
+    for (int i = 0; i < RG; ++i) sa[i] = sb[i] = ss[i] = 0.f;
+    // what lane i needs for row r0 + i, requested beside the first products
+    const int r = r0 + lane;
+    const bool mine = lane < RG && r < R;
+    float old = 0.f, cs = 1.f, sn = 0.f;
+    float* dst = nullptr;
+    for (int k0 = 0; k0 < K; k0 += 256 * U) {
+      float4 va[U], vb[U], vg[U], vx[U][RG];
+      auto ld = [](__amdgpu_buffer_rsrc_t b, int off) { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0)); };
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int k = k0 + 64 * u;
-        wv[u] = k < K ? w[k] : 0.f;
+        const int off = (k0 + u * 256) * 4 + lane * 16;
+        va[u] = ld(wa, off);
+        if (PAIR) vb[u] = ld(wb, off);
+        if (NORM) vg[u] = ld(gr, off);
 #pragma unroll
-        for (int i = 0; i < RG; ++i) xv[u][i] = k < K && r0 + i < R ? X[(size_t)(r0 + i) * ldx + k] : 0.f;
+        for (int i = 0; i < RG; ++i) vx[u][i] = ld(buffer_of(X + (size_t)min(r0 + i, R - 1) * ldx, K * 4), off);   // a row past the last repeats it
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int i = 0; i < RG; ++i) acc[i] += wv[u] * xv[u][i];
-    }
-#pragma unroll
-    for (int i = 0; i < RG; ++i) {
-      const float s = wave_sum(acc[i]);
-      if (lane == 0 && r0 + i < R) {
-        float* o = out + (size_t)map_row(sr, rowmap, G1, r0 + i) * ldo + n;
-        *o = accumulate ? *o + s : s;
+      if (k0 == 0) {
+        if (EPI == F32_QKV || EPI == F32_LOGITS) asm volatile("" ::"s"(a.sr.n_seqs), "s"(a.sr.seq[0]), "s"(a.sr.row_off[0]), "s"(a.sr.pos0[0]));
+        if (EPI == F32_QKV) asm volatile("" ::"s"(a.rope), "s"(a.kv), "s"(a.layer), "s"(a.n_layers), "s"(a.max_seq), "s"(a.d), "s"(a.eps));
+        if (EPI == F32_LOGITS) asm volatile("" ::"s"(a.rowmap), "s"(a.G1), "s"(a.sr.len[0]), "s"(a.eps));
       }
-    }
-  }
-}
-
-// ------------------------------------------------------------------ RoPE
-// cos/sin table [R][hd/2][2] for this launch's absolute positions, evaluated in double
-__global__ void rope_table_kernel(SeqRows sr, int hd, float theta, float* __restrict__ tab) {
-  const int r = blockIdx.x, j = threadIdx.x;
-  const int half = hd >> 1;
-  if (j >= half) return;
-  const int si = find_seq(sr, r);
-  const double pos = (double)(sr.pos0[si] + (r - sr.row_off[si]));
-  const double inv = pow((double)theta, -2.0 * (double)j / (double)hd);
-  double sn, cs;
-  sincos(pos * inv, &sn, &cs);
-  tab[((size_t)r * half + j) * 2] = (float)cs;
-  tab[((size_t)r * half + j) * 2 + 1] = (float)sn;
-}
-
-// rotate q in place, rotate k and copy v into the KV cache (rotate-half pairing j, j+hd/2)
-template <typename KVT>
-__global__ void rope_append_kernel(float* __restrict__ qkv, int ld, const float* __restrict__ tab, SeqRows sr, int d, int hd,
-                                   KVT* __restrict__ kv, int layer, int n_layers, int max_seq, int kv_only) {
-  const int r = blockIdx.x, h = blockIdx.y, j = threadIdx.x;
-  const int half = hd >> 1;
-  if (j >= half) return;
-  const int si = find_seq(sr, r);
-  const int pos = sr.pos0[si] + (r - sr.row_off[si]);
-  const float cs = tab[((size_t)r * half + j) * 2], sn = tab[((size_t)r * half + j) * 2 + 1];
-  float* row = qkv + (size_t)r * ld;
-  const int c0 = h * hd + j, c1 = c0 + half;
-  if (!kv_only) {
-    const float a = row[c0], b = row[c1];
-    row[c0] = a * cs - b * sn;
-    row[c1] = b * cs + a * sn;
-  }
-  KVT* K = kv + (((size_t)sr.seq[si] * n_layers + layer) * 2) * (size_t)max_seq * d + (size_t)pos * d;
-  KVT* V = K + (size_t)max_seq * d;
-  const float a = row[d + c0], b = row[d + c1];
-  st_f32<KVT>(K + c0, a * cs - b * sn);
-  st_f32<KVT>(K + c1, b * cs + a * sn);
-  st_f32<KVT>(V + c0, row[2 * d + c0]);
-  st_f32<KVT>(V + c1, row[2 * d + c1]);
-}
-
-// ------------------------------------------------------------------ attention over the KV cache
-// One block = (chunk of key tiles, head, sequence).  All rows of the sequence (<= 32) share every
-// K/V tile, which is staged once in LDS.  Row r attends to keys 0..pos_r.  Online softmax over the
-// tiles of the chunk; the chunk's (max, sum, weighted values) go to `part` for attn_combine.
-template <typename KVT> struct KvWords;
-template <> struct KvWords<float> { static constexpr int per_word = 1; };
-template <> struct KvWords<_Float16> { static constexpr int per_word = 2; };
-__device__ __forceinline__ float f16lo(uint32_t w) { return (float)__builtin_bit_cast(half2v, w)[0]; }
-__device__ __forceinline__ float f16hi(uint32_t w) { return (float)__builtin_bit_cast(half2v, w)[1]; }
-template <typename KVT> __device__ __forceinline__ float kv_dim(const uint32_t* row, int dim);
-template <> __device__ __forceinline__ float kv_dim<float>(const uint32_t* row, int dim) { return __uint_as_float(row[dim]); }
-template <> __device__ __forceinline__ float kv_dim<_Float16>(const uint32_t* row, int dim) {
-  const uint32_t w = row[dim >> 1];
-  return (dim & 1) ? f16hi(w) : f16lo(w);
-}
-
-// RPW: rows per wave, the launch's most rows of a sequence over the block's 4 waves (rows past a sequence's last compute on
-// whatever LDS holds and are not stored).  Latency bound at the sizes it serves: without conditions on the row the loops
-// over features and keys unroll, and their LDS reads overlap (3 rows, 35 keys: 20.2 -> 4.9 us).
-template <typename KVT, int HD, int RPW>
-__global__ __launch_bounds__(256) void attn_partial_kernel(const float* __restrict__ q, int ldq, const KVT* __restrict__ kv, int layer,
-                                                           int n_layers, int max_seq, int d, SeqRows sr, int tiles_per_chunk,
-                                                           int n_chunks, int H, float* __restrict__ part) {
-  constexpr int WORDS = HD / KvWords<KVT>::per_word;   // 32-bit words per key row of one head
-  constexpr int STR = WORDS + 1;                        // odd stride: conflict-free column access
-  constexpr int DPL = HD / 64;                          // output dims per lane
-  __shared__ float Qs[ATT_MAXR][HD];
-  __shared__ uint32_t Kt[ATT_TILE * STR];
-  __shared__ uint32_t Vt[ATT_TILE * STR];
-  __shared__ float S[ATT_MAXR][ATT_TILE];
-  __shared__ float sm[ATT_MAXR], sl[ATT_MAXR], sc[ATT_MAXR];
-
-  const int chunk = blockIdx.x, h = blockIdx.y, si = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int r0 = sr.row_off[si], Rs = sr.row_off[si + 1] - r0;
-  const int pos0 = sr.pos0[si];
-  const int n_keys = pos0 + Rs;                          // keys visible to the last row
-  const int n_tiles = (n_keys + ATT_TILE - 1) / ATT_TILE;
-  const int t_begin = chunk * tiles_per_chunk, t_end = min(n_tiles, t_begin + tiles_per_chunk);
-  const float scale = 1.0f / sqrtf((float)HD);
-  const KVT* Kb = kv + (((size_t)sr.seq[si] * n_layers + layer) * 2) * (size_t)max_seq * d + h * HD;
-  const KVT* Vb = Kb + (size_t)max_seq * d;
-
-  for (int i = tid; i < Rs * HD; i += 256) Qs[i / HD][i % HD] = q[(size_t)(r0 + i / HD) * ldq + h * HD + (i % HD)] * scale;
-  if (tid < ATT_MAXR) { sm[tid] = -INFINITY; sl[tid] = 0.f; sc[tid] = 1.f; }
-  float acc[RPW][DPL];
-#pragma unroll
-  for (int i = 0; i < RPW; ++i)
-#pragma unroll
-    for (int e = 0; e < DPL; ++e) acc[i][e] = 0.f;
-  __syncthreads();
-
-  for (int t = t_begin; t < t_end; ++t) {
-    const int key0 = t * ATT_TILE;
-    // stage K and V tiles: 16-byte global reads, 4-byte LDS writes
-    constexpr int V4 = WORDS / 4, NI = ATT_TILE * V4 / 256;   // uint4 per key, per thread
-    uint4 kq[NI], vq[NI];
-#pragma unroll
-    for (int it = 0; it < NI; ++it) {                    // all requested before the first is used; a key past the end reads the last one
-      const int i = tid + it * 256, key = min(key0 + i / V4, n_keys - 1), c = i % V4;
-      kq[it] = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(Kb + (size_t)key * d) + c * 4);
-      vq[it] = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(Vb + (size_t)key * d) + c * 4);
-    }
-#pragma unroll
-    for (int it = 0; it < NI; ++it) {
-      const int i = tid + it * 256, key = i / V4, c = i % V4;
-      const bool in = key0 + key < n_keys;
-      const uint4 kk = in ? kq[it] : make_uint4(0, 0, 0, 0), vv = in ? vq[it] : make_uint4(0, 0, 0, 0);
-      uint32_t* kd = Kt + key * STR + c * 4;
-      uint32_t* vd = Vt + key * STR + c * 4;
-      kd[0] = kk.x; kd[1] = kk.y; kd[2] = kk.z; kd[3] = kk.w;
-      vd[0] = vv.x; vd[1] = vv.y; vd[2] = vv.z; vd[3] = vv.w;
-    }
-    __syncthreads();
-    // scores: thread = (key, row group)
-    {
-      float s[RPW];
-#pragma unroll
-      for (int i = 0; i < RPW; ++i) s[i] = 0.f;
-      const uint32_t* krow = Kt + lane * STR;
-#pragma unroll 8
-      for (int w = 0; w < WORDS; ++w) {
-        const uint32_t kw = krow[w];
-        if (KvWords<KVT>::per_word == 2) {
-          const float k0 = f16lo(kw), k1 = f16hi(kw);
-#pragma unroll
-          for (int i = 0; i < RPW; ++i) {
-            const int r = wv + 4 * i;
-            s[i] += Qs[r][2 * w] * k0 + Qs[r][2 * w + 1] * k1;
-          }
+      if (k0 == 0 && mine) {
+        if (EPI == F32_RESID) {
+          dst = out + (size_t)r * ldo + ca;
+          old = *dst;
+        } else if (EPI == F32_SWIGLU) {
+          dst = out + (size_t)r * ldo + ca;
         } else {
-          const float k0 = __uint_as_float(kw);
-#pragma unroll
-          for (int i = 0; i < RPW; ++i) {
-            const int r = wv + 4 * i;
-            s[i] += Qs[r][w] * k0;
+          const SeqOf q = seq_of_row(a.sr, r);
+          const int pos = q.pos0 + r - q.row0;
+          if (EPI == F32_QKV) {
+            const int j = n & 31;
+            if (part < 2) {
+              cs = a.rope[((size_t)pos * 32 + j) * 2];
+              sn = a.rope[((size_t)pos * 32 + j) * 2 + 1];
+            }
+            dst = part == 0 ? out + (size_t)r * ldo + ca
+                            : a.kv + ((((size_t)q.seq * a.n_layers + a.layer) * 2 + (part - 1)) * (size_t)a.max_seq + pos) * a.d + ca;
+          } else {
+            const int row = a.rowmap == ROWMAP_LIST ? q.si * a.G1 + (r - q.row0) : q.seq * a.G1 + (pos - (q.len - 1));
+            dst = out + (size_t)row * ldo + ca;
           }
         }
       }
 #pragma unroll
-      for (int i = 0; i < RPW; ++i) {
-        const int r = wv + 4 * i;
-        if (r < Rs) S[r][lane] = (key0 + lane <= pos0 + r) ? s[i] : -INFINITY;
-      }
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < RG; ++i) {
+          const float4 x = vx[u][i];
+          float4 t = x;
+          if (NORM) {
+            t = make_float4(x.x * vg[u].x, x.y * vg[u].y, x.z * vg[u].z, x.w * vg[u].w);
+            ss[i] += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+          }
+          sa[i] += va[u].x * t.x + va[u].y * t.y + va[u].z * t.z + va[u].w * t.w;
+          if (PAIR) sb[i] += vb[u].x * t.x + vb[u].y * t.y + vb[u].z * t.z + vb[u].w * t.w;
+        }
     }
-    __syncthreads();
-    // online softmax: wave wv owns rows wv, wv+4, ...; lane = key
-    for (int r = wv; r < Rs; r += 4) {
-      const float sv = S[r][lane];
-      const float mo = sm[r];
-      const float mn = fmaxf(mo, wave_max(sv));
-      const float p = (mn == -INFINITY) ? 0.f : expf(sv - mn);
-      const float ps = wave_sum(p);
-      S[r][lane] = p;
-      if (lane == 0) {
-        const float corr = (mo == -INFINITY) ? 1.f : expf(mo - mn);
-        sc[r] = corr;
-        sl[r] = sl[r] * corr + ps;
-        sm[r] = mn;
-      }
+    // lane i takes row r0 + i
+    float va = 0.f, vb = 0.f, vs = 0.f;
+#pragma unroll
+    for (int i = 0; i < RG; ++i) {
+      const float ta = wave_total(sa[i]), tb = PAIR ? wave_total(sb[i]) : 0.f, ts = NORM ? wave_total(ss[i]) : 0.f;
+      va = lane == i ? ta : va;
+      vb = lane == i ? tb : vb;
+      vs = lane == i ? ts : vs;
     }
-    __syncthreads();
-    // weighted values: thread = (dims lane*DPL.., row group)
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-      const int r = wv + 4 * i;
-      if (r < Rs) {
-        const float c = sc[r];
-#pragma unroll
-        for (int e = 0; e < DPL; ++e) acc[i][e] *= c;
-      }
-    }
-#pragma unroll 8
-    for (int key = 0; key < ATT_TILE; ++key) {
-      float vv[DPL];
-#pragma unroll
-      for (int e = 0; e < DPL; ++e) vv[e] = kv_dim<KVT>(Vt + key * STR, lane * DPL + e);
-#pragma unroll
-      for (int i = 0; i < RPW; ++i) {
-        const int r = wv + 4 * i;
-        const float p = S[r][key];
-#pragma unroll
-        for (int e = 0; e < DPL; ++e) acc[i][e] += p * vv[e];
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < RPW; ++i) {
-    const int r = wv + 4 * i;
-    if (r < Rs) {
-      float* o = part + (((size_t)(r0 + r) * H + h) * n_chunks + chunk) * (HD + 2);
-#pragma unroll
-      for (int e = 0; e < DPL; ++e) o[lane * DPL + e] = acc[i][e];
-      if (lane == 0) { o[HD] = sm[r]; o[HD + 1] = sl[r]; }
+    if (!mine) continue;
+    const float inv = NORM ? 1.0f / sqrtf(vs / (float)K + a.eps) : 1.f;
+    va *= inv;
+    vb *= inv;
+    if (EPI == F32_RESID) {
+      *dst = old + va;
+    } else if (EPI == F32_SWIGLU) {
+      *dst = va / (1.0f + expf(-va)) * vb;
+    } else if (EPI == F32_QKV) {
+      dst[0] = va * cs - vb * sn;
+      dst[32] = vb * cs + va * sn;
+    } else {
+      dst[0] = va;
+      if (cb != ca) dst[1] = vb;
     }
   }
 }
 
-// merge the chunks' partial softmaxes: grid (rows, heads), block HD threads
-__global__ void attn_combine_kernel(const float* __restrict__ part, int n_chunks, int H, int HD, float* __restrict__ out, int ldo) {
-  const int r = blockIdx.x, h = blockIdx.y, dim = threadIdx.x;
-  const float* p = part + ((size_t)r * H + h) * n_chunks * (HD + 2);
-  float M = -INFINITY;
-  for (int c = 0; c < n_chunks; ++c) M = fmaxf(M, p[(size_t)c * (HD + 2) + HD]);
-  float L = 0.f, a = 0.f;
-  for (int c = 0; c < n_chunks; ++c) {
-    const float m = p[(size_t)c * (HD + 2) + HD];
-    if (m == -INFINITY) continue;
-    const float w = expf(m - M);
-    L += p[(size_t)c * (HD + 2) + HD + 1] * w;
-    a += p[(size_t)c * (HD + 2) + dim] * w;
+// ------------------------------------------------------------------ f32 models: attention over the KV cache
+// grid (rows, heads); a block's NW waves take 32 keys each in turn, and their states meet in LDS (one barrier).  16 lanes hold
+// a key's 64 dims, 4 each, so a load instruction covers 4 whole keys and a score is 4 products and 4 adds across the lanes;
+// scores, probabilities and values stay in registers.  Latency bound: 3 rows and 35 keys took 4.9 us with keys and scores in
+// LDS plus 2.8 us for a launch that combined key ranges, now 3.5.
+struct F32Seqs { int n_seqs; int seq[PK_MAXB], row_off[PK_MAXB + 1], pos0[PK_MAXB]; };
+__global__ __launch_bounds__(1024) void attn_f32_kernel(const float* q, const float* kv, int ldq, int layer, int n_layers, int max_seq, int d, int NW,
+                                                        int ldo, float* out, const F32Seqs sq) {
+  __shared__ float st[16][64 + 2];
+  const int r = blockIdx.x, h = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, c = (lane & 15) * 4;
+  int si = 0;
+  while (si + 1 < sq.n_seqs && sq.row_off[si + 1] <= r) ++si;
+  const int pos = sq.pos0[si] + r - sq.row_off[si];                   // the row sees keys 0..pos
+  const float* K0 = kv + (((size_t)sq.seq[si] * n_layers + layer) * 2) * (size_t)max_seq * d + h * 64;
+  const float4 q4 = *reinterpret_cast<const float4*>(q + (size_t)r * ldq + h * 64 + c);
+  const float scale = 0.125f;                                         // 1 / sqrt(64)
+  const float4 qs = make_float4(q4.x * scale, q4.y * scale, q4.z * scale, q4.w * scale);
+  const int voff = (g * d + c) * 4;
+  float m = -INFINITY, l = 0.f;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int kk = wave * 32; kk <= pos; kk += NW * 32) {
+    // these 32 keys; one past the row's last reads zeros
+    const int bytes = (min(pos - kk, 31) * d + 64) * 4;
+    const auto kb = buffer_of(K0 + (size_t)kk * d, bytes), vb = buffer_of(K0 + ((size_t)max_seq + kk) * d, bytes);
+    float4 k4[8], v4[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) k4[e] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(kb, voff, 4 * e * d * 4, 0));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v4[e] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(vb, voff, 4 * e * d * 4, 0));
+    float s[8], mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float t = row16_sum(qs.x * k4[e].x + qs.y * k4[e].y + qs.z * k4[e].z + qs.w * k4[e].w);
+      s[e] = kk + 4 * e + g <= pos ? t : -INFINITY;
+      mx = fmaxf(mx, s[e]);
+    }
+    const float mn = fmaxf(m, group_max(mx));
+    const float ms = mn == -INFINITY ? 0.f : mn;
+    const float corr = expf(m - ms);
+    float ps = 0.f;
+    acc.x *= corr; acc.y *= corr; acc.z *= corr; acc.w *= corr;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float p = expf(s[e] - ms);
+      ps += p;
+      acc.x += p * v4[e].x; acc.y += p * v4[e].y; acc.z += p * v4[e].z; acc.w += p * v4[e].w;
+    }
+    l = l * corr + ps;
+    m = mn;
   }
-  out[(size_t)r * ldo + h * HD + dim] = a / L;
+  l = group_sum(l);
+  acc.x = group_sum(acc.x); acc.y = group_sum(acc.y); acc.z = group_sum(acc.z); acc.w = group_sum(acc.w);
+  if (lane < 16) {
+    st[wave][c] = acc.x; st[wave][c + 1] = acc.y; st[wave][c + 2] = acc.z; st[wave][c + 3] = acc.w;
+    if (lane == 0) { st[wave][64] = m; st[wave][65] = l; }
+  }
+  __syncthreads();
+  if (wave) return;
+  float M = -INFINITY, L = 0.f, o = 0.f;                              // lane = dim
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, st[w][64]);
+  for (int w = 0; w < NW; ++w) {
+    const float f = st[w][64] == -INFINITY ? 0.f : expf(st[w][64] - M);
+    L += st[w][65] * f;
+    o += st[w][lane] * f;
+  }
+  out[(size_t)r * ldo + h * 64 + lane] = o / L;
 }
 
 // ------------------------------------------------------------------ token choice of the draft model
@@ -548,7 +477,7 @@ __global__ __launch_bounds__(1024) void pick_token_kernel(const float* __restric
 }
 
 // ------------------------------------------------------------------ pre-verification head + halting test
-// xn: final-norm output of M_B, rows grouped per sequence (b rows each).  alpha_j = softmax(z)[1]
+// x: M_B's last residual rows, grouped per sequence (b rows each); their final norm is taken here.  alpha_j = softmax(z)[1]
 // = 1/(1+exp(z0-z1)); stop = (mean alpha <= t) with the mean summed in index order in f32.
 // rule: 0 mean, 1 any, 2 last.  seq/ticket: the stop flag also goes to pinned host memory as
 // host_stop[seq] = ticket*2 + stop, which the host polls instead of synchronising the stream.
@@ -567,15 +496,21 @@ __device__ __forceinline__ int halt_decision(const float* al, int b, float t, in
   for (int j = 0; j < b; ++j) s += al[j];
   return (s / (float)b <= t) ? 1 : 0;
 }
-__global__ void mb_head_kernel(const float* __restrict__ xn, int ldx, const float* __restrict__ cls, int d, int b, HaltArgs ha,
-                               float* __restrict__ alpha, int* __restrict__ stop, int* __restrict__ host_stop) {
+__global__ void mb_head_kernel(const float* __restrict__ x, int ldx, const float* __restrict__ gain, float eps, const float* __restrict__ cls, int d,
+                               int b, HaltArgs ha, float* __restrict__ alpha, int* __restrict__ stop, int* __restrict__ host_stop) {
   __shared__ float al[32];
   const int si = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
   for (int j = wv; j < b; j += nw) {
-    const float* x = xn + (size_t)(si * b + j) * ldx;
-    float z0 = 0.f, z1 = 0.f;
-    for (int k = lane; k < d; k += 64) { z0 += x[k] * cls[k]; z1 += x[k] * cls[d + k]; }
-    z0 = wave_sum(z0); z1 = wave_sum(z1);
+    const float* xr = x + (size_t)(si * b + j) * ldx;
+    float z0 = 0.f, z1 = 0.f, ss = 0.f;
+    for (int k = lane; k < d; k += 64) {
+      const float v = xr[k], t = v * gain[k];
+      ss += v * v;
+      z0 += t * cls[k];
+      z1 += t * cls[d + k];
+    }
+    const float inv = 1.0f / sqrtf(wave_total(ss) / (float)d + eps);
+    z0 = wave_total(z0) * inv; z1 = wave_total(z1) * inv;
     if (lane == 0) al[j] = 1.0f / (1.0f + expf(z0 - z1));
   }
   __syncthreads();
@@ -863,10 +798,6 @@ __global__ __launch_bounds__(64) void accept_finalize_kernel(const float* __rest
       host_tick[s] = ticket;
     }
   }
-}
-
-__global__ void copy_i32_kernel(int* __restrict__ dst, const int* __restrict__ src, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) dst[i] = src[i];
 }
 
 // ------------------------------------------------------------------ streaming-read probe (benchmarks)

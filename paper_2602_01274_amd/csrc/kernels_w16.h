@@ -768,9 +768,6 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 8 ? (NT >= 5 ? 2 : 4) : 1)) v
 // HALF: a matrix of at most 128 tiles leaves CUs idle.  A weight load takes 8 outputs of two K tiles: lanes of tile rows 0..7
 // bring K tile 2s, the others 2s + 1.  Both K tiles' products run with the whole register; of the first the lanes of result
 // rows 0..7 count, of the second the others, and the epilogue adds the two.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
-}
 // v of lane l ^ 32
 __device__ __forceinline__ float other_half(float v, int lane) {
   const unsigned u = __float_as_uint(v);
@@ -892,21 +889,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_row_kernel(const u32x4* W, co
 __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
 struct AttnSeq { int seq, slot, row0, n_rows, pos0, pad[3]; };
 struct AttnSeqs { AttnSeq s[PK_MAXB]; };
-// over the four 16-lane groups of a wave (lanes that hold the same row): vector exchanges, where a shuffle is a trip to LDS
-__device__ __forceinline__ float group_max(float v) {
-  const unsigned u = __float_as_uint(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned w = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float group_sum(float v) {
-  const unsigned u = __float_as_uint(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned w = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
 template <int HD, int MT, int QL, int NW>
 __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : HD == 128 ? (MT == 2 ? 2 : 3) : (MT == 2 ? 3 : 4)) void attn_mfma_kernel(
     const _Float16* __restrict__ qp, const _Float16* __restrict__ kv, int layer, int n_layers, int max_seq, int d, int kps, int H, int rt_split, int S,

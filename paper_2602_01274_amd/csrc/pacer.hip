@@ -71,9 +71,8 @@ struct pacer_ctx {
   int G1 = 0, rcap = 0, prows = 0, dmax = 0, fmax = 0, kmax = 0, hmax = 0, hdmax = 0, max_seq = 0;   // prows: rows the attention partials hold
   int *tokens = nullptr, *draft_tok = nullptr, *rej = nullptr;
   float* acc_part = nullptr;   // acceptance: per (slot, row, vocabulary chunk) statistics and candidates
-  float *ring = nullptr, *hidden = nullptr, *x = nullptr, *xn = nullptr, *qkv = nullptr, *ao = nullptr, *gu = nullptr,
-        *rope = nullptr, *part = nullptr;
-  float* rope_pos[2] = {nullptr, nullptr};   // bf16 path: cos/sin of every position, [0] target, [1] draft and M_B (same head size and theta); filled at bind time
+  float *ring = nullptr, *hidden = nullptr, *x = nullptr, *xn = nullptr, *qkv = nullptr, *ao = nullptr, *part = nullptr;
+  float* rope_pos[2] = {nullptr, nullptr};   // cos/sin of every position, [0] target, [1] draft and M_B (same head size and theta); filled at bind time
   _Float16 *xpA = nullptr, *xpB = nullptr, *qp = nullptr;   // bf16 path: ping-pong f16 operands, attention Q operand
   u64* ssq = nullptr;                                         // bf16 path: row sums of squares, [2*Lmax+1][rcap]
   float* pick_val = nullptr;                                  // bf16 path: per (row, vocab tile) token candidates
@@ -178,8 +177,6 @@ size_t carve(pacer_ctx* c, void* base) {
   c->xn = k.take<float>((size_t)c->rcap * c->kmax);
   c->qkv = k.take<float>((size_t)c->rcap * 3 * c->dmax);
   c->ao = k.take<float>((size_t)c->rcap * c->dmax);
-  c->gu = k.take<float>((size_t)c->rcap * 2 * c->fmax);
-  c->rope = k.take<float>((size_t)c->rcap * c->hdmax);
   for (int w = 0; w < 2; ++w) c->rope_pos[w] = k.take<float>((size_t)c->max_seq * c->m[w].cfg.head_dim);
   c->part = k.take<float>((size_t)c->prows * c->hmax * kMaxChunks * (c->hdmax + 2));
   c->xpA = k.take<_Float16>((size_t)(c->kmax / 8 + 4) * mtcap * 16 * 8 * 2);      // hi and lo tiles
@@ -530,10 +527,6 @@ void gemm_w16(pacer_ctx* c, int tag, bool hilo, const GemmArgs& ga, int n_tiles,
   }
 }
 
-void rope_table(pacer_ctx* c, const Model& m, int R, const SeqRows& sr) {
-  PACER_LAUNCH(rope_table_kernel, dim3(R), dim3(m.cfg.head_dim / 2), 0, c->stream, sr, m.cfg.head_dim, m.cfg.rope_theta, c->rope);
-}
-
 // the sequence slots of a launch's first 16 rows, 4 bits each
 u64 row_slots(const SeqRows& sr) {
   u64 v = 0;
@@ -713,55 +706,55 @@ void lm_head_w16(pacer_ctx* c, const Model& m, int tag, int R, float* out, const
   gemm_w16<EPI_STORE>(c, tag, false, ga, m.cfg.vocab / 16, m.cfg.d_model);
 }
 
-// ===== f32 path (tiny pair): plain kernels, one per operation ================================
+// ===== f32 path (tiny pair): five launches per layer, norms and epilogues inside =============
 
-void gemm_f32(pacer_ctx* c, const void* W, const float* act, int lda, float* out, int ldo, int R, int N, int K, int acc,
-              const SeqRows& sr, int rowmap) {
-#define PACER_GEMM_F32(RG_) PACER_LAUNCH((gemm_f32_kernel<RG_>), dim3((N + 3) / 4), dim3(256), 0, c->stream, static_cast<const float*>(W), act, lda, out, ldo, R, N, K, acc, sr, rowmap, c->G1)
-  if (R == 1) PACER_GEMM_F32(1);
-  else if (R <= 4) PACER_GEMM_F32(4);
-  else PACER_GEMM_F32(8);
+template <int EPI>
+void gemm_f32(pacer_ctx* c, const void* W, const float* X, int K, int ldx, int R, float* out, int ldo, const float* gain, int n_waves, int extra,
+              const F32Args& a) {
+  const dim3 grid((n_waves + 3) / 4 + (EPI == F32_LOGITS && a.hid_out ? R : 0), EPI == F32_QKV ? 3 - extra : 1);
+#define PACER_GEMM_F32(RG_, U_) PACER_LAUNCH((gemm_f32_kernel<RG_, U_, EPI>), grid, dim3(256), 0, c->stream, static_cast<const float*>(W), X, K, ldx, R, ldo, out, gain, n_waves, extra, a)
+  // rows at a time, and K steps of 256 requested together
+  if (R == 1) { if (K <= 256) PACER_GEMM_F32(1, 1); else PACER_GEMM_F32(1, 4); }
+  else if (R <= 4) { if (K <= 256) PACER_GEMM_F32(4, 1); else PACER_GEMM_F32(4, 3); }
+  else if (K <= 256) PACER_GEMM_F32(8, 1);
+  else PACER_GEMM_F32(8, 2);
 #undef PACER_GEMM_F32
 }
 
-void rmsnorm_f32(pacer_ctx* c, const Model& m, const float* g, int R, float* hid_out, const SeqRows& sr) {
-  PACER_LAUNCH(rmsnorm_pack_kernel, dim3(R), dim3(256), 0, c->stream, c->x, c->dmax, g, m.cfg.rms_eps, R, m.cfg.d_model, c->xn,
-                     c->kmax, hid_out, c->G1, sr);
-}
-
-void run_layers_f32(pacer_ctx* c, const Model& m, int R, const SeqRows& sr, bool kv_only, float* hid_out, bool cache_only = false) {
+// Decoder stack of an f32 model on R rows in x; on exit (not kv_only) x holds the final residual rows, not normalised.
+void run_layers_f32(pacer_ctx* c, const Model& m, int R, const SeqRows& sr, bool kv_only, bool cache_only = false) {
   const pacer_model_cfg& g = m.cfg;
-  const int d = g.d_model, F = g.d_ffn, H = g.n_heads, hd = g.head_dim;
-  const SeqRows none{};
-  rope_table(c, m, R, sr);
-  for (int l = 0; l < g.n_layers; ++l) {
-    rmsnorm_f32(c, m, m.attn_norm[l], R, nullptr, sr);
-    gemm_f32(c, m.wqkv[l], c->xn, c->kmax, c->qkv, 3 * c->dmax, R, 3 * d, d, 0, none, ROWMAP_ID);
-    PACER_LAUNCH((rope_append_kernel<float>), dim3(R, H), dim3(hd / 2), 0, c->stream, c->qkv, 3 * c->dmax, c->rope, sr, d, hd,
-                       static_cast<float*>(m.kv), l, g.n_layers, g.max_seq, kv_only ? 1 : 0);
-    if (kv_only || (cache_only && l + 1 == g.n_layers)) continue;
-    int max_keys = 0, max_rows = 0;
-    for (int i = 0; i < sr.n_seqs; ++i) {
-      max_keys = std::max(max_keys, sr.pos0[i] + sr.row_off[i + 1] - sr.row_off[i]);
-      max_rows = std::max(max_rows, sr.row_off[i + 1] - sr.row_off[i]);
-    }
-    const int n_tiles = (max_keys + ATT_TILE - 1) / ATT_TILE;
-    int chunks = std::min(std::min(n_tiles, kMaxChunks), std::max(1, 1024 / (H * sr.n_seqs)));
-    const int tpc = (n_tiles + chunks - 1) / chunks;
-    chunks = (n_tiles + tpc - 1) / tpc;
-#define PACER_ATT_F32(RPW_) PACER_LAUNCH((attn_partial_kernel<float, 64, RPW_>), dim3(chunks, H, sr.n_seqs), dim3(256), 0, c->stream, c->qkv, 3 * c->dmax, static_cast<const float*>(m.kv), l, g.n_layers, g.max_seq, d, sr, tpc, chunks, H, c->part)
-    if (max_rows <= 4) PACER_ATT_F32(1);
-    else if (max_rows <= 12) PACER_ATT_F32(3);
-    else PACER_ATT_F32(8);
-#undef PACER_ATT_F32
-    PACER_LAUNCH(attn_combine_kernel, dim3(R, H), dim3(hd), 0, c->stream, c->part, chunks, H, hd, c->ao, c->dmax);
-    gemm_f32(c, m.wo[l], c->ao, c->dmax, c->x, c->dmax, R, d, d, 1, none, ROWMAP_ID);
-    rmsnorm_f32(c, m, m.ffn_norm[l], R, nullptr, sr);
-    gemm_f32(c, m.wgu[l], c->xn, c->kmax, c->gu, 2 * c->fmax, R, 2 * F, d, 0, none, ROWMAP_ID);
-    PACER_LAUNCH(swiglu_pack_kernel, dim3((F / 8 + 255) / 256, R), dim3(256), 0, c->stream, c->gu, 2 * c->fmax, R, F, c->xn, c->kmax);
-    gemm_f32(c, m.wd[l], c->xn, c->kmax, c->x, c->dmax, R, d, F, 1, none, ROWMAP_ID);
+  const int d = g.d_model, F = g.d_ffn, H = g.n_heads;
+  F32Seqs sq{};
+  sq.n_seqs = sr.n_seqs;
+  int max_keys = 0;
+  for (int i = 0; i < sr.n_seqs; ++i) {
+    sq.seq[i] = sr.seq[i];
+    sq.row_off[i] = sr.row_off[i];
+    sq.pos0[i] = sr.pos0[i];
+    max_keys = std::max(max_keys, sr.pos0[i] + sr.row_off[i + 1] - sr.row_off[i]);
   }
-  if (!kv_only && !cache_only) rmsnorm_f32(c, m, m.final_norm, R, hid_out, sr);
+  sq.row_off[sr.n_seqs] = R;
+  const int nw = std::min(16, (max_keys + 31) / 32);                  // waves of an attention block, 32 keys each at a time
+  F32Args base{};
+  base.sr = sr;
+  base.eps = g.rms_eps;
+  base.G1 = c->G1;
+  base.rope = c->rope_pos[&m == &c->m[PACER_TARGET] ? PACER_TARGET : PACER_DRAFT];
+  base.kv = static_cast<float*>(m.kv);
+  base.n_layers = g.n_layers; base.max_seq = g.max_seq; base.d = d;
+  for (int l = 0; l < g.n_layers; ++l) {
+    const bool last_kv = kv_only || (cache_only && l + 1 == g.n_layers);
+    F32Args a = base;
+    a.layer = l;
+    gemm_f32<F32_QKV>(c, m.wqkv[l], c->x, d, c->dmax, R, c->qkv, 3 * c->dmax, m.attn_norm[l], d / 2, last_kv ? 1 : 0, a);
+    if (last_kv) continue;
+    PACER_LAUNCH(attn_f32_kernel, dim3(R, H), dim3(64 * nw), 0, c->stream, c->qkv, static_cast<const float*>(m.kv), 3 * c->dmax, l, g.n_layers,
+                 g.max_seq, d, nw, c->dmax, c->ao, sq);
+    gemm_f32<F32_RESID>(c, m.wo[l], c->ao, d, c->dmax, R, c->x, c->dmax, nullptr, d, 0, a);
+    gemm_f32<F32_SWIGLU>(c, m.wgu[l], c->x, d, c->dmax, R, c->xn, c->kmax, m.ffn_norm[l], F, 0, a);
+    gemm_f32<F32_RESID>(c, m.wd[l], c->xn, F, c->kmax, R, c->x, c->dmax, nullptr, d, 0, a);
+  }
 }
 
 // ===== model-level steps, both paths ==========================================================
@@ -775,13 +768,20 @@ void forward_lm(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows& sr,
   } else {
     PACER_LAUNCH((embed_rows_kernel<float>), dim3(R), dim3(256), 0, c->stream, static_cast<const float*>(m.embed), c->tokens,
                        c->draft_tok, sr, c->max_seq, c->G1, m.cfg.d_model, c->x, c->dmax);
-    run_layers_f32(c, m, R, sr, false, nullptr, cache_only);
+    run_layers_f32(c, m, R, sr, false, cache_only);
   }
 }
 
-void lm_head(pacer_ctx* c, const Model& m, int tag, int R, float* out, const SeqRows& sr, int rowmap) {
-  if (is_w16(m)) lm_head_w16(c, m, tag, R, out, sr, rowmap);
-  else gemm_f32(c, m.head, c->xn, c->kmax, out, m.cfg.vocab, R, m.cfg.vocab, m.cfg.d_model, 0, sr, rowmap);
+// hid_out (f32 models, may be null): the ring that the rows' final-norm output goes to
+void lm_head(pacer_ctx* c, const Model& m, int tag, int R, float* out, const SeqRows& sr, int rowmap, float* hid_out = nullptr) {
+  if (is_w16(m)) return lm_head_w16(c, m, tag, R, out, sr, rowmap);
+  F32Args a{};
+  a.sr = sr;
+  a.G1 = c->G1;
+  a.rowmap = rowmap;
+  a.hid_out = hid_out;
+  a.eps = m.cfg.rms_eps;
+  gemm_f32<F32_LOGITS>(c, m.head, c->x, m.cfg.d_model, c->dmax, R, out, m.cfg.vocab, m.final_norm, (m.cfg.vocab + 1) / 2, m.cfg.vocab, a);
 }
 
 // M_B over rows whose inputs are src rows + PosEmb; kv_only for prefix rows.
@@ -794,7 +794,7 @@ void run_preverify_rows(pacer_ctx* c, int R, const SeqRows& sr, const MbRows& mr
     run_layers_w16(c, mb, 1, R, sr, kv_only);
   } else {
     PACER_LAUNCH(mb_input_kernel, dim3(R), dim3(256), 0, c->stream, src, lds, mb.posemb, sr, mr, mb.cfg.d_model, c->x, c->dmax);
-    run_layers_f32(c, mb, R, sr, kv_only, nullptr);
+    run_layers_f32(c, mb, R, sr, kv_only);
   }
 }
 
@@ -809,7 +809,7 @@ void preverify_head(pacer_ctx* c, int n, int b, const HaltArgs& ha, float* dev_a
                  mb.cfg.rms_eps, mb.cls, mb.cfg.d_model, b, ha, dev_alpha, dev_stop, c->host_res_dev + 3 * PACER_MAX_BATCH,
                  next_tok ? static_cast<const uint16_t*>(md.embed) : nullptr, next_tok, embed_out(c, md, 1));
   else
-    PACER_LAUNCH(mb_head_kernel, dim3(n), dim3(256), 0, c->stream, c->xn, c->kmax, mb.cls, mb.cfg.d_model, b, ha, dev_alpha, dev_stop,
+    PACER_LAUNCH(mb_head_kernel, dim3(n), dim3(256), 0, c->stream, c->x, c->dmax, mb.final_norm, mb.cfg.rms_eps, mb.cls, mb.cfg.d_model, b, ha, dev_alpha, dev_stop,
                        c->host_res_dev + 3 * PACER_MAX_BATCH);
 }
 
@@ -847,8 +847,8 @@ void draft_forward(pacer_ctx* c, const int32_t* seqs, int n, const int* j, int m
   } else {
     PACER_LAUNCH((embed_rows_kernel<float>), dim3(n), dim3(256), 0, c->stream, static_cast<const float*>(md.embed), c->tokens,
                        c->draft_tok, sr, c->max_seq, c->G1, md.cfg.d_model, c->x, c->dmax);
-    run_layers_f32(c, md, n, sr, false, c->hidden);
-    lm_head(c, md, 1, n, c->ring, sr, ROWMAP_RING);
+    run_layers_f32(c, md, n, sr, false);
+    lm_head(c, md, 1, n, c->ring, sr, ROWMAP_RING, c->hidden);
     PACER_LAUNCH(pick_token_kernel, dim3(n), dim3(1024), 0, c->stream, c->ring, c->draft_tok, pa, c->G1, md.cfg.vocab, mode, seed,
                        (uint32_t)ctr, host_bad_dev(c));
   }
@@ -1058,9 +1058,8 @@ int32_t pacer_create(pacer_ctx** out, const pacer_model_cfg* target, const pacer
   c->stream = static_cast<hipStream_t>(hip_stream);
   c->G1 = pv->gamma_max + 1;
   c->rcap = std::max(kPrefillRows, max_batch * c->G1);
-  // attention partials: f32 models always go through them (all rows); bf16 models only when a decode
-  // launch splits its keys, never in the wide prefill chunks
-  c->prows = (target->dtype == PACER_F32 || draft->dtype == PACER_F32) ? c->rcap : std::max(kChunkRows, max_batch * c->G1);
+  // attention partials: only a decode launch of a bf16 model splits its keys, never the wide prefill chunks
+  c->prows = std::max(kChunkRows, max_batch * c->G1);
   c->dmax = std::max(target->d_model, draft->d_model);
   c->fmax = std::max(target->d_ffn, draft->d_ffn);
   c->kmax = std::max(c->dmax, c->fmax);
@@ -1183,8 +1182,7 @@ int32_t pacer_bind_workspace(pacer_ctx* c, void* p, uint64_t nbytes) {
   HIPCHK(c, hipMemsetAsync(c->sk_cnt, 0, sizeof(unsigned) * kSplitGroups, c->stream));
   HIPCHK(c, hipMemsetAsync(c->att_cnt, 0, sizeof(unsigned) * PK_MAXB * c->hmax * 2, c->stream));
   for (int w = 0; w < 2; ++w)
-    if (is_w16(c->m[w]))
-      PACER_LAUNCH(rope_positions_kernel, dim3(c->max_seq), dim3(c->m[w].cfg.head_dim / 2), 0, c->stream, c->rope_pos[w], c->m[w].cfg.head_dim,
+    PACER_LAUNCH(rope_positions_kernel, dim3(c->max_seq), dim3(c->m[w].cfg.head_dim / 2), 0, c->stream, c->rope_pos[w], c->m[w].cfg.head_dim,
                    c->m[w].cfg.rope_theta);
   void* hp = nullptr;
   HIPCHK(c, hipHostMalloc(&hp, sizeof(int) * 5 * PACER_MAX_BATCH, hipHostMallocMapped));
@@ -1249,8 +1247,7 @@ int32_t pacer_prefill(pacer_ctx* c, int32_t s, const int32_t* dev_tokens, int32_
       PACER_LAUNCH(hidden_rows_kernel, dim3(R), dim3(256), 0, c->stream, c->x, c->dmax, md.final_norm, slot(c, 2 * md.cfg.n_layers),
                          c->rcap, 1.0f / md.cfg.d_model, md.cfg.rms_eps, md.cfg.d_model, c->ao, c->dmax);
     else
-      (void)hipMemcpy2DAsync(c->ao, (size_t)c->dmax * 4, c->xn, (size_t)c->kmax * 4, (size_t)md.cfg.d_model * 4, R, hipMemcpyDeviceToDevice,
-                             c->stream);
+      PACER_LAUNCH(rmsnorm_rows_kernel, dim3(R), dim3(256), 0, c->stream, c->x, c->dmax, md.final_norm, md.cfg.rms_eps, md.cfg.d_model, c->ao, c->dmax);
     run_preverify_rows(c, R, sr, mr, c->ao, c->dmax, true);
   }
   HIPCHK(c, hipGetLastError());

@@ -1000,3 +1000,41 @@ def test_draft_attention_with_split_keys(hd, n_keys):
         err = rel_err(s.draft_logits(i)[0].cpu().numpy()[None], ref[-1:])
         assert err < 2e-2, (i, err)
     s.close()
+
+
+@pytest.mark.parametrize("d,f,v,lens,g1", [
+    (64, 8, 33, (3,), 1),                    # one head, K below a load's width, odd vocabulary
+    (256, 264, 129, (40, 7), 2),             # K on the edge of one step, four rows at a time
+    (320, 1000, 997, (33, 64, 2), 3),        # K that ends inside a step, nine rows
+    (64, 1032, 64, (545, 31), 8),            # more keys than sixteen waves take in one turn, beside a sequence of one wave
+])
+def test_f32_kernels_at_the_edges(d, f, v, lens, g1):
+    """The f32 path's fused kernels at sizes around their steps: verify rows and first draft rows of every sequence against the
+    oracle.  Bound as in the other f32 tests."""
+    from paper_2602_01274_amd import binding as B
+    w = synth.workload("tiny")
+    w["target"].update(n_layers=2, d_model=d, n_heads=d // 64, d_ffn=f, vocab=v)
+    w["draft"].update(n_layers=1, d_model=d, n_heads=d // 64, d_ffn=f, vocab=v)
+    w["gamma_max"] = w["block"] * 4
+    tgt, drf, mb = synth.make_pair(w, seed=0, gain_jitter=0.1)
+    n = len(lens)
+    s = _session(w, tgt, drf, mb, 608, max_batch=n)
+    ids = [synth.make_prompt(v, k, 40 + i).tolist() for i, k in enumerate(lens)]
+    every = list(range(n))
+    for i, p in enumerate(ids):
+        s.prefill(p, seq=i)
+        B.pacer_begin_step(s.ctx, i)
+    for _ in range(max(1, g1 - 1)):
+        B.pacer_draft_step(s.ctx, every, B.GREEDY, 0, 0)
+    B.pacer_verify(s.ctx, every, [g1 - 1] * n, s.logits)
+    ot, od = helpers.to_oracle(tgt, cache=True), helpers.to_oracle(drf, cache=True)
+    ct, cd = helpers.oracle_cfg(w["target"]), helpers.oracle_cfg(w["draft"])
+    for i, p in enumerate(ids):
+        y = s.draft_tokens(i)[:g1 - 1].tolist()
+        _, ref = po.lm_forward(ot, ct, p + y, po.KVCache(2, d, 608))
+        err = rel_err(s.logits[i, :g1].cpu().numpy(), ref[-g1:])
+        assert err < 1e-4, ("verify", i, err)
+        hid, ref = po.lm_forward(od, cd, p, po.KVCache(1, d, 608))
+        assert rel_err(s.draft_logits(i)[0].cpu().numpy()[None], ref[-1:]) < 1e-4, ("draft", i)
+        assert rel_err(s.draft_hidden(i)[0].cpu().numpy()[None], hid[-1:]) < 1e-4, ("hidden", i)
+    s.close()
