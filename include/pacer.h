@@ -254,7 +254,7 @@ int32_t pacer_accept_rollback(pacer_ctx* ctx, const int32_t* seqs, int32_t n_seq
 /* For callers that cannot allocate device memory and hold no context: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  The acceptance rule of pacer_accept_rollback for ONE sequence on
  * logits the caller holds, through the same kernels, with their scratch (per-row, per-vocabulary-chunk statistics,
- * token candidates and reject flags; 17 KiB) in a fixed array inside the library's device image instead of a
+ * token candidates and an arrival counter; 18 KiB) in a fixed array inside the library's device image instead of a
  * workspace.  Calls no hipMalloc / hipFree and no allocating routine; enqueues on hip_stream and returns.
  *   dev_target_logits [gamma+1][vocab] f32  row i = target logits after y_1..y_i (row gamma: the bonus row)
  *   dev_draft_logits  [gamma+1][vocab] f32  row i = draft logits q_{i+1}; row gamma is read only if bonus_row != 0

@@ -81,6 +81,57 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// A wave's exchange without a trip to LDS: v of another lane of the same 16 (DPP), and the two swaps between 16-lane groups.
+template <int CTRL> __device__ __forceinline__ float dpp_f32(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+// over the four 16-lane groups of a wave, same lane of each
+__device__ __forceinline__ float group_max(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned w = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float group_sum(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned w = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+// over 16 lanes: quad_perm [1,0,3,2] and [2,3,0,1], row_half_mirror, row_mirror
+__device__ __forceinline__ float row16_sum(float v) {
+  v += dpp_f32<0xB1>(v);
+  v += dpp_f32<0x4E>(v);
+  v += dpp_f32<0x141>(v);
+  v += dpp_f32<0x140>(v);
+  return v;
+}
+__device__ __forceinline__ float wave_total(float v) { return group_sum(row16_sum(v)); }
+__device__ __forceinline__ float wave_largest(float v) {
+  v = fmaxf(v, dpp_f32<0xB1>(v));
+  v = fmaxf(v, dpp_f32<0x4E>(v));
+  v = fmaxf(v, dpp_f32<0x141>(v));
+  v = fmaxf(v, dpp_f32<0x140>(v));
+  return group_max(v);
+}
+template <int CTRL> __device__ __forceinline__ unsigned min_dpp(unsigned v) {
+  return min(v, (unsigned)__builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ unsigned wave_least(unsigned v) {
+  v = min_dpp<0x140>(min_dpp<0x141>(min_dpp<0x4E>(min_dpp<0xB1>(v))));
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = min(a[0], a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return min(b[0], b[1]);
+}
+// best candidate of a wave: the largest value, the lowest id (not negative) among equal ones
+__device__ __forceinline__ void wave_best(float& v, int& id) {
+  const float m = wave_largest(v);
+  id = (int)wave_least(v == m ? (unsigned)id : 0x7fffffffu);
+  v = m;
+}
 // Block-wide sum in a fixed order (deterministic).  red: LDS scratch of >= 16 floats.
 __device__ __forceinline__ float block_sum(float v, float* red) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
@@ -208,34 +259,6 @@ __device__ __forceinline__ u32x4 bf16x8_to_f16x8(u32x4 w) {
 }
 
 // ------------------------------------------------------------------ f32 models: GEMMs with fused norm and epilogue
-// A wave's exchange without a trip to LDS: v of another lane of the same 16 (DPP), and the two swaps between 16-lane groups.
-template <int CTRL> __device__ __forceinline__ float dpp_f32(float v) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, true));
-}
-// over the four 16-lane groups of a wave, same lane of each
-__device__ __forceinline__ float group_max(float v) {
-  const unsigned u = __float_as_uint(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned w = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float group_sum(float v) {
-  const unsigned u = __float_as_uint(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned w = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-// over 16 lanes: quad_perm [1,0,3,2] and [2,3,0,1], row_half_mirror, row_mirror
-__device__ __forceinline__ float row16_sum(float v) {
-  v += dpp_f32<0xB1>(v);
-  v += dpp_f32<0x4E>(v);
-  v += dpp_f32<0x141>(v);
-  v += dpp_f32<0x140>(v);
-  return v;
-}
-__device__ __forceinline__ float wave_total(float v) { return group_sum(row16_sum(v)); }
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
@@ -532,17 +555,20 @@ __global__ void mb_head_kernel(const float* __restrict__ x, int ldx, const float
 struct AccArgs { int n_seqs; int seq[PK_MAXB]; int slot[PK_MAXB]; int qslot[PK_MAXB]; int gamma[PK_MAXB]; int len[PK_MAXB]; float beta[PK_MAXB]; };
 
 // One row of logits is split into ACC_CHUNKS vocabulary ranges, one block each (a single block per row
-// spent 53 us walking 32000 entries three times).  Three launches:
-//   accept_stats_kernel   per (row, chunk): running max and sum of exp of the effective target logits and
-//                         of the draft logits over the chunk                                  (sampling only)
-//   accept_rows_kernel    per (row, chunk): log-sum-exp of the row from the chunk statistics (fixed chunk
-//                         order, so every chunk of a row derives the same value), then the chunk's best
-//                         candidates; chunk 0 also takes the row's accept test
-//   accept_finalize_kernel per sequence: best candidate over the chunks of each row, first rejection, tokens
+// spent 53 us walking 32000 entries three times).  Two launches:
+//   sampling  accept_stats_kernel   per (row, chunk): running max and sum of exp of the effective target logits and
+//                                   of the draft logits over the chunk
+//             accept_pick_kernel    ACC_PICKERS blocks per sequence: every block takes the log-sum-exps and accept tests of all rows
+//                                   from the statistics (a few KB), so that it knows the row where drafting is cut, and looks
+//                                   for the best candidates of that row only, in its part of the vocabulary; whoever comes last finishes the sequence
+//   greedy    accept_rows_kernel    per (row, chunk): best effective logit
+//             accept_finalize_kernel per sequence: best over the chunks of each row, first rejection, tokens
 // In a context rows i < gamma come first; the bonus row i = gamma (whose draft logits cost one more draft forward) only for
 // the sequences that turn out to have accepted every draft.  pacer_accept_noalloc, whose caller holds them, evaluates it beside.
 #define ACC_CHUNKS 16
 #define ACC_PART 8      // floats per (row, chunk): [0..3] = mp, sp, mq, sq ; [4..7] = best, bi, bestp, bip
+#define ACC_PICKERS 64  // blocks of a sequence that look for its candidates
+#define ACC_MAXROWS 32  // rows of a sequence: the pick kernel takes them four per wave in one go
 
 __device__ __forceinline__ void acc_chunk_range(int V, int chunk, int& v0, int& v1) {
   const int per = ((V + ACC_CHUNKS - 1) / ACC_CHUNKS + 3) & ~3;   // multiple of 4: a Philox block never straddles chunks
@@ -565,12 +591,15 @@ __device__ __forceinline__ bool acc_row(int phase, int gamma, int bx, int& i) {
   return i < gamma || (i == gamma && phase != ACC_PHASE_DRAFTS);
 }
 
-// grid (rows, n_seqs, ACC_CHUNKS).  One pass: a thread keeps the running maximum of what it has seen and the sum of exp
-// relative to it, eight entries requested at a time (two passes of dependent loads took 8.3 us for 17 rows of 32000).
-__global__ __launch_bounds__(256) void accept_stats_kernel(const float* __restrict__ tl, const float* __restrict__ ring, AccArgs aa, int G1,
-                                                           int V, int phase, float* __restrict__ part) {
-  __shared__ float red[4][4];
+// grid (rows, n_seqs, ACC_CHUNKS), 512 threads.  One pass: a thread keeps the running maximum of what it has seen and the sum
+// of exp relative to it, four entries requested at a time (17 rows of 32000: two passes of dependent loads 8.3 us; 256 threads
+// of eight entries and reductions through LDS 5.4; now 4.9).
+__global__ __launch_bounds__(512) void accept_stats_kernel(const float* tl, const float* ring, float* part, int* arrivals, int G1, int V, int phase,
+                                                           AccArgs aa) {
+  constexpr int NWV = 8, U = 4;
+  __shared__ float red[NWV][4];
   const int si = blockIdx.y, ch = blockIdx.z, sl = aa.slot[si];
+  if (blockIdx.x == 0 && ch == 0 && threadIdx.x == 0) arrivals[sl * G1] = 0;   // of the pick kernel's blocks, the next launch
   int i;
   if (!acc_row(phase, aa.gamma[si], blockIdx.x, i)) return;
   const float beta = aa.beta[si];
@@ -581,17 +610,16 @@ __global__ __launch_bounds__(256) void accept_stats_kernel(const float* __restri
   float m[2] = {-INFINITY, -INFINITY}, s[2] = {0.f, 0.f};              // [0] effective target, [1] draft
   // an entry of -inf adds nothing; a NaN makes the sum NaN (fmaxf ignores it)
   auto rel = [](float e, float mx) { return e == -INFINITY ? 0.f : expf(e - mx); };
-  constexpr int U = 8;
-  for (int base = v0 + threadIdx.x; base < v1; base += U * 256) {
+  for (int base = v0 + threadIdx.x; base < v1; base += U * 512) {
     float e[2][U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int v = base + u * 256;
+      const int v = base + u * 512;
       e[0][u] = v < v1 ? t[v] : -INFINITY;
       e[1][u] = v < v1 ? q[v] : -INFINITY;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) e[0][u] = base + u * 256 < v1 ? e[0][u] + beta * e[1][u] : -INFINITY;
+    for (int u = 0; u < U; ++u) e[0][u] = base + u * 512 < v1 ? e[0][u] + beta * e[1][u] : -INFINITY;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       float mn = m[k];
@@ -603,11 +631,11 @@ __global__ __launch_bounds__(256) void accept_stats_kernel(const float* __restri
       m[k] = mn;
     }
   }
-  // wave, then block (4 waves, in wave order)
+  // wave, then block (in wave order)
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    const float mw = wave_max(m[k]);
-    s[k] = wave_sum(s[k] * (m[k] == -INFINITY ? 1.f : expf(m[k] - mw)));   // nothing seen: s is 0, or NaN
+    const float mw = wave_largest(m[k]);
+    s[k] = wave_total(s[k] * (m[k] == -INFINITY ? 1.f : expf(m[k] - mw)));   // nothing seen: s is 0, or NaN
     m[k] = mw;
   }
   if ((threadIdx.x & 63) == 0) {
@@ -615,134 +643,217 @@ __global__ __launch_bounds__(256) void accept_stats_kernel(const float* __restri
     r[0] = m[0]; r[1] = s[0]; r[2] = m[1]; r[3] = s[1];
   }
   __syncthreads();
-  if (threadIdx.x < 2) {
-    const int k = threadIdx.x * 2;
-    float mb = -INFINITY, sb = 0.f;
-    for (int w = 0; w < 4; ++w) mb = fmaxf(mb, red[w][k]);
-    for (int w = 0; w < 4; ++w) sb += red[w][k + 1] * (red[w][k] == -INFINITY ? 1.f : expf(red[w][k] - mb));
-    float* o = part + ((size_t)(sl * G1 + i) * ACC_CHUNKS + ch) * ACC_PART;
-    o[k] = mb; o[k + 1] = sb;
+  if (threadIdx.x < 16) {                                // 8 lanes per statistic, one wave's each
+    static_assert(NWV == 8, "");
+    const int k = (threadIdx.x >> 3) * 2;
+    const float mw = red[threadIdx.x & 7][k], sw = red[threadIdx.x & 7][k + 1];
+    float mb = mw;
+    mb = fmaxf(mb, dpp_f32<0xB1>(mb));
+    mb = fmaxf(mb, dpp_f32<0x4E>(mb));
+    mb = fmaxf(mb, dpp_f32<0x141>(mb));
+    float sb = sw * (mw == -INFINITY ? 1.f : expf(mw - mb));
+    sb += dpp_f32<0xB1>(sb);
+    sb += dpp_f32<0x4E>(sb);
+    sb += dpp_f32<0x141>(sb);
+    if ((threadIdx.x & 7) == 0) {
+      float* o = part + ((size_t)(sl * G1 + i) * ACC_CHUNKS + ch) * ACC_PART;
+      o[k] = mb; o[k + 1] = sb;
+    }
   }
 }
 
-// grid (rows, n_seqs, ACC_CHUNKS), 512 threads: row i of sequence slot si, vocabulary chunk ch.  Writes the chunk's
-// candidates (token emitted if this row is where drafting is cut) and, from chunk 0, rej (row's draft rejected).
-__global__ __launch_bounds__(512) void accept_rows_kernel(const float* __restrict__ tl, const float* __restrict__ ring,
-                                                          const int* __restrict__ draft_tok, AccArgs aa, int G1, int V, int mode,
-                                                          uint64_t seed, uint32_t step, int phase, float* __restrict__ part,
-                                                          int* __restrict__ rej) {
+// Four consecutive entries v..v+3 of both rows (one Philox block); 16-byte loads where the rows start on 16 bytes
+__device__ __forceinline__ void acc_load4(const float* t, const float* q, bool wide, int v, int v1, float (&tv)[4], float (&qv)[4]) {
+  if (wide && v + 4 <= v1) {
+    const float4 a = *reinterpret_cast<const float4*>(t + v), b = *reinterpret_cast<const float4*>(q + v);
+    tv[0] = a.x; tv[1] = a.y; tv[2] = a.z; tv[3] = a.w;
+    qv[0] = b.x; qv[1] = b.y; qv[2] = b.z; qv[3] = b.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      tv[e] = v + e < v1 ? t[v + e] : -INFINITY;
+      qv[e] = v + e < v1 ? q[v + e] : -INFINITY;
+    }
+  }
+}
+
+// greedy: grid (rows, n_seqs, ACC_CHUNKS), 512 threads: best effective logit of row i over chunk ch
+__global__ __launch_bounds__(512) void accept_rows_kernel(const float* __restrict__ tl, const float* __restrict__ ring, AccArgs aa, int G1, int V,
+                                                          int phase, float* __restrict__ part) {
   __shared__ float redv[16];
   __shared__ int redi[16];
-  const int si = blockIdx.y, ch = blockIdx.z, s = aa.seq[si], sl = aa.slot[si];
-  const int gamma = aa.gamma[si];
+  const int si = blockIdx.y, ch = blockIdx.z, sl = aa.slot[si];
   int i;
-  if (!acc_row(phase, gamma, blockIdx.x, i)) return;
+  if (!acc_row(phase, aa.gamma[si], blockIdx.x, i)) return;
   const float beta = aa.beta[si];
   const float* t = tl + (size_t)(sl * G1 + i) * V;
   const float* q = ring + (size_t)(aa.qslot[si] * G1 + i) * V;
-  const int y = i < gamma ? draft_tok[aa.qslot[si] * G1 + i] : -1;
-  float* prow = part + (size_t)(sl * G1 + i) * ACC_CHUNKS * ACC_PART;
-  float* o = prow + ch * ACC_PART;
+  float* o = part + ((size_t)(sl * G1 + i) * ACC_CHUNKS + ch) * ACC_PART;
   int v0, v1;
   acc_chunk_range(V, ch, v0, v1);
-  // four consecutive entries (one Philox block) per thread and round; 16-byte loads where the row starts on 16 bytes
   const bool wide = ((reinterpret_cast<uintptr_t>(t) | reinterpret_cast<uintptr_t>(q)) & 15) == 0;
-  auto load4 = [&](int v, float (&tv)[4], float (&qv)[4]) {
-    if (wide && v + 4 <= v1) {
-      const float4 a = *reinterpret_cast<const float4*>(t + v), b = *reinterpret_cast<const float4*>(q + v);
-      tv[0] = a.x; tv[1] = a.y; tv[2] = a.z; tv[3] = a.w;
-      qv[0] = b.x; qv[1] = b.y; qv[2] = b.z; qv[3] = b.w;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        tv[e] = v + e < v1 ? t[v + e] : -INFINITY;
-        qv[e] = v + e < v1 ? q[v + e] : -INFINITY;
-      }
-    }
-  };
-  if (mode == 0) {
-    float best = -INFINITY;
-    int bi = 0x7fffffff;
-    for (int v = v0 + threadIdx.x * 4; v < v1; v += blockDim.x * 4) {
-      float tv[4], qv[4];
-      load4(v, tv, qv);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float x = tv[e] + beta * qv[e];
-        if (v + e < v1 && x > best) { best = x; bi = v + e; }
-      }
-    }
-    block_argmax(best, bi, redv, redi);
-    if (threadIdx.x == 0) {
-      o[4] = -INFINITY; o[5] = __int_as_float(0x7fffffff);
-      o[6] = best; o[7] = __int_as_float(bi);
-    }
-    return;
-  }
-  // log-sum-exp of effective target and of draft logits from the chunk statistics: one chunk per lane, combined in the same
-  // order in every block of the row
-  const float* pc = prow + (threadIdx.x & 15) * ACC_PART;
-  const float m1 = pc[0], s1 = pc[1], m2 = pc[2], s2 = pc[3];
-  float mp = m1, mq = m2;
-#pragma unroll
-  for (int x = 8; x > 0; x >>= 1) { mp = fmaxf(mp, __shfl_xor(mp, x, 64)); mq = fmaxf(mq, __shfl_xor(mq, x, 64)); }
-  float sp = m1 > -INFINITY ? s1 * expf(m1 - mp) : 0.f, sq = m2 > -INFINITY ? s2 * expf(m2 - mq) : 0.f;
-#pragma unroll
-  for (int x = 8; x > 0; x >>= 1) { sp += __shfl_xor(sp, x, 64); sq += __shfl_xor(sq, x, 64); }
-  const float lsp = mp + logf(sp), lsq = mq + logf(sq);
-  // candidate token: Gumbel-max over log max(0, p - q) (rows < gamma) or log p (bonus row);
-  // if no residual mass exists the row falls back to log p with the same noise
-  float best = -INFINITY, bestp = -INFINITY;
-  int bi = 0x7fffffff, bip = 0x7fffffff;
-  for (int blk = (v0 >> 2) + threadIdx.x; blk * 4 < v1; blk += blockDim.x) {
+  float best = -INFINITY;
+  int bi = 0x7fffffff;
+  for (int v = v0 + threadIdx.x * 4; v < v1; v += 512 * 4) {
     float tv[4], qv[4];
-    load4(blk * 4, tv, qv);
-    const uint4 b = vocab_bits(seed, s, step, (uint32_t)(i + 1), PURPOSE_NEXT, (uint32_t)blk);
-    const float g4[4] = {gumbel(u01(b.x)), gumbel(u01(b.y)), gumbel(u01(b.z)), gumbel(u01(b.w))};
+    acc_load4(t, q, wide, v, v1, tv, qv);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int v = blk * 4 + e;
-      if (v < v1) {
-        const float lp = tv[e] + beta * qv[e] - lsp;
-        const float kp = lp + g4[e];
-        if (kp > bestp) { bestp = kp; bip = v; }
-        if (i < gamma) {
-          const float w = expf(lp) - expf(qv[e] - lsq);
-          if (w > 0.f) {
-            const float kr = logf(w) + g4[e];
-            if (kr > best) { best = kr; bi = v; }
-          }
-        }
-      }
+      const float x = tv[e] + beta * qv[e];
+      if (v + e < v1 && x > best) { best = x; bi = v + e; }
     }
   }
-  block_argmax(bestp, bip, redv, redi);
-  if (i < gamma) block_argmax(best, bi, redv, redi);
+  block_argmax(best, bi, redv, redi);
   if (threadIdx.x == 0) {
-    o[4] = best; o[5] = __int_as_float(bi);
-    o[6] = bestp; o[7] = __int_as_float(bip);
-    if (ch == 0) {
-      int rj = 0;
-      if (i < gamma) {
-        const int yc = min(max(y, 0), V - 1);          // a caller-held draft id outside the vocabulary must not index past the row
-        const float ratio = expf((t[yc] + beta * q[yc] - lsp) - (q[yc] - lsq));
-        const uint4 b = vocab_bits(seed, s, step, (uint32_t)(i + 1), PURPOSE_ACCEPT, 0u);
-        rj = (u01(b.x) > ratio) ? 1 : 0;
-      }
-      rej[sl * G1 + i] = rj;
-    }
+    o[6] = best; o[7] = __int_as_float(bi);
   }
 }
 
-// n = first rejected row (or gamma).  n < gamma: next token = row n's candidate, tokens appended, results (n, z) to the
-// caller's arrays and to pinned host memory.  n = gamma: the bonus row's candidate if it has been evaluated (phases
-// BONUS and ALL); in phase DRAFTS its draft logits still need one more draft forward: the drafts are appended and
-// (gamma, -1) says that phase BONUS is still to come.  The ticket is written last; the host polls for it.
+// Results of one sequence (one thread calls it; the accepted drafts' tokens are the caller's): the emitted token, (n, z) to the
+// caller's arrays and to pinned host memory.  The ticket is written last; the host polls for it.
+__device__ __forceinline__ void acc_emit(const AccArgs& aa, int si, int n, int z, int* tk, int* out_n, int* out_z, int* host_res, int* host_tick, int ticket,
+                                         int V, int* host_bad) {
+  const int s = aa.seq[si], sl = aa.slot[si];
+  if (z >= 0 && tk) tk[n] = checked_token(z, V, host_bad, s);   // out_z keeps the raw value: 0x7fffffff = no finite logit decided
+  out_n[sl] = n;
+  out_z[sl] = z;
+  if (host_res) {
+    host_res[2 * s] = n;
+    host_res[2 * s + 1] = z;
+    __threadfence_system();            // the results first, then the ticket the host polls for
+    host_tick[s] = ticket;
+  }
+}
+
+// sampling, after accept_stats_kernel: grid (ACC_PICKERS, n_seqs), 512 threads of one entry each at a time.  Bound by a chain
+// of round trips and by the instructions between them (a Philox block, logarithms and exponentials: 0.5 us for one entry, 1.5
+// for the four that a Philox block serves, hence one per thread).  Candidates of the one row that is cut at, instead of all
+// rows' in a launch between the statistics and a third one that found that row, take a window of 16 from 15.7 us a call to 10.4.
+// A row's log-sum-exps combine the chunks in the order of their butterfly over 16 lanes, the same in every block.
+// cand: per slot [ACC_PICKERS][2] (value, id) of the residual and of p.
+__global__ __launch_bounds__(512) void accept_pick_kernel(const float* tl, const float* ring, const int* draft_tok, const float* part, int* arrivals, int G1,
+                                                          int V, uint64_t seed, uint32_t step, int phase, uint64_t* cand, int max_seq, int* tokens,
+                                                          int* out_n, int* out_z, int* host_res, int* host_tick, int ticket, int* host_bad, AccArgs aa) {
+  static_assert(ACC_CHUNKS == 16 && ACC_MAXROWS == 32, "16 lanes per row, four rows per wave, eight waves");
+  __shared__ float lse[ACC_MAXROWS][2];
+  __shared__ int rej[ACC_MAXROWS];
+  __shared__ float redv[2][8];
+  __shared__ int redi[2][8];
+  __shared__ int last;
+  const int blk = blockIdx.x, si = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int s = aa.seq[si], sl = aa.slot[si], qs = aa.qslot[si], gamma = aa.gamma[si];
+  const float beta = aa.beta[si];
+  const int rows = phase == ACC_PHASE_DRAFTS ? gamma : gamma + 1, first = phase == ACC_PHASE_BONUS ? gamma : 0;   // rows with statistics
+  {
+    const int i = wave * 4 + (lane >> 4);                // row of this group of 16 lanes, one chunk per lane
+    const int ic = max(first, min(i, rows - 1));
+    int rj = 0;
+    if (rows > first) {
+      const float4 pc = *reinterpret_cast<const float4*>(part + ((size_t)(sl * G1 + ic) * ACC_CHUNKS + (lane & 15)) * ACC_PART);
+      const int y = ic < gamma ? draft_tok[qs * G1 + ic] : 0;
+      const int yc = min(max(y, 0), V - 1);              // a caller-held draft id outside the vocabulary must not index past the row
+      const float ty = tl[(size_t)(sl * G1 + ic) * V + yc], qy = ring[(size_t)(qs * G1 + ic) * V + yc];
+      const uint4 b = vocab_bits(seed, s, step, (uint32_t)(ic + 1), PURPOSE_ACCEPT, 0u);
+      float mp = pc.x, mq = pc.z;
+      mp = fmaxf(mp, dpp_f32<0x128>(mp)); mq = fmaxf(mq, dpp_f32<0x128>(mq));      // row_ror 8, 4, 2, 1
+      mp = fmaxf(mp, dpp_f32<0x124>(mp)); mq = fmaxf(mq, dpp_f32<0x124>(mq));
+      mp = fmaxf(mp, dpp_f32<0x122>(mp)); mq = fmaxf(mq, dpp_f32<0x122>(mq));
+      mp = fmaxf(mp, dpp_f32<0x121>(mp)); mq = fmaxf(mq, dpp_f32<0x121>(mq));
+      float sp = pc.x > -INFINITY ? pc.y * expf(pc.x - mp) : 0.f, sq = pc.z > -INFINITY ? pc.w * expf(pc.z - mq) : 0.f;
+      sp += dpp_f32<0x128>(sp); sq += dpp_f32<0x128>(sq);
+      sp += dpp_f32<0x124>(sp); sq += dpp_f32<0x124>(sq);
+      sp += dpp_f32<0x122>(sp); sq += dpp_f32<0x122>(sq);
+      sp += dpp_f32<0x121>(sp); sq += dpp_f32<0x121>(sq);
+      const float lsp = mp + logf(sp), lsq = mq + logf(sq);
+      const float ratio = expf((ty + beta * qy - lsp) - (qy - lsq));
+      rj = u01(b.x) > ratio ? 1 : 0;
+      if ((lane & 15) == 0) { lse[i][0] = lsp; lse[i][1] = lsq; }
+    }
+    if ((lane & 15) == 0) rej[i] = i < gamma && phase != ACC_PHASE_BONUS ? rj : 0;
+  }
+  __syncthreads();
+  const unsigned long long bad = __ballot(lane < ACC_MAXROWS && rej[lane & 31]);
+  const int n = bad ? __ffsll(bad) - 1 : gamma;          // first rejected row, or every draft accepted
+  int z = -1;
+  if (n < gamma || phase != ACC_PHASE_DRAFTS) {
+    // candidate tokens of row n: Gumbel-max over log max(0, p - q) (rows < gamma) or log p (bonus row);
+    // if no residual mass exists the row falls back to log p with the same noise
+    const float* t = tl + (size_t)(sl * G1 + n) * V;
+    const float* q = ring + (size_t)(qs * G1 + n) * V;
+    const float lsp = lse[n][0], lsq = lse[n][1];
+    float best[2] = {-INFINITY, -INFINITY};              // [0] residual, [1] p
+    int bi[2] = {0x7fffffff, 0x7fffffff};
+    for (int v = blk * 512 + threadIdx.x; v < V; v += ACC_PICKERS * 512) {
+      const float tv = t[v], qv = q[v];
+      const uint4 b = vocab_bits(seed, s, step, (uint32_t)(n + 1), PURPOSE_NEXT, (uint32_t)v >> 2);
+      const float g = gumbel(u01((v & 2) ? ((v & 1) ? b.w : b.z) : ((v & 1) ? b.y : b.x)));
+      const float lp = tv + beta * qv - lsp;
+      const float kp = lp + g;
+      if (kp > best[1]) { best[1] = kp; bi[1] = v; }
+      if (n < gamma) {
+        const float w = expf(lp) - expf(qv - lsq);
+        if (w > 0.f) {
+          const float kr = logf(w) + g;
+          if (kr > best[0]) { best[0] = kr; bi[0] = v; }
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      wave_best(best[k], bi[k]);
+      if (lane == 0) { redv[k][wave] = best[k]; redi[k][wave] = bi[k]; }
+    }
+    __syncthreads();
+    // the block's candidates, written through to memory; the last block to arrive reads all of them (hand-over without a
+    // device-scope fence: see gemm_w16_kernel)
+    if (wave == 0) {
+      uint64_t* o = cand + (size_t)sl * ACC_PICKERS * 2;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        float v = redv[k][lane & 7];
+        int id = redi[k][lane & 7];
+        wave_best(v, id);
+        if (lane == 0)
+          __hip_atomic_store(o + blk * 2 + k, (uint64_t)__float_as_uint(v) | (uint64_t)(uint32_t)id << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt 0: the write-through stores have completed
+      int got = 0;
+      if (lane == 0) got = __hip_atomic_fetch_add(arrivals + sl * G1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      got = __builtin_amdgcn_readfirstlane(got);
+      if (got == ACC_PICKERS - 1) {
+        static_assert(ACC_PICKERS == 64, "a lane per block");
+        float cv[2];
+        int ci[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const uint64_t w = __hip_atomic_load(o + lane * 2 + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          cv[k] = __uint_as_float((uint32_t)w);
+          ci[k] = (int)(w >> 32);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) wave_best(cv[k], ci[k]);
+        z = n < gamma && cv[0] > -INFINITY ? ci[0] : ci[1];
+      }
+      if (lane == 0) last = got == ACC_PICKERS - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+  } else if (blk) {
+    return;                                              // nothing to look for: one block reports
+  }
+  int* tk = tokens ? tokens + (size_t)s * max_seq + aa.len[si] : nullptr;
+  if (phase != ACC_PHASE_BONUS && tk && (int)threadIdx.x < n) tk[threadIdx.x] = draft_tok[qs * G1 + threadIdx.x];
+  if (threadIdx.x == 0) acc_emit(aa, si, n, z, tk, out_n, out_z, host_res, host_tick, ticket, V, host_bad);
+}
+
+// greedy: n = first rejected row (or gamma).  n < gamma: next token = row n's best, tokens appended.  n = gamma: the bonus
+// row's best if it has been evaluated (phases BONUS and ALL); in phase DRAFTS its draft logits still need one more draft
+// forward: the drafts are appended and (gamma, -1) says that phase BONUS is still to come.
 // tokens and the host words may be null (acceptance on caller-held logits without a context).
 // One wave per sequence: 16 lanes look at a row's 16 chunks, so that the rows' candidates are a few rounds of loads (a
 // serial walk over rows and chunks took 50 us for 16 greedy windows).
-__global__ __launch_bounds__(64) void accept_finalize_kernel(const float* __restrict__ part, const int* __restrict__ rej, const int* __restrict__ draft_tok,
-                                       AccArgs aa, int G1, int mode, int phase, int max_seq, int* __restrict__ tokens,
+__global__ __launch_bounds__(64) void accept_finalize_kernel(const float* __restrict__ part, const int* __restrict__ draft_tok,
+                                       AccArgs aa, int G1, int phase, int max_seq, int* __restrict__ tokens,
                                        int* __restrict__ out_n, int* __restrict__ out_z, int* __restrict__ host_res,
                                        int* __restrict__ host_tick, int ticket, int V, int* host_bad) {
   static_assert(ACC_CHUNKS == 16, "one lane per chunk, four rows at a time");
@@ -755,49 +866,29 @@ __global__ __launch_bounds__(64) void accept_finalize_kernel(const float* __rest
   };
   int n = gamma;
   if (phase != ACC_PHASE_BONUS) {
-    if (mode == 0) {
-      // greedy: row i's draft is rejected when it differs from the row's argmax
-      for (int i0 = 0; i0 < gamma && n == gamma; i0 += 4) {
-        const int i = i0 + (lane >> 4), ic = min(i, gamma - 1);
-        const float* pr = part + ((size_t)(sl * G1 + ic) * ACC_CHUNKS + ch) * ACC_PART;
-        float best = pr[6];
-        int bi = __float_as_int(pr[7]);
-        // a chunk without a finite value leaves (-inf, sentinel), as does a row of them
-        over_chunks(best, bi);
-        const unsigned long long bad = __ballot(i < gamma && bi != draft_tok[qs * G1 + ic]);
-        if (bad) n = i0 + (__ffsll(bad) - 1) / 16;
-      }
-    } else {
-      for (int i0 = 0; i0 < gamma && n == gamma; i0 += 64) {
-        const unsigned long long bad = __ballot(i0 + lane < gamma && rej[sl * G1 + min(i0 + lane, gamma - 1)]);
-        if (bad) n = i0 + __ffsll(bad) - 1;
-      }
+    // row i's draft is rejected when it differs from the row's argmax
+    for (int i0 = 0; i0 < gamma && n == gamma; i0 += 4) {
+      const int i = i0 + (lane >> 4), ic = min(i, gamma - 1);
+      const float* pr = part + ((size_t)(sl * G1 + ic) * ACC_CHUNKS + ch) * ACC_PART;
+      float best = pr[6];
+      int bi = __float_as_int(pr[7]);
+      // a chunk without a finite value leaves (-inf, sentinel), as does a row of them
+      over_chunks(best, bi);
+      const unsigned long long bad = __ballot(i < gamma && bi != draft_tok[qs * G1 + ic]);
+      if (bad) n = i0 + (__ffsll(bad) - 1) / 16;
     }
   }
   int z = -1;
   if (phase != ACC_PHASE_DRAFTS || n < gamma) {
-    // the emitted token: best residual candidate of row n over the chunks, else best candidate of p
     const float* pr = part + ((size_t)(sl * G1 + n) * ACC_CHUNKS + ch) * ACC_PART;
-    float best = pr[4], bestp = pr[6];
-    int bi = __float_as_int(pr[5]), bip = __float_as_int(pr[7]);
-    over_chunks(best, bi);
-    over_chunks(bestp, bip);
-    z = (n < gamma && best > -INFINITY) ? bi : bip;
+    float best = pr[6];
+    z = __float_as_int(pr[7]);
+    over_chunks(best, z);
   }
   int* tk = tokens ? tokens + (size_t)s * max_seq + aa.len[si] : nullptr;
   if (phase != ACC_PHASE_BONUS && tk)
     for (int k = threadIdx.x; k < n; k += blockDim.x) tk[k] = draft_tok[qs * G1 + k];
-  if (threadIdx.x == 0) {
-    if (z >= 0 && tk) tk[n] = checked_token(z, V, host_bad, s);   // out_z keeps the raw value: 0x7fffffff = no finite logit decided
-    out_n[sl] = n;
-    out_z[sl] = z;
-    if (host_res) {
-      host_res[2 * s] = n;
-      host_res[2 * s + 1] = z;
-      __threadfence_system();            // the results first, then the ticket the host polls for
-      host_tick[s] = ticket;
-    }
-  }
+  if (threadIdx.x == 0) acc_emit(aa, si, n, z, tk, out_n, out_z, host_res, host_tick, ticket, V, host_bad);
 }
 
 // ------------------------------------------------------------------ streaming-read probe (benchmarks)

@@ -69,7 +69,8 @@ struct pacer_ctx {
   // workspace carve-up
   bool ws_bound = false;
   int G1 = 0, rcap = 0, prows = 0, dmax = 0, fmax = 0, kmax = 0, hmax = 0, hdmax = 0, max_seq = 0;   // prows: rows the attention partials hold
-  int *tokens = nullptr, *draft_tok = nullptr, *rej = nullptr;
+  int *tokens = nullptr, *draft_tok = nullptr, *acc_cnt = nullptr;
+  uint64_t* acc_cand = nullptr;   // acceptance by sampling: candidates of the pick kernel's blocks
   float* acc_part = nullptr;   // acceptance: per (slot, row, vocabulary chunk) statistics and candidates
   float *ring = nullptr, *hidden = nullptr, *x = nullptr, *xn = nullptr, *qkv = nullptr, *ao = nullptr, *part = nullptr;
   float* rope_pos[2] = {nullptr, nullptr};   // cos/sin of every position, [0] target, [1] draft and M_B (same head size and theta); filled at bind time
@@ -170,7 +171,8 @@ size_t carve(pacer_ctx* c, void* base) {
   c->tokens = k.take<int>((size_t)B * c->max_seq);
   c->draft_tok = k.take<int>((size_t)B * G1);
   c->acc_part = k.take<float>((size_t)B * G1 * ACC_CHUNKS * ACC_PART);
-  c->rej = k.take<int>((size_t)B * G1);
+  c->acc_cnt = k.take<int>((size_t)B * G1);
+  c->acc_cand = k.take<uint64_t>((size_t)B * ACC_PICKERS * 2);
   c->ring = k.take<float>((size_t)B * G1 * V);
   c->hidden = k.take<float>((size_t)B * G1 * dD);
   c->x = k.take<float>((size_t)c->rcap * c->dmax);
@@ -911,16 +913,17 @@ void mb_prefix_rows(pacer_ctx* c, const int* ids, int m, bool bonus) {
 void accept_launch(pacer_ctx* c, const AccArgs& aa, int rows, int phase, int mode, uint64_t seed, uint64_t ctr, const float* dev_logits,
                    int* dev_n, int* dev_z) {
   const int V = c->m[PACER_TARGET].cfg.vocab;
-  if (rows > 0) {
-    const dim3 grid(rows, aa.n_seqs, ACC_CHUNKS);
-    if (mode != PACER_GREEDY)
-      PACER_LAUNCH(accept_stats_kernel, grid, dim3(256), 0, c->stream, dev_logits, c->ring, aa, c->G1, V, phase, c->acc_part);
-    PACER_LAUNCH(accept_rows_kernel, grid, dim3(512), 0, c->stream, dev_logits, c->ring, c->draft_tok, aa, c->G1, V, mode, seed,
-                 (uint32_t)ctr, phase, c->acc_part, c->rej);
+  const dim3 grid(rows, aa.n_seqs, ACC_CHUNKS);
+  int *host_res = c->host_res_dev, *host_tick = c->host_res_dev + 2 * PACER_MAX_BATCH;
+  if (mode != PACER_GREEDY) {
+    if (rows > 0) PACER_LAUNCH(accept_stats_kernel, grid, dim3(512), 0, c->stream, dev_logits, c->ring, c->acc_part, c->acc_cnt, c->G1, V, phase, aa);
+    PACER_LAUNCH(accept_pick_kernel, dim3(ACC_PICKERS, aa.n_seqs), dim3(512), 0, c->stream, dev_logits, c->ring, c->draft_tok, c->acc_part, c->acc_cnt, c->G1, V,
+                 seed, (uint32_t)ctr, phase, c->acc_cand, c->max_seq, c->tokens, dev_n, dev_z, host_res, host_tick, ++c->acc_calls, host_bad_dev(c), aa);
+  } else {
+    if (rows > 0) PACER_LAUNCH(accept_rows_kernel, grid, dim3(512), 0, c->stream, dev_logits, c->ring, aa, c->G1, V, phase, c->acc_part);
+    PACER_LAUNCH(accept_finalize_kernel, dim3(aa.n_seqs), dim3(64), 0, c->stream, c->acc_part, c->draft_tok, aa, c->G1, phase, c->max_seq, c->tokens,
+                 dev_n, dev_z, host_res, host_tick, ++c->acc_calls, V, host_bad_dev(c));
   }
-  PACER_LAUNCH(accept_finalize_kernel, dim3(aa.n_seqs), dim3(64), 0, c->stream, c->acc_part, c->rej, c->draft_tok, aa, c->G1, mode,
-               phase, c->max_seq, c->tokens, dev_n, dev_z, c->host_res_dev, c->host_res_dev + 2 * PACER_MAX_BATCH, ++c->acc_calls, V,
-               host_bad_dev(c));
   for (int i = 0; i < aa.n_seqs; ++i) c->seq[aa.seq[i]].acc_ticket = c->acc_calls;
 }
 
@@ -976,7 +979,7 @@ int fold(pacer_ctx* c, int s) {
 }
 
 // ---- acceptance without a context and without any allocation ---------------------------------
-// The per-(row, vocabulary chunk) statistics and candidates and the per-row reject flags of the acceptance
+// The per-(row, vocabulary chunk) statistics and candidates and the arrival counter of the acceptance
 // kernels, for PACER_NOALLOC_MAX_GAMMA + 1 rows, in an array that is part of the library's device image: each
 // GPU the library runs on holds its own copy until the process ends.  Host code never uses the array's name as
 // an address (on the host it is only a stand-in for the symbol): the device address is looked up once per
@@ -984,7 +987,8 @@ int fold(pacer_ctx* c, int s) {
 constexpr int kNoAllocRows = PACER_NOALLOC_MAX_GAMMA + 1;
 struct NoAllocScratch {
   float part[kNoAllocRows * ACC_CHUNKS * ACC_PART];
-  int rej[kNoAllocRows];
+  uint64_t cand[ACC_PICKERS * 2];
+  int arrivals[kNoAllocRows];
 };
 constexpr int kMaxDevices = 64;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -1521,16 +1525,20 @@ int32_t pacer_accept_noalloc(const float* dev_target_logits, const float* dev_dr
   aa.beta[0] = beta;
   const int G1 = gamma + 1;
   // Every word of the scratch that a launch reads was written earlier in this same call (statistics by
-  // accept_stats, candidates and reject flags by accept_rows), so nothing has to start at zero.
+  // accept_stats, which also clears the arrival counter of the launch after it; candidates by that launch), so nothing has to
+  // start at zero, and calls that overlapped leave nothing behind that a later call would read.
   // The caller holds the bonus row's draft logits, so one set of launches evaluates it beside the others.
   const int phase = bonus_row ? ACC_PHASE_ALL : ACC_PHASE_DRAFTS;
   const dim3 grid(gamma + (bonus_row ? 1 : 0), 1, ACC_CHUNKS);
-  if (mode != PACER_GREEDY)
-    hipLaunchKernelGGL(accept_stats_kernel, grid, dim3(256), 0, st, dev_target_logits, dev_draft_logits, aa, G1, vocab, phase, sc->part);
-  hipLaunchKernelGGL(accept_rows_kernel, grid, dim3(512), 0, st, dev_target_logits, dev_draft_logits, dev_draft_tokens, aa, G1, vocab, mode, seed,
-                     (uint32_t)ctr, phase, sc->part, sc->rej);
-  hipLaunchKernelGGL(accept_finalize_kernel, dim3(1), dim3(64), 0, st, sc->part, sc->rej, dev_draft_tokens, aa, G1, mode, phase, 0, (int*)nullptr,
-                     dev_n, dev_z, (int*)nullptr, (int*)nullptr, 0, vocab, (int*)nullptr);
+  if (mode != PACER_GREEDY) {
+    hipLaunchKernelGGL(accept_stats_kernel, grid, dim3(512), 0, st, dev_target_logits, dev_draft_logits, sc->part, sc->arrivals, G1, vocab, phase, aa);
+    hipLaunchKernelGGL(accept_pick_kernel, dim3(ACC_PICKERS, 1), dim3(512), 0, st, dev_target_logits, dev_draft_logits, dev_draft_tokens, sc->part, sc->arrivals,
+                       G1, vocab, seed, (uint32_t)ctr, phase, sc->cand, 0, (int*)nullptr, dev_n, dev_z, (int*)nullptr, (int*)nullptr, 0, (int*)nullptr, aa);
+  } else {
+    hipLaunchKernelGGL(accept_rows_kernel, grid, dim3(512), 0, st, dev_target_logits, dev_draft_logits, aa, G1, vocab, phase, sc->part);
+    hipLaunchKernelGGL(accept_finalize_kernel, dim3(1), dim3(64), 0, st, sc->part, dev_draft_tokens, aa, G1, phase, 0, (int*)nullptr, dev_n, dev_z,
+                       (int*)nullptr, (int*)nullptr, 0, vocab, (int*)nullptr);
+  }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_noctx(PACER_EHIP, "accept_noalloc: %s", hipGetErrorString(e));
   return PACER_OK;

@@ -241,3 +241,9 @@ def test_accept_noalloc_against_float64_at_odd_sizes(gamma, vocab, shift):
             assert (int(out_n.item()), int(out_z.item())) == (n, int(np.argmax(key[n]))), (mode, trial, margin)
             compared.add(mode)
     assert len(compared) == 2
+
+
+@pytest.mark.parametrize("gamma,vocab,shift", [(2, 32769, 1), (3, 70003, 0)])
+def test_accept_noalloc_vocabularies_beyond_one_round_of_the_pick_kernel(gamma, vocab, shift):
+    """64 blocks of 512 threads take one entry each at a time: one entry more than that, and two full rounds and a part."""
+    test_accept_noalloc_against_float64_at_odd_sizes(gamma, vocab, shift)
