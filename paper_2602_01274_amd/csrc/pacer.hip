@@ -601,6 +601,7 @@ void run_layers_w16(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows&
   base.mt_total_out = mt_total;
   base.row_slot = row_slots(sr);
   for (int l = 0; l < L; ++l) {
+    const bool last_kv = kv_only || (cache_only && l + 1 == L);      // nothing reads this layer's queries
     {
       GemmArgs ga = base;
       ga.W = static_cast<const u32x4*>(m.wqkv[l]);
@@ -611,10 +612,10 @@ void run_layers_w16(pacer_ctx* c, const Model& m, int tag, int R, const SeqRows&
       ga.kv = static_cast<_Float16*>(m.kv);
       ga.rope = c->rope_pos[tag == 0 ? PACER_TARGET : PACER_DRAFT];
       ga.layer = l;
-      ga.nt_begin = kv_only ? d / 16 : 0;
-      gemm_w16<EPI_QKV>(c, tag, true, ga, (kv_only ? 2 : 3) * d / 16, d);
+      ga.nt_begin = last_kv ? d / 16 : 0;
+      gemm_w16<EPI_QKV>(c, tag, true, ga, (last_kv ? 2 : 3) * d / 16, d);
     }
-    if (kv_only || (cache_only && l + 1 == L)) continue;
+    if (last_kv) continue;
     {
       const _Float16* kv = static_cast<const _Float16*>(m.kv);
       // 17..32 rows per sequence: two row tiles.  With a short context and few (head, sequence) pairs the
