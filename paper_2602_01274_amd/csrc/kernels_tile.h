@@ -259,7 +259,6 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void gemm_tile_kernel(const GemmAr
       }
     }
   }
-  constexpr bool paired = (EPI == EPI_SWIGLU) || (EPI == EPI_QKV);
   constexpr int BCH = EPI == EPI_RESID || EPI == EPI_QKV ? (12 / NC > 0 ? (12 / NC < MR ? 12 / NC : MR) : 1) : 1;   // rows whose inputs are in flight together
   RowCtx rc[MR];
 #pragma unroll
@@ -280,13 +279,7 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void gemm_tile_kernel(const GemmAr
       for (int a = 0; a < NC; ++a) {
         const int nt = nt0 + wc * NC + a;
         if (nt >= nt_end) continue;
-        const f32x4 s = acc[a][b];
-        f32x4 s2 = {0.f, 0.f, 0.f, 0.f};
-        if (paired) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) s2[r] = __shfl_xor(s[r], 32, 64);
-        }
-        const float sq = gemm_epilogue<EPI, true>(ga, rc[b], ax[b - b0][a], nt, m, lane, s, s2);
+        const float sq = gemm_epilogue<EPI, true>(ga, rc[b], ax[b - b0][a], nt, m, lane, acc[a][b]);
         if (EPI == EPI_RESID) ssq += tile_ssq(sq);
       }
       if (EPI == EPI_RESID) add_row_ssq(ga, rc[b], m, lane, ssq);

@@ -327,12 +327,9 @@ __device__ __forceinline__ EpiAux epi_aux(const GemmArgs& ga, const RowCtx& rc, 
     const int tiles_d = ga.d >> 4, half = ga.hd >> 1, tsh = ga.hd == 128 ? 3 : 2;      // 8 or 4 tiles per head
     if (nt < 2 * tiles_d) {
       const int tq = nt >= tiles_d ? nt - tiles_d : nt;
-      const int h = tq >> tsh, j0 = 8 * (tq & ((1 << tsh) - 1)) + 4 * (g4 & 1);        // rotation pairs j0..j0+3
-      const f32x4* tb = reinterpret_cast<const f32x4*>(ga.rope + ((size_t)rc.pos * half + j0) * 2);
-      x.a = tb[0];
-      x.b = tb[1];
-      // lane l ^ 32 holds the other members of the pairs: lanes with g4 < 2 produce dims j0.., the others j0 + hd/2..
-      const int dim = j0 + (g4 >= 2 ? half : 0);
+      // rotation pairs (dim, dim + hd/2) and (dim + 1, dim + 1 + hd/2), see gemm_epilogue
+      const int h = tq >> tsh, dim = 8 * (tq & ((1 << tsh) - 1)) + 4 * (g4 & 1) + (g4 >= 2 ? 2 : 0);
+      x.a = *reinterpret_cast<const f32x4*>(ga.rope + ((size_t)rc.pos * half + dim) * 2);
       if (nt < tiles_d)
         // attention operand: [slot][head][kt][2 row tiles][hi|lo][lane][8], lane = 16*(dim%32/8) + row%16
         x.p = reinterpret_cast<char*>(ga.qp + ((((size_t)rc.si * ga.H + h) * (ga.hd >> 5) + (dim >> 5)) * 2 + (rc.rl >> 4)) * 1024 + (((dim & 31) >> 3) * 16 + (rc.rl & 15)) * 8 + (dim & 7));
@@ -349,7 +346,7 @@ __device__ __forceinline__ EpiAux epi_aux(const GemmArgs& ga, const RowCtx& rc, 
       x.a = f32x4{gumbel(u01(bits.x)), gumbel(u01(bits.y)), gumbel(u01(bits.z)), gumbel(u01(bits.w))};
     }
   } else {
-    // lanes l and l ^ 32 hold gate and up of the same four features: each takes two of them
+    // each of lanes l and l ^ 32 takes two of the four features whose gate and up they hold, see gemm_epilogue
     x.p = reinterpret_cast<char*>(packed_at(ga.xp_out, ga.mt_total_out, m, nt * 8 + (g4 & 1) * 4 + (g4 >= 2 ? 2 : 0)));
   }
   return x;
@@ -359,37 +356,66 @@ __device__ __forceinline__ EpiAux epi_aux(const GemmArgs& ga, const RowCtx& rc, 
 // wave add whole numbers before the one atomic: the accumulator ends up with the same bits however tiles and half tiles are
 // dealt to waves and blocks.
 __device__ __forceinline__ u64 tile_ssq(float sq) {
-  sq += __shfl_xor(sq, 16, 64);
-  const u64 half = (u64)(sq * SSQ_SCALE + 0.5f);
-  return half + __shfl_xor((unsigned long long)half, 32, 64);
+  const unsigned u = __float_as_uint(sq);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const u64 half = (u64)((__uint_as_float(a[0]) + __uint_as_float(a[1])) * SSQ_SCALE + 0.5f);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)half, (unsigned)half, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(half >> 32), (unsigned)(half >> 32), false, false);
+  return ((u64)hi[0] << 32 | lo[0]) + ((u64)hi[1] << 32 | lo[1]);
 }
 __device__ __forceinline__ void add_row_ssq(const GemmArgs& ga, const RowCtx& rc, int m, int l, u64 fixed) {
   if (rc.live && (l >> 4) == 0) atomicAdd(ga.ssq_out + (size_t)(blockIdx.x % SSQ_SUB) * ga.ssq_stride + m, fixed);
 }
+// the hardware's 2^x (1 ulp; results below 2^-126 are zero)
+__device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
 // 4 x 4 transpose of v among the four lanes of a quad: lane i gets v[i] of lanes 0..3
-__device__ __forceinline__ void quad_transpose(float (&v)[4], int l) {
+template <int O>
+__device__ __forceinline__ void quad_step(float (&v)[4], int l) {
+  const bool up = l & O;
 #pragma unroll
-  for (int o = 1; o <= 2; o <<= 1) {
-    const bool up = l & o;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (i & o) continue;
-      const float got = __shfl_xor(up ? v[i] : v[i + o], o, 64);
-      v[i] = up ? got : v[i];
-      v[i + o] = up ? v[i + o] : got;
-    }
+  for (int i = 0; i < 4; ++i) {
+    if (i & O) continue;
+    const float got = dpp_f32<O == 1 ? 0xB1 : 0x4E>(up ? v[i] : v[i + O]);       // of lane l ^ O
+    v[i] = up ? got : v[i];
+    v[i + O] = up ? v[i + O] : got;
   }
+}
+__device__ __forceinline__ void quad_transpose(float (&v)[4], int l) {
+  quad_step<1>(v, l);
+  quad_step<2>(v, l);
+}
+// x: lanes 0..31 keep theirs and give y's; lanes 32..63 get x's upper partner (one exchange for two values)
+__device__ __forceinline__ void swap_halves(float& x, float& y) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(p[0]);
+  y = __uint_as_float(p[1]);
+}
+// g / (1 + exp(-g)) * u.  exp(-g) = 2^n 2^f with n + f = -g log2(e), f small and with the product's rounding put back; the
+// quotient by a refined reciprocal.  The divisor lies in [1, 2^126], so neither needs the range handling of expf and of a
+// division, a third of this epilogue's instructions; the error is theirs (2.3 ulp over g in [-85, 100]).
+__device__ __forceinline__ float silu_times(float g, float u) {
+  const float p = -g * 1.44269504f;                                    // log2(e) = 1.44269504 + 1.925963e-8
+  const float lost = fmaf(-g, 1.92596303e-8f, fmaf(-g, 1.44269504f, -p));
+  const float pc = fminf(p, 126.f), n = __builtin_rintf(pc);
+  const float d = 1.0f + __builtin_amdgcn_ldexpf(exp2_hw((pc - n) + lost), (int)n);
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(fmaf(-d, r, 1.0f), r, r);
+  float q = g * r;
+  q = fmaf(fmaf(-d, q, g), r, q);
+  return q * u;
 }
 
 // Epilogue of one accumulator lane, shared by the GEMM kernels.  Lane l of a 16x16 result tile holds tile rows (outputs)
-// 4*(l/16)..+3 of activation row m; s2 holds the same of lane l ^ 32, whose outputs are the partners i+8 resp. i-8
-// (paired weight layouts: rotation pairs of QKV, gate/up of SwiGLU).  All 64 lanes of the tile call this together.
+// 4*(l/16)..+3 of activation row m.  All 64 lanes of the tile call this together: in the paired weight layouts (rotation pairs
+// of QKV, gate/up of SwiGLU) lane l ^ 32 holds the partners i+8 resp. i-8 of this lane's outputs, and the two exchange so that
+// each has both members of two of the four pairs.
+// (Exchanges as vector swaps; through LDS, with expf and divisions: 512 rows QKV 90.9 -> 89.4 us, 160 rows 71.9 -> 70.5, 1 row of
+// d 768 QKV 3.5 -> 3.4, gate/up 4.1 -> 4.0.)
 // RESID returns the lane's part of the row's sum of squares over this tile, for tile_ssq.
 // XP: RESID's operand goes to xp, which the caller has worked out ahead.
 // VT: rows of a tile may be 16 consecutive positions (prompt rows): V is stored 4 positions at a time where they are.
 template <int EPI, bool VT = false, bool XP = false>
-__device__ __forceinline__ float gemm_epilogue(const GemmArgs& ga, const RowCtx& rc, const EpiAux& ax, int nt, int m, int l, f32x4 s, f32x4 s2,
-                                               _Float16* xp = nullptr) {
+__device__ __forceinline__ float gemm_epilogue(const GemmArgs& ga, const RowCtx& rc, const EpiAux& ax, int nt, int m, int l, f32x4 s, _Float16* xp = nullptr) {
   typedef _Float16 half4 __attribute__((ext_vector_type(4)));
   const int g4 = l >> 4;
   const bool live = rc.live;
@@ -432,35 +458,32 @@ __device__ __forceinline__ float gemm_epilogue(const GemmArgs& ga, const RowCtx&
       sq = xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
     }
   } else if (EPI == EPI_SWIGLU) {
-    if (live) {
-      const bool up_lane = g4 >= 2;
-      const int r0 = up_lane ? 2 : 0;
-      float v[2];
-#pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        const float gt = (up_lane ? s2[r + 2] : s[r]) * rs, up = (up_lane ? s[r + 2] : s2[r]) * rs;
-        v[r] = gt / (1.0f + expf(-gt)) * up;
-      }
-      store_packed2(reinterpret_cast<_Float16*>(ax.p), v[0], v[1]);
-    }
+    float g0 = s[0], u0 = s[2], g1 = s[1], u1 = s[3];
+    swap_halves(g0, u0);
+    swap_halves(g1, u1);
+    if (live) store_packed2(reinterpret_cast<_Float16*>(ax.p), silu_times(g0 * rs, u0 * rs), silu_times(g1 * rs, u1 * rs));
   } else {  // EPI_QKV
     _Float16* p = reinterpret_cast<_Float16*>(ax.p);
     const int tiles_d = ga.d >> 4;
     if (nt < 2 * tiles_d) {
+      float a0 = s[0], b0 = s[2], a1 = s[1], b1 = s[3];
+      swap_halves(a0, b0);
+      swap_halves(a1, b1);
       if (live) {
-        const bool second = g4 >= 2;
-        const float cs[4] = {ax.a[0], ax.a[2], ax.b[0], ax.b[2]}, sn[4] = {ax.a[1], ax.a[3], ax.b[1], ax.b[3]};
-        float v[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float mine = s[r] * rs, other = s2[r] * rs;
-          v[r] = second ? mine * cs[r] + other * sn[r] : mine * cs[r] - other * sn[r];
-        }
-        const half4 hi = {(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
-        *reinterpret_cast<half4*>(p) = hi;
+        a0 *= rs; b0 *= rs; a1 *= rs; b1 *= rs;
+        const float v[4] = {a0 * ax.a[0] - b0 * ax.a[1], a1 * ax.a[2] - b1 * ax.a[3],              // dims dim, dim + 1
+                            b0 * ax.a[0] + a0 * ax.a[1], b1 * ax.a[2] + a1 * ax.a[3]};             // and hd/2 further
+        const half2v h0 = {(_Float16)v[0], (_Float16)v[1]}, h1 = {(_Float16)v[2], (_Float16)v[3]};
+        const int far = (ga.hd >> 6) * 512;              // half a head in both layouts: blocks of 32 dims, 512 elements each (Q: 2048)
         if (nt < tiles_d) {
-          const half4 lo = {(_Float16)(v[0] - (float)hi[0]), (_Float16)(v[1] - (float)hi[1]), (_Float16)(v[2] - (float)hi[2]), (_Float16)(v[3] - (float)hi[3])};
-          *reinterpret_cast<half4*>(p + 512) = lo;
+          const half2v l0 = {(_Float16)(v[0] - (float)h0[0]), (_Float16)(v[1] - (float)h0[1])}, l1 = {(_Float16)(v[2] - (float)h1[0]), (_Float16)(v[3] - (float)h1[1])};
+          *reinterpret_cast<half2v*>(p) = h0;
+          *reinterpret_cast<half2v*>(p + 512) = l0;
+          *reinterpret_cast<half2v*>(p + 4 * far) = h1;
+          *reinterpret_cast<half2v*>(p + 4 * far + 512) = l1;
+        } else {
+          *reinterpret_cast<half2v*>(p) = h0;
+          *reinterpret_cast<half2v*>(p + far) = h1;
         }
       }
     } else {
@@ -723,23 +746,12 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 8 ? (NT >= 5 ? 2 : 4) : 1)) v
     const int m = (ga.mt0 + b) * 16 + (l & 15);
     const int nt = nt0 + a;
     if (nt >= ga.nt_end) continue;
-    const bool paired = (EPI == EPI_SWIGLU) || (EPI == EPI_QKV);
     f32x4 s = red[0][ab][l];
 #pragma unroll
     for (int w = 1; w < NRED; ++w) s += red[w][ab][l];
-    f32x4 s2 = {0.f, 0.f, 0.f, 0.f};                   // partner rows (paired layouts)
-    if (paired) {
-      s2 = red[0][ab][l ^ 32];
-#pragma unroll
-      for (int w = 1; w < NRED; ++w) s2 += red[w][ab][l ^ 32];
-    }
     if (X17 && HL == 2 && b == 1 && (l & 15) == 0) {   // row 16: hi product in column 0, lo product in column 1
 #pragma unroll
       for (int w = 0; w < NRED; ++w) s += red[w][ab][l + 1];
-      if (paired) {
-#pragma unroll
-        for (int w = 0; w < NRED; ++w) s2 += red[w][ab][(l ^ 32) + 1];
-      }
     }
     if (!AHEAD) look_up(it);
     RowCtx rc = rcs[it];
@@ -749,7 +761,7 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 8 ? (NT >= 5 ? 2 : 4) : 1)) v
       for (int i = 0; i < SSQ_SUB; ++i) ssq += ssq_pre[it][i];
       rc.rs = 1.0f / sqrtf((float)ssq * SSQ_INV_SCALE * ga.inv_dim + ga.eps);
     }
-    const float sq = gemm_epilogue<EPI>(ga, rc, axs[it], nt, m, l, s, s2);
+    const float sq = gemm_epilogue<EPI>(ga, rc, axs[it], nt, m, l, s);
     if (EPI == EPI_RESID) add_row_ssq(ga, rc, m, l, tile_ssq(sq));
   }
 }
@@ -847,16 +859,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_row_kernel(const u32x4* W, co
   if (wave) return;
 #pragma unroll
   for (int w = 0; w < WAVES - 1; ++w) s += red[w][lane];
-  f32x4 s2 = {0.f, 0.f, 0.f, 0.f};
-  if (HALF || EPI == EPI_SWIGLU || EPI == EPI_QKV) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) s2[r] = other_half(s[r], lane);
-  }
   if (HALF) {
-    s += s2;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s[r] += other_half(s[r], lane);
     if (lane >= 32) rc.live = false;                   // lane - 32 finishes these outputs
   }
-  const float sq = gemm_epilogue<EPI, false, true>(ga, rc, ax, nt, m, l, s, s2, xp);
+  const float sq = gemm_epilogue<EPI, false, true>(ga, rc, ax, nt, m, l, s, xp);
   if (EPI == EPI_RESID) {
     const u64 fixed = tile_ssq(sq);
     if (rc.live && lane < 16) atomicAdd(ssq_to, fixed);
@@ -886,7 +894,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_row_kernel(const u32x4* W, co
 // read, masks only in groups that need them, the scale inside the exponent's fma, exchanges between the 16-lane groups as
 // vector instructions, sums of a row kept per lane until the end, no rescaling while no maximum moves: 12 heads, 530 keys
 // 5.4 -> 4.4 us, 13 rows 200 keys 4.6 -> 3.9, 512 prompt rows of 12 heads over up to 4000 keys 15.7 -> 12.8.
-__device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
 struct AttnSeq { int seq, slot, row0, n_rows, pos0, pad[3]; };
 struct AttnSeqs { AttnSeq s[PK_MAXB]; };
 template <int HD, int MT, int QL, int NW>
