@@ -70,17 +70,6 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 template <typename T> __device__ __forceinline__ float ld_f32(const T* p);
 template <> __device__ __forceinline__ float ld_f32<float>(const float* p) { return *p; }
 template <> __device__ __forceinline__ float ld_f32<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
 // A wave's exchange without a trip to LDS: v of another lane of the same 16 (DPP), and the two swaps between 16-lane groups.
 template <int CTRL> __device__ __forceinline__ float dpp_f32(float v) {
   return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, true));
@@ -135,7 +124,7 @@ __device__ __forceinline__ void wave_best(float& v, int& id) {
 // Block-wide sum in a fixed order (deterministic).  red: LDS scratch of >= 16 floats.
 __device__ __forceinline__ float block_sum(float v, float* red) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-  v = wave_sum(v);
+  v = wave_total(v);
   __syncthreads();
   if (lane == 0) red[w] = v;
   __syncthreads();
@@ -146,12 +135,7 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
 // Block-wide argmax; the lowest index wins among equal values.  Result valid in all threads.
 __device__ __forceinline__ void block_argmax(float& v, int& idx, float* redv, int* redi) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    float ov = __shfl_xor(v, o, 64);
-    int oi = __shfl_xor(idx, o, 64);
-    if (ov > v || (ov == v && oi < idx)) { v = ov; idx = oi; }
-  }
+  wave_best(v, idx);
   __syncthreads();
   if (lane == 0) { redv[w] = v; redi[w] = idx; }
   __syncthreads();

@@ -151,7 +151,8 @@ __global__ void rope_positions_kernel(float* __restrict__ tab, int hd, float the
 }
 
 // Row r of a forward's input from embedding row e: x, the first norm's operand f16(x * g) and the row's sums of
-// squares (slot 0 = sum x^2, the other slots cleared).  Called by all threads of a block.
+// squares (slot 0 = sum x^2; the other slots and parts cleared unless somebody else does).  Called by all threads of a block;
+// `meanwhile` runs while the row and the gains are on their way.
 struct EmbedOut {
   float* x;              // residual stream rows [.][ldx]
   int ldx;
@@ -161,41 +162,67 @@ struct EmbedOut {
   u64* ssq;
   int n_slots, slot_stride;
 };
-__device__ __forceinline__ void embed_row_w16(const uint16_t* __restrict__ e, int d, int r, const EmbedOut& o, float* red) {
-  uint2 w0 = {0u, 0u};
-  if ((int)threadIdx.x * 4 < d) w0 = *reinterpret_cast<const uint2*>(e + threadIdx.x * 4);
+template <typename F>
+__device__ __forceinline__ void embed_row_w16(const uint16_t* __restrict__ e, int d, int r, const EmbedOut& o, float* red, bool clear_others, F meanwhile) {
+  constexpr int CH = 4;                                  // 8-byte chunks per thread requested together: 4096 features of 256 threads
   float ss = 0.f;
-  for (int k = threadIdx.x * 4; k < d; k += blockDim.x * 4) {
-    const uint2 w = k == (int)threadIdx.x * 4 ? w0 : *reinterpret_cast<const uint2*>(e + k);
-    const float v0 = __uint_as_float(w.x << 16), v1 = __uint_as_float(w.x & 0xffff0000u);
-    const float v2 = __uint_as_float(w.y << 16), v3 = __uint_as_float(w.y & 0xffff0000u);
-    *reinterpret_cast<float4*>(o.x + (size_t)r * o.ldx + k) = make_float4(v0, v1, v2, v3);
-    store_packed4(packed_at(o.xp, o.MT_total, r, k), v0 * o.g[k], v1 * o.g[k + 1], v2 * o.g[k + 2], v3 * o.g[k + 3]);
-    ss += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
+  for (int k0 = threadIdx.x * 4; k0 - (int)threadIdx.x * 4 < d; k0 += CH * 256 * 4) {
+    uint2 w[CH];
+    float4 g[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int k = min(k0 + u * 1024, d - 4);           // a chunk past the end repeats the last one and is dropped
+      w[u] = *reinterpret_cast<const uint2*>(e + k);
+      g[u] = *reinterpret_cast<const float4*>(o.g + k);
+    }
+    if (k0 == (int)threadIdx.x * 4) meanwhile();
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int k = k0 + u * 1024;
+      if (k >= d) break;
+      const float v0 = __uint_as_float(w[u].x << 16), v1 = __uint_as_float(w[u].x & 0xffff0000u);
+      const float v2 = __uint_as_float(w[u].y << 16), v3 = __uint_as_float(w[u].y & 0xffff0000u);
+      *reinterpret_cast<float4*>(o.x + (size_t)r * o.ldx + k) = make_float4(v0, v1, v2, v3);
+      store_packed4(packed_at(o.xp, o.MT_total, r, k), v0 * g[u].x, v1 * g[u].y, v2 * g[u].z, v3 * g[u].w);
+      ss += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
+    }
   }
   ss = block_sum(ss, red);
-  ssq_init_row(o.ssq, o.n_slots, o.slot_stride, r, ss);
+  if (clear_others) ssq_init_row(o.ssq, o.n_slots, o.slot_stride, r, ss);
+  else if (threadIdx.x == 0) o.ssq[r] = (u64)(ss * SSQ_SCALE + 0.5f);
 }
+// Clears the accumulators of rows 0..R-1 but for slot 0 part 0: wave w of block z takes accumulator 4z + w.  (Each row's block
+// clearing its own scatters 8-byte stores over all of them: 520 a row for a 32-layer model, in lines that 16 rows share.  512
+// rows of d 4096 took 10.1 us, 17 rows 8.0; now 8.4 and 4.5.)
+__device__ __forceinline__ void ssq_clear_rows(u64* ssq, int n_slots, int stride, int R, int z) {
+  const int i = z * 4 + (threadIdx.x >> 6);
+  if (i == 0 || i >= n_slots * SSQ_SUB) return;
+  for (int r = threadIdx.x & 63; r < R; r += 64) ssq[(size_t)i * stride + r] = 0ull;
+}
+__host__ __device__ constexpr int ssq_clear_blocks(int n_slots) { return (n_slots * SSQ_SUB + 3) / 4; }
 
-__global__ void embed_w16_kernel(const uint16_t* __restrict__ E, const int* __restrict__ tokens, const int* __restrict__ draft_tok,
-                                 SeqRows sr, int max_seq, int G1, int d, EmbedOut out) {
+// grid R + ssq_clear_blocks, 256 threads
+__global__ __launch_bounds__(256) void embed_w16_kernel(const uint16_t* __restrict__ E, const int* __restrict__ tokens, const int* __restrict__ draft_tok,
+                                 int R, int max_seq, int G1, int d, SeqRows sr, EmbedOut out) {
   __shared__ float red[16];
   const int r = blockIdx.x;
-  const int si = find_seq(sr, r);
-  const int s = sr.seq[si];
-  const int p = sr.pos0[si] + (r - sr.row_off[si]);
-  const int tok = p < sr.len[si] ? tokens[(size_t)s * max_seq + p] : draft_tok[s * G1 + (p - sr.len[si])];
-  embed_row_w16(E + (size_t)tok * d, d, r, out, red);
+  if (r >= R) return ssq_clear_rows(out.ssq, out.n_slots, out.slot_stride, R, r - R);
+  const SeqOf q = seq_of_row(sr, r);
+  const int s = q.seq, p = q.pos0 + (r - q.row0);
+  const int tok = p < q.len ? tokens[(size_t)s * max_seq + p] : draft_tok[s * G1 + (p - q.len)];
+  embed_row_w16(E + (size_t)tok * d, d, r, out, red, false, [] {});
 }
 
 // input rows of the pre-verification layer: x = hidden + PosEmb[e]; operand and ssq as above
-__global__ void mb_input_w16_kernel(const float* __restrict__ src, int lds, const float* __restrict__ posemb, SeqRows sr, MbRows mr,
+// grid R + ssq_clear_blocks, 256 threads
+__global__ __launch_bounds__(256) void mb_input_w16_kernel(const float* __restrict__ src, int lds, const float* __restrict__ posemb, int R,
                                     int d, float* __restrict__ x, int ldx, const float* __restrict__ g, _Float16* __restrict__ xp,
-                                    int MT_total, u64* __restrict__ ssq, int n_slots, int slot_stride) {
+                                    int MT_total, u64* __restrict__ ssq, int n_slots, int slot_stride, SeqRows sr, MbRows mr) {
   __shared__ float red[16];
   const int r = blockIdx.x;
-  const int si = find_seq(sr, r);
-  const int rr = r - sr.row_off[si];
+  if (r >= R) return ssq_clear_rows(ssq, n_slots, slot_stride, R, r - R);
+  const SeqOf q = seq_of_row(sr, r);
+  const int si = q.si, rr = r - q.row0;
   const float* h = src + (size_t)(mr.src_row0[si] + rr) * lds;
   const float* e = posemb + (size_t)(mr.e0[si] < 0 ? 0 : mr.e0[si] + rr) * d;
   float4 a0 = {0.f, 0.f, 0.f, 0.f}, b0 = a0;
@@ -210,7 +237,7 @@ __global__ void mb_input_w16_kernel(const float* __restrict__ src, int lds, cons
     ss += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
   }
   ss = block_sum(ss, red);
-  ssq_init_row(ssq, n_slots, slot_stride, r, ss);
+  if (threadIdx.x == 0) ssq[r] = (u64)(ss * SSQ_SCALE + 0.5f);
 }
 
 // hidden = x * g * row_scale for R rows (prompt ingestion: feeds M_B's prefix rows)
@@ -1131,10 +1158,10 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : HD == 128 ? (MT == 2 ? 2 : 
 
 // ------------------------------------------------------------------ tail of a draft forward
 // one block per listed sequence: hidden state h = x * g_final * row_scale into the ring, and the token
-// = best of the per-tile candidates the LM-head GEMM left.  With E != null the block goes on to what the next draft
+// = best of the per-tile candidates the LM-head GEMM left.  The block goes on to what the next draft
 // step would start with, the embedding of the token it has just chosen (row si of next.x, operand, sums of
 // squares): a launch less per draft step.  The host skips its embedding launch only if that step really comes next.
-__global__ void draft_tail_kernel(const float* x, int ldx, const float* __restrict__ g, const u64* ssq,
+__global__ __launch_bounds__(256) void draft_tail_kernel(const float* x, int ldx, const float* __restrict__ g, const u64* ssq,
                                   int ssq_stride, float inv_dim, float eps, int d, float* __restrict__ hidden, const float* __restrict__ pick_val,
                                   const int* __restrict__ pick_idx, int pick_tiles, int* __restrict__ draft_tok, PickArgs pa, int G1,
                                   const uint16_t* __restrict__ E, EmbedOut next, int V, int* host_bad) {
@@ -1165,12 +1192,14 @@ __global__ void draft_tail_kernel(const float* x, int ldx, const float* __restri
   float* ho = hidden + (size_t)(s * G1 + j) * d;
   float best = -INFINITY;
   int bi = 0x7fffffff;
-  if (in_regs) {
+  auto hidden_from_regs = [&] {
 #pragma unroll
     for (int u = 0; u < XMAX; ++u) {
       const int k = threadIdx.x + u * blockDim.x;
       if (k < d) ho[k] = xv[u] * gv[u] * rs;
     }
+  };
+  if (in_regs) {
 #pragma unroll
     for (int u = 0; u < CMAX; ++u)
       if (cv[u] > best || (cv[u] == best && ci[u] < bi)) { best = cv[u]; bi = ci[u]; }
@@ -1185,7 +1214,8 @@ __global__ void draft_tail_kernel(const float* x, int ldx, const float* __restri
   block_argmax(best, bi, redv, redi);       // (its barriers also separate the reads of x and ssq above from the writes below)
   bi = checked_token(bi, V, threadIdx.x == 0 ? host_bad : nullptr, s);   // candidates without a finite value leave the sentinel
   if (threadIdx.x == 0) draft_tok[s * G1 + j] = bi;
-  if (E) embed_row_w16(E + (size_t)bi * d, d, si, next, red);
+  // the hidden state while the chosen token's embedding is on its way
+  embed_row_w16(E + (size_t)bi * d, d, si, next, red, true, [&] { if (in_regs) hidden_from_regs(); });
 }
 
 // pre-verification head on the un-normalised residual rows: z = (x*g*rs) . cls
@@ -1237,8 +1267,8 @@ __global__ void mb_head_w16_kernel(const float* x, int ldx, const float* __restr
 #pragma unroll
     for (int i = 0; i < SSQ_SUB; ++i) t += sq[i];
     const float rs = 1.0f / sqrtf((float)t * SSQ_INV_SCALE * inv_dim + eps);
-    z0 = wave_sum(z0) * rs;
-    z1 = wave_sum(z1) * rs;
+    z0 = wave_total(z0) * rs;
+    z1 = wave_total(z1) * rs;
     if (lane == 0) al[jj] = 1.0f / (1.0f + expf(z0 - z1));
   }
   __syncthreads();
@@ -1250,5 +1280,5 @@ __global__ void mb_head_w16_kernel(const float* x, int ldx, const float* __restr
   }
   // E != null (single-sequence launches only: row 0 of next.x is one of the rows this block has just read): the
   // embedding of the newest draft token, which the next round's first draft step would start with if drafting goes on
-  if (E) embed_row_w16(E + (size_t)next_tok[0] * d, d, 0, next, red);
+  if (E) embed_row_w16(E + (size_t)next_tok[0] * d, d, 0, next, red, true, [] {});
 }

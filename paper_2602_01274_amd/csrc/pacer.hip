@@ -682,8 +682,9 @@ EmbedOut embed_out(pacer_ctx* c, const Model& m, int R) {
   return o;
 }
 void embed_w16(pacer_ctx* c, const Model& m, int R, const SeqRows& sr) {
-  PACER_LAUNCH(embed_w16_kernel, dim3(R), dim3(256), 0, c->stream, static_cast<const uint16_t*>(m.embed), c->tokens, c->draft_tok, sr,
-               c->max_seq, c->G1, m.cfg.d_model, embed_out(c, m, R));
+  const EmbedOut o = embed_out(c, m, R);
+  PACER_LAUNCH(embed_w16_kernel, dim3(R + ssq_clear_blocks(o.n_slots)), dim3(256), 0, c->stream, static_cast<const uint16_t*>(m.embed), c->tokens, c->draft_tok,
+               R, c->max_seq, c->G1, m.cfg.d_model, sr, o);
 }
 
 struct PickCfg { int on, mode; uint64_t seed; uint32_t step; };
@@ -792,8 +793,8 @@ void run_preverify_rows(pacer_ctx* c, int R, const SeqRows& sr, const MbRows& mr
   const Model& mb = c->m[PACER_PREVERIFY];
   c->pre_valid = false;
   if (is_w16(mb)) {
-    PACER_LAUNCH(mb_input_w16_kernel, dim3(R), dim3(256), 0, c->stream, src, lds, mb.posemb, sr, mr, mb.cfg.d_model, c->x, c->dmax,
-                       mb.attn_norm[0], c->xpA, (R + 15) / 16, c->ssq, 3, c->rcap);
+    PACER_LAUNCH(mb_input_w16_kernel, dim3(R + ssq_clear_blocks(3)), dim3(256), 0, c->stream, src, lds, mb.posemb, R, mb.cfg.d_model, c->x, c->dmax,
+                       mb.attn_norm[0], c->xpA, (R + 15) / 16, c->ssq, 3, c->rcap, sr, mr);
     run_layers_w16(c, mb, 1, R, sr, kv_only);
   } else {
     PACER_LAUNCH(mb_input_kernel, dim3(R), dim3(256), 0, c->stream, src, lds, mb.posemb, sr, mr, mb.cfg.d_model, c->x, c->dmax);
