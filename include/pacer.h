@@ -299,7 +299,8 @@ int32_t pacer_peek(pacer_ctx* ctx, int32_t seq, int32_t what, void** dev_ptr, ui
  * few-tile matrix (fewer than 512 output tiles of 16: the O and down projections) of n_out x n_in
  * weights on `rows` activation rows (1..32) with `operand_parts` f16 parts per activation (1 = hi,
  * 2 = hi + lo): output tiles per block and K slices across blocks (1 = K is not split; with more, the
- * blocks of a tile group add their partial tiles through the workspace).  PACER_EINVAL on a null
+ * blocks of a tile group add their partial tiles through the workspace).  Up to 16 rows over a K that a
+ * block's registers hold take another kernel, which this does not describe.  PACER_EINVAL on a null
  * pointer or sizes outside those bounds. */
 int32_t pacer_launch_plan(int32_t n_out, int32_t n_in, int32_t rows, int32_t operand_parts,
                           int32_t* tiles_per_block, int32_t* k_slices);
