@@ -27,6 +27,22 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// The cross-block hand-overs rest on gfx950 behaviour (see "KSB" at gemm_w16_kernel) and on the encoding of
+// s_waitcnt for that target: refuse to build device code for anything else.
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "these kernels are written for gfx950 (MI355X): the fence-free hand-over and the s_waitcnt immediates are specific to it"
+#endif
+// Memory order of the arrival-counter increment of those hand-overs.  Relaxed by default: ordering comes from the
+// write-through stores having completed (vmcnt 0) before the block's barrier, and from loads that do not hit in L2.
+// Building with -DPACER_FENCED_HANDOVER makes the increment an agent-scope acquire-release (L2 write-back before it,
+// invalidation after it, 4 to 15 us per launch): the variant to compare with if results ever differ between runs.
+#ifdef PACER_FENCED_HANDOVER
+#define PACER_HO_ORDER __ATOMIC_ACQ_REL
+#else
+#define PACER_HO_ORDER __ATOMIC_RELAXED
+#endif
+#define PACER_WAIT_VMCNT0() __builtin_amdgcn_s_waitcnt(0x0F70)   // gfx9 encoding: vmcnt = 0, expcnt and lgkmcnt at their maxima (no wait)
+
 #define PK_MAXB 16
 
 // Rows of a launch: sequence si (slot in the call's list) owns rows row_off[si]..row_off[si+1]-1
@@ -800,9 +816,12 @@ __global__ __launch_bounds__(512) void accept_pick_kernel(const float* tl, const
         if (lane == 0)
           __hip_atomic_store(o + blk * 2 + k, (uint64_t)__float_as_uint(v) | (uint64_t)(uint32_t)id << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt 0: the write-through stores have completed
+      // one wave stores, waits and counts, so there is no barrier that would keep the compiler from moving the counter up
+      asm volatile("" ::: "memory");
+      PACER_WAIT_VMCNT0();                               // the write-through stores have completed
+      asm volatile("" ::: "memory");
       int got = 0;
-      if (lane == 0) got = __hip_atomic_fetch_add(arrivals + sl * G1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (lane == 0) got = __hip_atomic_fetch_add(arrivals + sl * G1, 1, PACER_HO_ORDER, __HIP_MEMORY_SCOPE_AGENT);
       got = __builtin_amdgcn_readfirstlane(got);
       if (got == ACC_PICKERS - 1) {
         static_assert(ACC_PICKERS == 64, "a lane per block");

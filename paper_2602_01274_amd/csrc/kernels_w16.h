@@ -29,22 +29,6 @@
 #pragma once
 #include "kernels.h"
 
-// The cross-block hand-overs below rest on gfx950 behaviour (see "KSB" at gemm_w16_kernel) and on the encoding of
-// s_waitcnt for that target: refuse to build device code for anything else.
-#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
-#error "kernels_w16.h is written for gfx950 (MI355X): the fence-free hand-over and the s_waitcnt immediates are specific to it"
-#endif
-// Memory order of the arrival-counter increment of those hand-overs.  Relaxed by default: ordering comes from the
-// write-through stores having completed (vmcnt 0) before the block's barrier, and from loads that do not hit in L2.
-// Building with -DPACER_FENCED_HANDOVER makes the increment an agent-scope acquire-release (L2 write-back before it,
-// invalidation after it, 4 to 15 us per launch): the variant to compare with if results ever differ between runs.
-#ifdef PACER_FENCED_HANDOVER
-#define PACER_HO_ORDER __ATOMIC_ACQ_REL
-#else
-#define PACER_HO_ORDER __ATOMIC_RELAXED
-#endif
-#define PACER_WAIT_VMCNT0() __builtin_amdgcn_s_waitcnt(0x0F70)   // gfx9 encoding: vmcnt = 0, expcnt and lgkmcnt at their maxima (no wait)
-
 #define PACK_PLAIN 0
 #define PACK_QKV 1
 #define PACK_GATEUP 2
